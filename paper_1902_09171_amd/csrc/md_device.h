@@ -73,7 +73,7 @@ struct CellDev {
   float hs2;                      // squared (measured) displacement that still keeps the list complete
   float dmax2;                    // largest squared measured displacement since the last build, as last reduced
   float qeps;                     // bound on the error of a measured displacement: the 16-bit build reference
-  int pad3;
+  float list_lo2, list_hi2;       // list build: |d|^2 from FP32 offsets surely below / above (rc + skin)^2
   // molecular statics (FIRE): time step, mixing parameter, the velocity update of this iteration
   // (v = fa v + fb f, or zero when frozen), iterations since the power last turned negative,
   // converged flag and iterations used
@@ -143,12 +143,11 @@ struct MDArgs {
   const Tile* tiles;
   Part* parts;
   int ntiles, ncells;
-  int* abin; int* bcount; int* bstart; int* bnum; int* bfill; int* binned; int* sort_tmp;
-  long long bins_total;
-  // work list of the rebuild phases (k_rebuild_work): the cells flagged for a rebuild in cell
-  // order, and the exclusive prefix sums of their tiles and of their 64-bin chunks (ncell + 1
-  // entries each); work_count[0..2] = cells, tiles, chunks
-  int *work_cells, *work_tstart, *work_kstart, *work_count;
+  int* abin; int* bcount; int* bstart; int* bnum; int* bfill; int* binned; int* bkey;
+  // work list of the rebuild phases: the cells flagged for a rebuild and the exclusive prefix sums of
+  // their tiles; *work_pack = cells << 32 | tiles (work_add, k_rebuild_work)
+  int *work_cells, *work_tstart;
+  unsigned long long* work_pack;
   int bin_factor;                  // bins at least (rc + skin) / bin_factor wide; stencil +- bin_factor
   // integrator constants (computed once on the host, documented expressions)
   double dt, h, drag, c24, mmv, half_skin2, rcs2;
@@ -539,6 +538,19 @@ __device__ __forceinline__ int wave_min(int v) {
   return v;
 }
 
+// Inclusive prefix sum over the 64 lanes of a wave: row shifts by 1, 2, 4, 8 inside the 16-lane rows, then
+// the row totals broadcast onwards (lanes without a source add 0).  Six register-to-register adds,
+// where shuffles took six round trips through the LDS crossbar.
+__device__ __forceinline__ int wave_inclusive_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1, 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2, 3
+  return v;
+}
+
 // the same trees over the lanes whose index is a multiple of L only (the other lanes hold zeros):
 // lane 0 receives the result
 template <int L, class T>
@@ -637,6 +649,10 @@ __device__ __forceinline__ void add_virial(double w[6], double gr, const double 
   w[3] = fma(t0, dd[1], w[3]); w[4] = fma(t0, dd[2], w[4]); w[5] = fma(t1, dd[2], w[5]);
 }
 
+// an empty list, by the kernel that runs before the reduction that fills it
+__device__ __forceinline__ void work_clear(const MDArgs& a) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *a.work_pack = 0;
+}
 // ------------------------------------------------------------------ force kernels
 // List entries of one trip: UNR consecutive entries of one list block, as 32-bit words loaded with
 // one vector load (the trip's first entry is a multiple of UNR, so they are aligned).
@@ -698,6 +714,7 @@ __global__ __launch_bounds__(TILE * TPA) void k_force_kg(MDArgs a, int mode) {
   using R = typename P::R;
   constexpr int NT = TILE * TPA;
   __shared__ PartShared<NT / 64> psh;
+  work_clear(a);
   const int tb = block_tile_xcd(a.ntiles, blockIdx.x);
   if (tb >= a.ntiles) return;
   const Tile t = a.tiles[tb];
@@ -864,6 +881,7 @@ __global__ __launch_bounds__(TILE * TPA) void k_force_eam(MDArgs a, int mode) {
   using R = typename P::R;
   constexpr int NT = TILE * TPA;
   __shared__ PartShared<NT / 64> psh;
+  work_clear(a);
   const int tb = block_tile_xcd(a.ntiles, blockIdx.x);
   if (tb >= a.ntiles) return;
   const Tile t = a.tiles[tb];
@@ -954,6 +972,7 @@ __global__ __launch_bounds__(TILE * TPA) void k_force_eam(MDArgs a, int mode) {
 template <class P>
 __global__ __launch_bounds__(TILE) void k_start(MDArgs a) {
   __shared__ PartShared<1> psh;
+  work_clear(a);
   const int tb = block_tile(a.ntiles, blockIdx.x);
   if (tb >= a.ntiles) return;
   const Tile t = a.tiles[tb];
@@ -1057,6 +1076,7 @@ __global__ __launch_bounds__(TILE) void k_zero_v(MDArgs a) {
 template <class P>
 __global__ __launch_bounds__(TILE) void k_fire_move(MDArgs a) {
   __shared__ PartShared<1> psh;
+  work_clear(a);
   const int tb = block_tile(a.ntiles, blockIdx.x);
   if (tb >= a.ntiles) return;
   const Tile t = a.tiles[tb];
@@ -1096,6 +1116,13 @@ __global__ void k_fire_iters(const CellDev* cells, int ncells, int* iters, int* 
   done[c] = cells[c].fdone;
 }
 
+// one thread enters a cell into the work list: one atomic hands out its place and its first tile
+// together, so both arrays increase together whatever order the cells come in
+__device__ __forceinline__ void work_add(const MDArgs& a, int cell, int ntile) {
+  const unsigned long long old = atomicAdd(a.work_pack, (1ull << 32) | (unsigned)ntile);
+  a.work_cells[old >> 32] = cell;
+  a.work_tstart[old >> 32] = (int)(unsigned)old;
+}
 // Per-cell reduction of the tile partials: one wave per cell.  Lane t sums every 64th tile in
 // order; the 64 lane sums of each of the 10 summed quantities (V, pe, xi) are then added through
 // LDS in a fixed two-level order (four groups of 16 lanes, then the four group sums in order), so
@@ -1109,7 +1136,7 @@ struct RedShared {
   double col[RED_Q][RED_NT + 1];
   double grp[4][RED_Q];
 };
-__device__ __forceinline__ void reduce_cell(const MDArgs& a, int cell, int mode, RedShared& sh) {
+__device__ __forceinline__ void reduce_cell(const MDArgs& a, int cell, int mode, RedShared& sh, int fill) {
   CellDev& C = a.cells[cell];
   auto& col = sh.col;
   auto& grp = sh.grp;
@@ -1175,6 +1202,7 @@ __device__ __forceinline__ void reduce_cell(const MDArgs& a, int cell, int mode,
             __double_as_longlong(grp[2][7 + q]) + __double_as_longlong(grp[3][7 + q]);
   const long long x0 = xs[0], x1 = xs[1], x2 = xs[2];
   if (st != 0 && cstatus == 0) C.status = st;
+  if (fill && md > chs2) work_add(a, cell, ntile);
   if (mode == RED_MOVE) {                // statics: positions moved; rebuild when they left the skin
     C.rebuild = md > chs2;
     C.dmax2 = md;
@@ -1183,7 +1211,7 @@ __device__ __forceinline__ void reduce_cell(const MDArgs& a, int cell, int mode,
   if (mode == RED_STATIC) {              // statics: one FIRE decision per cell (same order as the oracle)
     C.pe = r[6];
     const double P = r[0], F2 = r[1], V2 = r[2];
-    if ((double)md <= a.fire_ftol2 || st != 0 || C.fiter >= a.fire_max_iter) { C.fdone = 1; return; }
+    if ((double)md <= a.fire_ftol2 || st != 0 || C.fiter >= a.fire_max_iter) { C.fdone = 1; C.rebuild = 0; return; }
     if (P > 0.0) {
       if (++C.fcount > 5) { C.fdt = fmin(1.1 * C.fdt, 10.0 * a.dt); C.falpha *= 0.99; }
       C.fa = 1.0 - C.falpha;
@@ -1233,20 +1261,20 @@ __device__ __forceinline__ void reduce_cell(const MDArgs& a, int cell, int mode,
   }
 }
 
-__global__ __launch_bounds__(RED_NT) void k_reduce(MDArgs a, int mode) {
+// fill: the reductions that flag rebuilds (RED_START, RED_STEP, RED_MOVE) enter them into the work list
+__global__ __launch_bounds__(RED_NT) void k_reduce(MDArgs a, int mode, int fill) {
   __shared__ RedShared sh;
-  reduce_cell(a, blockIdx.x, mode, sh);
+  reduce_cell(a, blockIdx.x, mode, sh, fill);
 }
 
 // ------------------------------------------------------------------ neighbour build
-// Neighbour build of the cells flagged for a rebuild, in four phases (each kernel exits at
-// once for cells that are not flagged):
+// Neighbour build of the cells flagged for a rebuild, in phases:
 //   k_bin        per atom: wrap into the box, fixed-point S and the build reference, bin index
 //                in scaled space, histogram (tiles)
 //   k_bin_scan   exclusive scan of the histogram (one block per cell)
-//   k_bin_fill   scatter of cell-local indices into their bins (tiles)
-//   k_bin_sort   order every bin by atom index (one thread per bin), so that the neighbour lists
-//                and the force sums built from them are deterministic
+//   k_bin_fill   scatter of cell-local and original indices into their bins (tiles)
+//   k_reorder_gather, k_build_list   the atoms in (bin, original index) order, so that the neighbour
+//                lists and the force sums built from them are deterministic, then the lists
 // atomicAdd(ctr + key, 1) for every valid lane of the wave, one atomic per run of equal keys in
 // consecutive lanes: the atoms of a tile are stored in bin order from the last build and have
 // mostly stayed in their bins, so neighbouring lanes usually share a key.  The run's first lane
@@ -1301,24 +1329,31 @@ __device__ __forceinline__ void bin_atom(const MDArgs& a, const CellDev& C, long
 // block-strided over the tiles of the rebuilding cells, so a step in which few cells rebuild
 // launches a small grid instead of one block per tile of the batch.
 constexpr int WORK_WAVES = 4;
-// the k with start[k] <= w < start[k + 1] in a strictly increasing prefix array of n + 1 entries
+__device__ __forceinline__ int work_cells_n(const MDArgs& a) { return (int)(*a.work_pack >> 32); }
+__device__ __forceinline__ int work_tiles_n(const MDArgs& a) { return (int)(unsigned)*a.work_pack; }
+// The last k with start[k] <= w in a strictly increasing array of n entries from 0, for a w common to
+// the wave: every lane looks at one entry of 64 (one round trip up to 64 cells, where bisection takes
+// one per halving).
 __device__ __forceinline__ int work_find(const int* start, int n, int w) {
-  int lo = 0, hi = n - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (start[mid] <= w) lo = mid; else hi = mid - 1;
+  const int lane = (int)(threadIdx.x & 63u);
+  int lo = 0;
+  while (n > 1) {
+    const int step = (n + 63) / 64, e = lane * step;
+    const int below = __builtin_popcountll(__builtin_amdgcn_ballot_w64(e < n && start[lo + min(e, n - 1)] <= w)) - 1;
+    lo += below * step;
+    n = min(step, n - below * step);
   }
   return lo;
 }
 // batch tile index of the w-th tile of the rebuild work list
 __device__ __forceinline__ int work_tile(const MDArgs& a, int w) {
-  const int k = work_find(a.work_tstart, a.work_count[0], w);
+  const int k = work_find(a.work_tstart, work_cells_n(a), w);
   return a.cells[a.work_cells[k]].tile_off + (w - a.work_tstart[k]);
 }
 template <class Fn>
 __device__ __forceinline__ void for_work_tiles(const MDArgs& a, Fn&& fn) {
   const int lane = threadIdx.x & 63;
-  const XcdLoop L(a.work_count[1], WORK_WAVES, threadIdx.x >> 6);
+  const XcdLoop L(work_tiles_n(a), WORK_WAVES, threadIdx.x >> 6);
   for (int k = L.k; k < L.end; k += L.step) {
     const Tile t = a.tiles[work_tile(a, k)];
     if (lane < t.count) fn(t, (long long)t.begin + lane);
@@ -1328,7 +1363,7 @@ __device__ __forceinline__ void for_work_tiles(const MDArgs& a, Fn&& fn) {
 template <class Fn>
 __device__ __forceinline__ void for_work_tiles_wave(const MDArgs& a, Fn&& fn) {
   const int lane = threadIdx.x & 63;
-  const XcdLoop L(a.work_count[1], WORK_WAVES, threadIdx.x >> 6);
+  const XcdLoop L(work_tiles_n(a), WORK_WAVES, threadIdx.x >> 6);
   for (int k = L.k; k < L.end; k += L.step) {
     const Tile t = a.tiles[work_tile(a, k)];
     const bool valid = lane < t.count;
@@ -1351,32 +1386,31 @@ __device__ __forceinline__ float measured_threshold(double hs2, float qeps) {
 
 constexpr int SCAN_NT = 1024;
 // Exclusive scan of one value per thread over a block of SCAN_NT threads: an inclusive scan inside
-// each wave by shuffles, the 16 wave totals scanned by the first wave through LDS (wsum: 16 ints),
-// two barriers.  Returns the exclusive prefix; *total receives the block's sum.
+// each wave, the 16 wave totals through LDS (wsum: 16 ints) scanned again by every wave, two barriers.  Returns the exclusive prefix; *total receives the block's sum.
 __device__ __forceinline__ int block_exscan(int v, int* wsum, int* total) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  int inc = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(inc, o);
-    if (lane >= o) inc += y;
-  }
+  const int inc = wave_inclusive_scan(v);
   if (lane == 63) wsum[wv] = inc;
   __syncthreads();
-  if (wv == 0) {
-    int w = lane < SCAN_NT / 64 ? wsum[lane] : 0;
-#pragma unroll
-    for (int o = 1; o < SCAN_NT / 64; o <<= 1) {
-      const int y = __shfl_up(w, o);
-      if (lane >= o) w += y;
-    }
-    if (lane < SCAN_NT / 64) wsum[lane] = w;
-  }
-  __syncthreads();
-  const int before = wv > 0 ? wsum[wv - 1] : 0;
-  *total = wsum[SCAN_NT / 64 - 1];
+  // every wave scans the wave totals for itself
+  const int w = wave_inclusive_scan(lane < SCAN_NT / 64 ? wsum[lane] : 0);
+  const int before = wv > 0 ? __builtin_amdgcn_readlane(w, wv - 1) : 0;
+  *total = __builtin_amdgcn_readlane(w, SCAN_NT / 64 - 1);
   __syncthreads();                 // wsum is reused by the next call
   return before + inc - v;
+}
+
+// Bounds on |d|^2 for the list build's FP32 test (build_bin).  A candidate's or an atom's offset from
+// the bin's first atom is at most pm in each component (three bins in every dimension) and is rounded
+// once, their difference once more, so a component of d is off by at most 3 2^-24 pm and |d|^2 by at most
+// 2 sqrt(3) (rc + skin) times that, plus its own rounding; doubled.
+__device__ __forceinline__ void list_band(const MDArgs& a, CellDev& C) {
+  const double b0 = 3.0 / C.nb[0], b1 = 3.0 / C.nb[1], b2 = 3.0 / C.nb[2];
+  const double px = fabs(C.H[0]) * b0 + fabs(C.H[1]) * b1 + fabs(C.H[2]) * b2;
+  const double py = fabs(C.H[4]) * b1 + fabs(C.H[5]) * b2, pm = fmax(px, fmax(py, fabs(C.H[8]) * b2));
+  const double band = 0x1.0p-23 * (10.4 * sqrt(a.rcs2) * pm + 4.0 * a.rcs2);
+  C.list_lo2 = (float)(a.rcs2 - band);
+  C.list_hi2 = (float)(a.rcs2 + band);
 }
 
 // exclusive scan of one cell's histogram by a block of SCAN_NT threads (sh: at least 16 ints of LDS)
@@ -1388,6 +1422,7 @@ __device__ __forceinline__ void scan_cell(const MDArgs& a, CellDev& C, int* sh) 
     for (int q = 0; q < 6; ++q) C.Hb[q] = C.H[up[q]];
     C.hs2 = measured_threshold(a.half_skin2, C.qeps);
     C.dmax2 = 0.f;
+    list_band(a, C);
   }
   int carry = 0;
   for (int base = 0; base < nbins; base += SCAN_NT) {   // coalesced chunks of SCAN_NT bins
@@ -1409,152 +1444,59 @@ __device__ __forceinline__ void scan_cell(const MDArgs& a, CellDev& C, int* sh) 
 // one block per rebuilding cell, block-strided over the work list
 __global__ __launch_bounds__(SCAN_NT) void k_bin_scan(MDArgs a) {
   __shared__ int sh[SCAN_NT / 64];
-  const XcdLoop L(a.work_count[0]);
+  const XcdLoop L(work_cells_n(a));
   for (int k = L.k; k < L.end; k += L.step) scan_cell(a, a.cells[a.work_cells[k]], sh);
 }
 
-// The work list of a rebuild: the cells flagged for one, in cell order, with the prefix sums of
-// their tiles and of their 64-bin chunks (a cell's bins start at a multiple of 64, so a chunk
-// belongs to one cell).  One block of SCAN_NT threads: exclusive scans of the flags and counts.
+// The work list of a rebuild outside the MD steps (in a step the reduction that flags a cell enters
+// it): the cells flagged for one, in cell order.  One block of SCAN_NT threads: exclusive scans of the
+// flags and tile counts.
 __global__ __launch_bounds__(SCAN_NT) void k_rebuild_work(MDArgs a) {
   __shared__ int sh[SCAN_NT / 64];
-  int bc = 0, bt = 0, bk = 0;
+  int bc = 0, bt = 0;
   for (int c0 = 0; c0 < a.ncells; c0 += SCAN_NT) {
     const int c = c0 + threadIdx.x;
-    int fl = 0, nt = 0, nk = 0;
-    if (c < a.ncells) {
-      const CellDev& C = a.cells[c];
-      if (C.rebuild) {
-        fl = 1;
-        nt = C.ntile;
-        nk = (C.nb[0] * C.nb[1] * C.nb[2] + 63) / 64;
-      }
+    int fl = 0, nt = 0;
+    if (c < a.ncells && a.cells[c].rebuild) {
+      fl = 1;
+      nt = a.cells[c].ntile;
     }
-    int tc, tt, tk;
+    int tc, tt;
     const int ec = block_exscan(fl, sh, &tc);
     const int et = block_exscan(nt, sh, &tt);
-    const int ek = block_exscan(nk, sh, &tk);
     if (fl) {
       a.work_cells[bc + ec] = c;
       a.work_tstart[bc + ec] = bt + et;
-      a.work_kstart[bc + ec] = bk + ek;
     }
-    bc += tc; bt += tt; bk += tk;
+    bc += tc; bt += tt;
   }
-  if (threadIdx.x == 0) {
-    a.work_tstart[bc] = bt;
-    a.work_kstart[bc] = bk;
-    a.work_count[0] = bc; a.work_count[1] = bt; a.work_count[2] = bk;
-  }
+  if (threadIdx.x == 0) *a.work_pack = ((unsigned long long)bc << 32) | (unsigned)bt;
+}
+
+// a bin's index in its cell from its packed coordinates
+__device__ __forceinline__ int bin_index(const CellDev& C, int pk) {
+  return ((pk & BIN_MASK) * C.nb[1] + ((pk >> BIN_BITS) & BIN_MASK)) * C.nb[2] + (pk >> (2 * BIN_BITS));
 }
 
 __device__ __forceinline__ void fill_atom(const MDArgs& a, const CellDev& C, long long i, bool valid) {
-  int bin = -1;
-  if (valid) {
-    const int pk = a.abin[i];
-    bin = ((pk & BIN_MASK) * C.nb[1] + ((pk >> BIN_BITS) & BIN_MASK)) * C.nb[2] + (pk >> (2 * BIN_BITS));
-  }
+  const int bin = valid ? bin_index(C, a.abin[i]) : -1;
   const int slot = wave_run_add(a.bfill + C.bin_off, bin, valid);
-  if (valid) a.binned[C.off + a.bstart[C.bin_off + bin] + slot] = (int)(i - C.off);
+  if (valid) {
+    const long long q = C.off + a.bstart[C.bin_off + bin] + slot;
+    a.binned[q] = (int)(i - C.off);
+    a.bkey[q] = a.gid[i];
+  }
 }
 
 __global__ __launch_bounds__(TILE * WORK_WAVES) void k_bin_fill(MDArgs a) {
   for_work_tiles_wave(a, [&](const Tile& t, long long i, bool valid) { fill_atom(a, a.cells[t.cell], i, valid); });
 }
 
-// one lane per bin slot of every cell (grid over the bin capacity), one wave per block.  Each bin
-// is ordered by the original index (gid) of its atoms, so that the reorder that follows depends
-// only on positions, not on earlier reorders.  When the wave's 64 bins fit in the cap keys of
-// dynamic LDS (sized by the host from the expected bin occupancy) their keys are staged there and every lane rank-sorts its own bin (key v goes to position
-// #{keys < v}; keys are distinct); otherwise bins of up to SMALL_BIN atoms are insertion-sorted by
-// their lane and larger bins are rank-sorted by the whole wave, one after another, through the
-// scratch array.  Sorted keys are mapped back to current cell-local indices through pos_of.
-constexpr int SMALL_BIN = 24;
-constexpr int SORT_LDS_MAX = 16384;  // staged keys per wave at most (64 KB)
-__device__ __forceinline__ void sort_chunk(const MDArgs& a, const int* bin_cell, int cap, long long g, int* stage) {
-  int big = 0;                       // this lane's bin needs the wave
-  int *p = nullptr, n = 0, off = 0;
-  {
-    const int c = bin_cell[g];
-    const CellDev& C = a.cells[c];
-    const int b = (int)(g - C.bin_off);
-    if (b < C.nb[0] * C.nb[1] * C.nb[2]) {
-      p = a.binned + C.off + a.bstart[g];
-      n = a.bnum[g];
-      off = C.off;
-    }
-  }
-  int incl = n;                      // exclusive offsets of the 64 bins in the staging array
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int v = __shfl_up(incl, o);
-    if ((int)threadIdx.x >= o) incl += v;
-  }
-  const int total = __shfl(incl, 63);
-  if (total == 0) return;
-  if (total <= cap) {
-    int* sk = stage + (incl - n);
-    for (int e = 0; e < n; ++e) sk[e] = a.gid[off + p[e]];
-    __syncthreads();
-    for (int e = 0; e < n; ++e) {
-      const int v = sk[e];
-      int rank = 0;
-      for (int q = 0; q < n; ++q) rank += sk[q] < v;
-      p[rank] = a.pos_of[off + v];
-    }
-    return;
-  }
-  for (int e = 0; e < n; ++e) p[e] = a.gid[off + p[e]];     // sort keys in place
-  big = n > SMALL_BIN;
-  if (!big)
-    for (int u = 1; u < n; ++u) {
-      const int v = p[u];
-      int q = u - 1;
-      while (q >= 0 && p[q] > v) { p[q + 1] = p[q]; --q; }
-      p[q + 1] = v;
-    }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __syncthreads();
-  // large bins, one after another, by all 64 lanes
-  unsigned long long mask = __ballot(big);
-  while (mask) {
-    const int src = __ffsll((long long)mask) - 1;
-    mask &= mask - 1;
-    int* pb = (int*)__shfl((long long)(size_t)p, src);
-    const int m = __shfl(n, src);
-    int* tmp = a.sort_tmp + (pb - a.binned);
-    for (int e = threadIdx.x; e < m; e += 64) {
-      const int v = pb[e];
-      int rank = 0;
-      for (int q = 0; q < m; ++q) rank += pb[q] < v;
-      tmp[rank] = v;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __syncthreads();
-    for (int e = threadIdx.x; e < m; e += 64) pb[e] = tmp[e];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __syncthreads();
-  }
-  for (int e = 0; e < n; ++e) p[e] = a.pos_of[off + p[e]];  // keys back to current indices
-}
-
-// one wave per 64-bin chunk of the rebuilding cells, block-strided over the work list
-__global__ __launch_bounds__(64) void k_bin_sort(MDArgs a, const int* bin_cell, int cap) {
-  extern __shared__ int stage[];
-  const XcdLoop L(a.work_count[2]);
-  for (int w = L.k; w < L.end; w += L.step) {
-    __syncthreads();                 // the previous chunk's keys have been read
-    const int k = work_find(a.work_kstart, a.work_count[0], w);
-    const long long chunk = a.cells[a.work_cells[k]].bin_off / 64 + (w - a.work_kstart[k]);
-    sort_chunk(a, bin_cell, cap, chunk * 64 + threadIdx.x, stage);
-  }
-}
-
-// Reorder the atoms of every rebuilding cell by (bin, original index): position q of the cell
-// receives the atom binned[q].  Phase 1 gathers positions, velocities, the fixed-point coordinates,
-// bin coordinates and original indices into the scratch rows and records pos_of; phase 2 copies
-// them back (also as the build reference) and rewrites the bond partners from bond0 through pos_of
-// (inside the list build, or as the last phase of the one-block-per-cell preparation).
+// Reorder the atoms of every rebuilding cell by (bin, original index), so that the order depends only
+// on positions, not on earlier reorders.  Phase 1 moves positions, velocities, the fixed-point
+// coordinates, bin coordinates and original indices into the scratch rows and records pos_of; phase 2
+// copies them back (also as the build reference) and rewrites the bond partners from bond0 through
+// pos_of (inside the list build, or as the last phase of the one-block-per-cell preparation).
 // The stored total force is not moved: the prime or last step of the run writes it afterwards.
 template <class P>
 struct Reorder {
@@ -1577,9 +1519,9 @@ __device__ __forceinline__ void store_bonds(const MDArgs& a, long long i, int b0
     ((int4*)a.bond)[i] = make_int4(b0, b1, b2, b3);
 }
 
+// the atom `src` (batch position) to the scratch row q
 template <class P>
-__device__ __forceinline__ void reorder_gather_atom(const MDArgs& a, const CellDev& C, long long q) {
-  const long long src = C.off + a.binned[q];
+__device__ __forceinline__ void reorder_gather_atom(const MDArgs& a, const CellDev& C, long long src, long long q) {
   const Reorder<P> r(a);
   r.x[q] = a.x[src]; r.y[q] = a.y[src]; r.z[q] = a.z[src];
   r.vx[q] = a.vx[src]; r.vy[q] = a.vy[src]; r.vz[q] = a.vz[src];
@@ -1590,9 +1532,24 @@ __device__ __forceinline__ void reorder_gather_atom(const MDArgs& a, const CellD
   a.pos_of[C.off + g] = (int)(q - C.off);
 }
 
+// Phase 1 over the bin slots, in whatever order the fill left a bin's atoms: a slot's place in its bin
+// is the number of smaller keys (original indices, distinct) there.  Every lane ranks its own atom, a
+// handful of key reads that its neighbours in the bin share, where one lane per bin took a serial
+// sort of the whole bin in a launch of its own: 12.6 us per MD step for 100 cells of 10^4 beads at ~5
+// atoms per bin, 48 us for 50 glassy cells at ~19, against nothing and +1 us of this kernel.
 template <class P>
 __global__ __launch_bounds__(TILE * WORK_WAVES) void k_reorder_gather(MDArgs a) {
-  for_work_tiles(a, [&](const Tile& t, long long i) { reorder_gather_atom<P>(a, a.cells[t.cell], i); });
+  for_work_tiles(a, [&](const Tile& t, long long q) {
+    const CellDev& C = a.cells[t.cell];
+    const long long src = C.off + a.binned[q];
+    const int v = a.bkey[q];
+    const int bin = C.bin_off + bin_index(C, a.abin[src]);
+    const int beg = a.bstart[bin], m = a.bnum[bin];
+    const int* key = a.bkey + C.off + beg;
+    int rank = 0;
+    for (int e = 0; e < m; ++e) rank += key[e] < v;
+    reorder_gather_atom<P>(a, C, src, (long long)C.off + beg + rank);
+  });
 }
 
 template <class P>
@@ -1634,7 +1591,7 @@ __device__ __forceinline__ void prep_cell(const MDArgs& a, int cell, int* sh, in
     fill_atom(a, C, (long long)C.off + (v ? l0 + t : 0), v);
   }
   __syncthreads();
-  for (int q = t; q < n; q += SCAN_NT) key[q] = a.gid[C.off + a.binned[C.off + q]];
+  for (int q = t; q < n; q += SCAN_NT) key[q] = a.bkey[C.off + q];
   __syncthreads();
   const int nbins = C.nb[0] * C.nb[1] * C.nb[2];
   for (int b = t; b < nbins; b += SCAN_NT) {
@@ -1647,7 +1604,7 @@ __device__ __forceinline__ void prep_cell(const MDArgs& a, int cell, int* sh, in
     }
   }
   __syncthreads();
-  for (int q = t; q < n; q += SCAN_NT) reorder_gather_atom<P>(a, C, (long long)C.off + q);
+  for (int q = t; q < n; q += SCAN_NT) reorder_gather_atom<P>(a, C, (long long)C.off + a.binned[C.off + q], (long long)C.off + q);
   __syncthreads();
   for (int q = t; q < n; q += SCAN_NT) reorder_scatter_atom<P>(a, C, (long long)C.off + q);
 }
@@ -1668,7 +1625,7 @@ __global__ __launch_bounds__(SCAN_NT) void k_reduce_prep(MDArgs a, int mode) {
   __shared__ RedShared rsh;
   __shared__ int sh[SCAN_NT];
   __shared__ int key[PREP_ATOMS];
-  reduce_cell(a, blockIdx.x, mode, rsh);
+  reduce_cell(a, blockIdx.x, mode, rsh, 1);
   __syncthreads();
   if (!__hip_atomic_load(&a.cells[blockIdx.x].rebuild, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
   prep_cell<P>(a, blockIdx.x, sh, key);
@@ -1691,17 +1648,19 @@ __global__ __launch_bounds__(TILE) void k_reset_order(MDArgs a, int first, int c
 
 // Verlet list of every atom (after the reorder, so positions are in bin order): cell-local j with
 // |d| < rc + skin over the neighbour bins b - f ... b + f of every dimension (bins at least
-// (rc + skin) / f wide).  Because the atoms are stored in bin order and bins are numbered with z
-// fastest, the z-neighbour bins of each (x, y) column of the stencil are one contiguous range of
-// positions (two at the periodic edge in z).  One lane per atom walks its ranges in stencil order,
-// UNR candidates in flight, and appends every accepted one to its list: the list comes out in
-// candidate order (nearly sorted by position, so its gathers hit few cache lines) and is
-// deterministic.  A range's bounds come from the bin table while the previous range is walked.  The
-// atoms of a wave are 64 consecutive atoms of one cell, mostly of a few neighbouring bins, so at a
-// given step their lanes read the same or nearby positions.
+// (rc + skin) / f wide), in candidate order: the (x, y) columns of the stencil in turn, each column's
+// z-neighbour bins one contiguous range of positions (two at the periodic edge in z), because the atoms
+// are stored in bin order and bins are numbered with z fastest.  The lists come out nearly sorted by
+// position (the force pass's gathers hit few cache lines) and deterministic.
+//
+// The atoms of one bin have the same candidates, so a wave takes a bin at a time: its lanes hold the
+// candidates (64 per round, up to BLD_ROUNDS rounds in registers), read once with coalesced loads
+// and turned into Cartesian offsets from the bin's first atom, and every atom of the bin in turn is
+// broadcast against them.  The 64-bit mask of a comparison is the accepted candidates in order: an
+// accepted lane's place is the running count plus the accepted lanes below it.  No lane waits for a
+// longer range of its neighbours', and a cell of 10^4 beads gives ~2200 waves instead of 157.
 constexpr int MAX_BIN_FACTOR = 2;
-constexpr int BUILD_WAVES = 4;     // tiles per block of the list build, one per wave
-struct BuildGeo {                  // one atom's stencil: bins per dimension and the z ranges
+struct BuildGeo {                  // a bin's stencil: bins per dimension and the z ranges
   int lo[3], cnt[3], nb[3];        // first neighbour bin (unwrapped) and count per dimension
   int zr[2][2], nzr;               // z bins [z0, z1] of every column, or two such ranges
   int ncol, nrange;
@@ -1727,185 +1686,237 @@ __device__ __forceinline__ void build_geo(const CellDev& C, int pk, int fb, Buil
   G.ncol = G.cnt[0] * G.cnt[1];
   G.nrange = G.ncol * G.nzr;
 }
+// a lane's value, in every lane
+__device__ __forceinline__ float lane_value(float v, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+template <class P>
+__device__ __forceinline__ typename P::S lane_value_s(const typename P::S& v, int l) {
+  typename P::S r;
+  int w[sizeof(v) / 4];
+  __builtin_memcpy(w, &v, sizeof(v));
+#pragma unroll
+  for (int q = 0; q < (int)(sizeof(v) / 4); ++q) w[q] = __builtin_amdgcn_readlane(w[q], l);
+  __builtin_memcpy(&r, w, sizeof(v));
+  return r;
+}
+// whether a pair is listed: |d|^2 below (rc + skin)^2, from the separation that the pair passes form
+template <class P>
+__device__ __forceinline__ bool exact_in(const typename P::S& sj, const typename P::S& si, const typename P::Geo& g,
+                                         typename P::R rcs2) {
+  typename P::R d[3];
+  P::sep(sj, si, g, d);
+  return d[0] * d[0] + d[1] * d[1] + d[2] * d[2] < rcs2;
+}
+
 // range r of the stencil (column-major over x, y, then the z parts): first position and count
 __device__ __forceinline__ int2 build_range(const MDArgs& a, const CellDev& C, const BuildGeo& G, int r) {
-  const int col = r / G.nzr, part = r - col * G.nzr;
-  const int u0 = col / G.cnt[1], u1 = col - u0 * G.cnt[1];
+  const int col = G.nzr == 2 ? r >> 1 : r, part = G.nzr == 2 ? r & 1 : 0;
+  // col / cnt[1] for col < 64 and cnt[1] <= 2 MAX_BIN_FACTOR + 1
+  const int inv = G.cnt[1] == 1 ? 65536 : G.cnt[1] == 2 ? 32768 : G.cnt[1] == 3 ? 21846 : G.cnt[1] == 4 ? 16384 : 13108;
+  const int u0 = (col * inv) >> 16, u1 = col - u0 * G.cnt[1];
   int x = G.lo[0] + u0, y = G.lo[1] + u1;
   x = x < 0 ? x + G.nb[0] : (x >= G.nb[0] ? x - G.nb[0] : x);
   y = y < 0 ? y + G.nb[1] : (y >= G.nb[1] ? y - G.nb[1] : y);
   const int bc = C.bin_off + (x * G.nb[1] + y) * G.nb[2];
-  const int bf = bc + G.zr[part][0], bl = bc + G.zr[part][1];
+  const int bf = bc + (part ? G.zr[1][0] : G.zr[0][0]), bl = bc + (part ? G.zr[1][1] : G.zr[0][1]);
   const int beg = a.bstart[bf];
   return make_int2(beg, a.bstart[bl] + a.bnum[bl] - beg);
 }
-// The reorder's second half for this atom happens here (its row copied from the reorder scratch to
-// the per-atom arrays, bond partners renumbered), and the candidates are read from the scratch, which
-// holds the same reordered coordinates: no other lane reads the arrays being written, and the
-// rebuild needs no separate scatter launch.
-template <class P, class LT>
-__device__ __forceinline__ void build_tile(const MDArgs& a, const Tile& t, int slot) {
-  if (slot >= t.count) return;
-  const CellDev& C = a.cells[t.cell];
-  const long long i = (long long)t.begin + slot;
-  const int li = (int)(i - C.off);
-  const Reorder<P> ro(a);
-  reorder_scatter_atom<P>(a, C, i);
-  const typename P::S* sbase = (const typename P::S*)ro.s;
-  const typename P::S si = sbase[i];
+
+constexpr int BLD_WAVES = 4;       // waves per block of the list build
+constexpr int BLD_ROUNDS = 3;      // rounds of 64 candidates held in registers
+constexpr int BLD_RUN_TILES = 1024;  // rebuild sets of at least so many tiles: runs of bins per wave
+struct BinRanges {                 // one bin's candidate ranges, by lane
+  int off[64];                     // first candidate of each range (past the last range: INT_MAX)
+  int delta[64];                   // position of candidate c of range r: c + delta[r]
+};
+struct BinHead {                   // a bin's atoms and stencil, and this lane's range of it
+  int m, first, nrange;
+  int2 rng;
+};
+
+// bin (x, y, z) of cell C: its atoms, and the candidate range of every lane below nrange
+__device__ __forceinline__ BinHead bin_head(const MDArgs& a, const CellDev& C, int x, int y, int z) {
+  const int lane = (int)(threadIdx.x & 63u), bin = C.bin_off + (x * C.nb[1] + y) * C.nb[2] + z;
+  BinHead h;
+  h.m = a.bnum[bin];
+  h.first = a.bstart[bin];
   BuildGeo G;
-  build_geo(C, ro.abin[i], a.bin_factor, G);
-  const typename P::R rcs2 = (typename P::R)a.rcs2;
+  build_geo(C, x | (y << BIN_BITS) | (z << (2 * BIN_BITS)), a.bin_factor, G);
+  h.nrange = G.nrange;
+  h.rng = lane < G.nrange ? build_range(a, C, G, lane) : make_int2(0, 0);
+  return h;
+}
+
+// The lists of the atoms of one bin: the wave's share of them, atoms part, part + nparts, ... .
+// s: the reordered coordinates of the batch.
+//
+// LOCAL (every dimension has at least 2 f + 3 bins): a candidate (within f bins) lies less than half the
+// box from the bin's first atom, as every atom of the bin does, so the difference of the two offsets
+// is the minimum image: the test takes 3 subtractions and 3 multiply-adds in FP32 (issued at nearly
+// twice the rate of FP64 and conversions here) on offsets rounded once from FP64.  A candidate whose
+// |d|^2 lies between the cell's list_lo2 and list_hi2 takes the exact test, so the lists are those of the exact
+// test alone.  With fewer bins every test is the exact one.
+template <class P, class LT, bool LOCAL>
+__device__ __forceinline__ void build_bin(const MDArgs& a, int cell, const BinHead& h, int part, int nparts,
+                                          const typename P::S* s, BinRanges& rg) {
+  using R = typename P::R;
+  const CellDev& C = a.cells[cell];
+  const int lane = (int)(threadIdx.x & 63u);
+  const int m = __builtin_amdgcn_readfirstlane(h.m), first = __builtin_amdgcn_readfirstlane(h.first);
+  if (m <= part) return;
+  const typename P::S* sc = s + C.off;
+  const int incl = wave_inclusive_scan(h.rng.y);
+  const int total = __builtin_amdgcn_readlane(incl, 63), off = incl - h.rng.y;
+  __builtin_amdgcn_wave_barrier();                // the last bin's ranges have been read
+  rg.off[lane] = lane < h.nrange ? off : 0x7fffffff;
+  rg.delta[lane] = h.rng.x - off;
+  // candidate index of the bin's first atom: its range is the one that holds its position
+  const unsigned long long own = __builtin_amdgcn_ballot_w64((unsigned)(first - h.rng.x) < (unsigned)h.rng.y);
+  const int self0 = first - __builtin_amdgcn_readlane(h.rng.x - off, __builtin_ctzll(own));
+  __builtin_amdgcn_wave_barrier();
   const typename P::Geo g = P::geo(C);
-  const typename P::S* sc = sbase + C.off;
+  const R rcs2 = (R)a.rcs2;
+  const float lo2 = C.list_lo2, hi2 = C.list_hi2;
   LT* const list = (LT*)a.nbr;
-  const unsigned np = (unsigned)a.npad, ii = (unsigned)i;
+  const unsigned row = (unsigned)a.npad << a.lblk, bm = (1u << a.lblk) - 1u;   // list_index, by rows of blocks
   const int cap = a.maxnb;
-  int count = 0;
-  int2 cur = build_range(a, C, G, 0);
-  for (int r = 0; r < G.nrange; ++r) {
-    const int2 nxt = r + 1 < G.nrange ? build_range(a, C, G, r + 1) : make_int2(0, 0);
-    for (int p = 0; p < cur.y; p += UNR) {
-      int pos[UNR];
-      typename P::S sj[UNR];
+  const typename P::S sref = sc[first];
+  for (int g0 = 0; g0 < m; g0 += 64) {            // the bin's atoms, by lane (one group unless m > 64)
+    const int ng = min(64, m - g0);
+    const typename P::S so = sc[first + g0 + min(lane, ng - 1)];
+    R po[3] = {0, 0, 0};
+    if constexpr (LOCAL) P::sep(so, sref, g, po);
+    int cnt_reg = 0;
+    for (int ct = 0; ct < total; ct += 64 * BLD_ROUNDS) {
+      int pos[BLD_ROUNDS];
+      typename P::S sj[BLD_ROUNDS];
+      float pj[BLD_ROUNDS][3];
 #pragma unroll
-      for (int u = 0; u < UNR; ++u) {
-        pos[u] = p + u < cur.y ? cur.x + p + u : li;
-        sj[u] = P::load_rel(sc, pos[u]);
+      for (int q = 0; q < BLD_ROUNDS; ++q) {
+        const int c = ct + q * 64 + lane;
+        pos[q] = first;
+        if (ct + q * 64 < total) {
+          int r = 0;                                  // the last range that begins at or before c
+          if (h.nrange > 16) {
+            r = rg.off[32] <= c ? 32 : 0;
+            r = rg.off[r + 16] <= c ? r + 16 : r;
+          }
+          r = rg.off[r + 8] <= c ? r + 8 : r;
+          r = rg.off[r + 4] <= c ? r + 4 : r;
+          r = rg.off[r + 2] <= c ? r + 2 : r;
+          r = rg.off[r + 1] <= c ? r + 1 : r;
+          pos[q] = c < total ? c + rg.delta[r] : first;
+        }
+        sj[q] = P::load_rel(sc, pos[q]);
       }
+      if constexpr (LOCAL) {
 #pragma unroll
-      for (int u = 0; u < UNR; ++u) {
-        typename P::R d[3];
-        P::sep(sj[u], si, g, d);
-        if (pos[u] != li && d[0] * d[0] + d[1] * d[1] + d[2] * d[2] < rcs2) {
-          if (count < cap) list[list_index((unsigned)count, np, ii, a.lblk)] = (LT)pos[u];
-          ++count;
+        for (int q = 0; q < BLD_ROUNDS; ++q) {
+          R d[3];
+          P::sep(sj[q], sref, g, d);
+          const bool ok = ct + q * 64 + lane < total;
+#pragma unroll
+          for (int e = 0; e < 3; ++e) pj[q][e] = ok ? (float)d[e] : 1e18f;
         }
       }
+      // 64 is a multiple of nparts: the wave's atoms of the group are part, part + nparts, ...
+      for (int at = part; at < ng; at += nparts) {
+        float ox = 0.f, oy = 0.f, oz = 0.f;
+        typename P::S si = so;
+        if constexpr (LOCAL) { ox = lane_value((float)po[0], at); oy = lane_value((float)po[1], at); oz = lane_value((float)po[2], at); }
+        else si = lane_value_s<P>(so, at);
+        LT* const li = list + ((size_t)(unsigned)(C.off + first + g0 + at) << a.lblk);
+        const int selfc = self0 + g0 + at - ct;
+        int cnt = ct ? __builtin_amdgcn_readlane(cnt_reg, at) : 0;
+#pragma unroll
+        for (int q = 0; q < BLD_ROUNDS; ++q) {
+          if (ct + q * 64 >= total) break;
+          unsigned long long mask;
+          if constexpr (LOCAL) {
+            const float dx = pj[q][0] - ox, dy = pj[q][1] - oy, dz = pj[q][2] - oz;
+            const float r2 = dx * dx + dy * dy + dz * dz;
+            mask = __builtin_amdgcn_ballot_w64(r2 < lo2);
+            const unsigned long long most = __builtin_amdgcn_ballot_w64(r2 < hi2);
+            if (mask != most)
+              mask |= most & __builtin_amdgcn_ballot_w64(exact_in<P>(P::load_rel(sc, pos[q]), lane_value_s<P>(so, at), g, rcs2));
+          } else {
+            mask = __builtin_amdgcn_ballot_w64(exact_in<P>(sj[q], si, g, rcs2));
+            const int left = total - ct - q * 64;
+            if (left < 64) mask &= (1ull << left) - 1ull;
+          }
+          if ((selfc >> 6) == q) mask &= ~(1ull << (selfc & 63));
+          const unsigned k = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, (unsigned)cnt));
+          cnt += __builtin_popcountll(mask);
+          if (cnt > cap) mask &= __builtin_amdgcn_ballot_w64((int)k < cap);
+          if (__builtin_amdgcn_inverse_ballot_w64(mask)) li[(size_t)(k >> a.lblk) * row + (k & bm)] = (LT)pos[q];
+        }
+        cnt_reg = lane == at ? cnt : cnt_reg;
+      }
     }
+    if (lane < ng && (lane & (nparts - 1)) == part) {
+      if (cnt_reg > cap) atomicMin(&a.cells[cell].status, (int)ST_CAP);
+      a.nn[C.off + first + g0 + lane] = min(cnt_reg, cap);
+    }
+  }
+}
+
+// `run` consecutive bins of one cell from its bin b0, the next bin's ranges requested before a bin's
+// candidates are tested
+template <class P, class LT>
+__device__ __forceinline__ void build_run(const MDArgs& a, int cell, int b0, int run, int part, int nparts,
+                                          const typename P::S* s, BinRanges& rg) {
+  const CellDev& C = a.cells[cell];
+  const int nb0 = C.nb[0], nb1 = C.nb[1], nb2 = C.nb[2];
+  const bool local = min(min(nb0, nb1), nb2) >= 2 * a.bin_factor + 3;
+  int z = b0 % nb2, t = b0 / nb2;
+  int y = t % nb1, x = t / nb1;
+  BinHead cur = bin_head(a, C, x, y, z);
+  for (int e = 0; e < run; ++e) {
+    if (++z == nb2) { z = 0; if (++y == nb1) { y = 0; ++x; } }
+    BinHead nxt = cur;
+    if (e + 1 < run) nxt = bin_head(a, C, x, y, z);
+    if (local) build_bin<P, LT, true>(a, cell, cur, part, nparts, s, rg);
+    else build_bin<P, LT, false>(a, cell, cur, part, nparts, s, rg);
     cur = nxt;
   }
-  if (count > cap) {
-    atomicMin(&a.cells[t.cell].status, (int)ST_CAP);
-    count = cap;
-  }
-  a.nn[i] = count;
 }
 
-// The tiles of the rebuild work list, one per wave, block-strided (XcdLoop), with the reorder's
-// scatter fused in.  Rebuild sets of fewer than BUILD_SPLIT tiles leave most of the GPU idle with one
-// lane per atom; there k_build_list_lanes builds the same lists with BUILD_LPA lanes per atom.
-constexpr int BUILD_SPLIT = 4096;
+// The lists of the rebuilding cells, over the work list, block-strided (XcdLoop).  An item is a tile's
+// share of its cell's bins, split over `split` waves: a run of a few consecutive bins whose cell is
+// looked up once; where bins hold many atoms (copper: ~60), 2^lparts waves share each bin's atoms.
+// scatter: after the phase kernels the reorder's second half is done here too, tile by tile - nothing
+// else reads the arrays that it writes, and the candidates come from the scratch rows, which hold the
+// same reordered coordinates.  After the one-block-per-cell preparation, which reorders completely,
+// they are read from s_cur.
+// Measured on one MI355X, per MD step, against one lane per atom (sets of 4096 tiles and more) and eight
+// lanes per atom walking the candidate ranges: 100 cells of 10^4 beads 62.6 -> 37.1 us, 50 glassy
+// cells 102 -> 54 us, 128 cells of 40 000 beads 205 -> 147 us (all 5.1 M beads at once 2.19 -> 1.57 ms).
 template <class P, class LT>
-__global__ __launch_bounds__(TILE * BUILD_WAVES) void k_build_list(MDArgs a) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  if (a.work_count[1] < BUILD_SPLIT) return;
-  const XcdLoop L(a.work_count[1], BUILD_WAVES, wave);
-  for (int k = L.k; k < L.end; k += L.step) build_tile<P, LT>(a, a.tiles[work_tile(a, k)], lane);
-}
-
-// The same lists for small rebuild sets, BUILD_LPA lanes per atom: the atom's ranges are looked up
-// once into LDS, its lanes walk the concatenated candidates interleaved (lane l takes candidates l,
-// l + BUILD_LPA, ...), and for each candidate slot a ballot over the atom's lanes gives every
-// accepted candidate its index (the running count plus the accepted lanes below), so the list
-// comes out in the same candidate order as with one lane per atom.  SCATTER: the reorder's scatter
-// is fused in as in k_build_list (the atom's first lane copies its row); without it (after the
-// one-block-per-cell preparation, which reorders completely) the candidates come from s_cur.
-constexpr int BUILD_LPA = 8;
-constexpr int MAX_RANGES = (2 * MAX_BIN_FACTOR + 1) * (2 * MAX_BIN_FACTOR + 1) * 2;
-template <class P, class LT, bool SCATTER>
-__device__ __forceinline__ void build_tile_lanes(const MDArgs& a, const Tile& t, int2 (*rng)[MAX_RANGES]) {
-  const int slot = threadIdx.x / BUILD_LPA, lane = threadIdx.x % BUILD_LPA;
-  const bool active = slot < t.count;
-  const CellDev& C = a.cells[t.cell];
-  const long long i = (long long)t.begin + (active ? slot : 0);
-  const int li = (int)(i - C.off);
+__global__ __launch_bounds__(64 * BLD_WAVES) void k_build_list(MDArgs a, int scatter, int lparts) {
+  __shared__ BinRanges rg[BLD_WAVES];
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int nc = work_cells_n(a), ntl = work_tiles_n(a);
+  if (ntl == 0) return;
   const Reorder<P> ro(a);
-  if constexpr (SCATTER) {
-    if (active && lane == 0) reorder_scatter_atom<P>(a, C, i);
-  }
-  const typename P::S* sc = (SCATTER ? (const typename P::S*)ro.s : (const typename P::S*)a.s_cur) + C.off;
-  const typename P::S si = sc[li];
-  BuildGeo G;
-  build_geo(C, SCATTER ? ro.abin[i] : a.abin[i], a.bin_factor, G);
-  int2* rg = rng[slot];
-  for (int r = lane; r < G.nrange; r += BUILD_LPA) rg[r] = build_range(a, C, G, r);
-  __syncthreads();
-  const typename P::R rcs2 = (typename P::R)a.rcs2;
-  const typename P::Geo g = P::geo(C);
-  const unsigned np = (unsigned)a.npad, ii = (unsigned)i;
-  const unsigned gshift = (threadIdx.x & 63u) & ~(unsigned)(BUILD_LPA - 1), below = (1u << lane) - 1u;
-  int count = 0;
-  if (active && G.nrange > 0) {
-    int r = 0, off = 0;                       // range r holds candidates [off, off + cur.y)
-    int2 cur = rg[0];
-    for (int c0 = lane;; c0 += UNR * BUILD_LPA) {
-      int pos[UNR];
-      bool ok[UNR];
-#pragma unroll
-      for (int u = 0; u < UNR; ++u) {
-        const int c = c0 + u * BUILD_LPA;
-        while (r < G.nrange && c >= off + cur.y) {
-          off += cur.y;
-          if (++r < G.nrange) cur = rg[r];
-        }
-        ok[u] = r < G.nrange;
-        pos[u] = ok[u] ? cur.x + (c - off) : li;
-      }
-      if (!ok[0]) break;
-      typename P::S sj[UNR];
-#pragma unroll
-      for (int u = 0; u < UNR; ++u) sj[u] = P::load_rel(sc, pos[u]);
-#pragma unroll
-      for (int u = 0; u < UNR; ++u) {
-        bool acc = false;
-        if (ok[u] && pos[u] != li) {
-          typename P::R d[3];
-          P::sep(sj[u], si, g, d);
-          acc = d[0] * d[0] + d[1] * d[1] + d[2] * d[2] < rcs2;
-        }
-        const unsigned gm = (unsigned)(__ballot(acc) >> gshift) & ((1u << BUILD_LPA) - 1u);
-        if (acc) {
-          const int k = count + __popc(gm & below);
-          if (k < a.maxnb) ((LT*)a.nbr)[list_index((unsigned)k, np, ii, a.lblk)] = (LT)pos[u];
-        }
-        count += __popc(gm);
-      }
-      if (!ok[UNR - 1]) break;
-    }
-  }
-  // the atom's total: its lanes stop counting when their own candidates end, so take the largest
-  int n = count;
-#pragma unroll
-  for (int o = 1; o < BUILD_LPA; o <<= 1) n = max(n, __shfl_xor(n, o, BUILD_LPA));
-  if (active && lane == 0) {
-    if (n > a.maxnb) {
-      atomicMin(&a.cells[t.cell].status, (int)ST_CAP);
-      n = a.maxnb;
-    }
-    a.nn[i] = n;
-  }
-}
-
-// use_work: the work list's tiles, block-strided (XcdLoop), when there are fewer than BUILD_SPLIT;
-// else one block per tile of the batch (placed like the force passes), exiting at once for cells
-// that do not rebuild
-template <class P, class LT>
-__global__ __launch_bounds__(TILE * BUILD_LPA) void k_build_list_lanes(MDArgs a, int use_work) {
-  __shared__ int2 rng[TILE][MAX_RANGES];      // candidate ranges (first position, count) per atom
-  if (use_work) {
-    if (a.work_count[1] >= BUILD_SPLIT) return;
-    const XcdLoop L(a.work_count[1]);
-    for (int k = L.k; k < L.end; k += L.step) {
-      __syncthreads();                        // the previous tile's ranges have been read
-      build_tile_lanes<P, LT, true>(a, a.tiles[work_tile(a, k)], rng);
-    }
-  } else {
-    const int tb = block_tile_xcd(a.ntiles, blockIdx.x);
-    if (tb >= a.ntiles) return;
-    const Tile t = a.tiles[tb];
-    if (!a.cells[t.cell].rebuild) return;
-    build_tile_lanes<P, LT, false>(a, t, rng);
+  if (scatter)
+    for_work_tiles(a, [&](const Tile& t, long long i) { reorder_scatter_atom<P>(a, a.cells[t.cell], i); });
+  const typename P::S* s = scatter ? ro.s : (const typename P::S*)a.s_cur;
+  // a tile holds 10-14 bins at Kremer-Grest densities: single bins until every resident wave has two,
+  // then runs of three or four (5.1 M beads at once: 1.95 ms by single bins, 1.62 ms by runs of four);
+  // 3-4 of the glassy cells' fuller bins (two waves each), one of copper's
+  const int lsplit = lparts > 1 ? 0 : lparts == 1 ? 2 : ntl < BLD_RUN_TILES ? 4 : 2;
+  const XcdLoop L((ntl << lsplit) << lparts, BLD_WAVES, wave);
+  for (int k = L.k; k < L.end; k += L.step) {
+    const int it = k >> lparts, part = k & ((1 << lparts) - 1);
+    const int w = work_find(a.work_tstart, nc, it >> lsplit);
+    const int cell = __builtin_amdgcn_readfirstlane(a.work_cells[w]);
+    const int q = it - (__builtin_amdgcn_readfirstlane(a.work_tstart[w]) << lsplit);
+    const CellDev& C = a.cells[cell];
+    const unsigned nbins = (unsigned)(C.nb[0] * C.nb[1] * C.nb[2]), nq = (unsigned)C.ntile << lsplit;
+    const int b0 = (int)((unsigned long long)q * nbins / nq), b1 = (int)((unsigned long long)(q + 1) * nbins / nq);
+    if (b1 > b0) build_run<P, LT>(a, cell, b0, b1 - b0, part, 1 << lparts, s, rg[wave]);
   }
 }
 

@@ -51,12 +51,12 @@ struct rcell_ctx {
   bool own_stream = false;
   std::string err;
   std::vector<int> off, n, tile_off, ntile, bin_off, bin_cap;
-  long long bins_total = 0, bins_alloc = 0;
+  long long bins_alloc = 0;
   std::vector<double> occ;        // expected atoms per bin of each cell
   double density_max = 0.0;       // the densest cell at create (atoms per volume)
   double fire_ftol2 = 0.0;        // statics: convergence threshold and move limit of the current call
   int fire_max_iter = 0;
-  int sort_cap = 256;             // keys staged in LDS per wave by the bin sort
+  int build_lparts = 0;           // log2 of the list build's waves per bin
   // device memory
   double *x = nullptr, *y = nullptr, *z = nullptr, *vx = nullptr, *vy = nullptr, *vz = nullptr;
   void *fx = nullptr, *fy = nullptr, *fz = nullptr;
@@ -70,10 +70,11 @@ struct rcell_ctx {
   bool list16 = false;            // 16-bit list entries (every cell has at most 65536 atoms, mixed)
   bool small_cells = false;       // every cell has at most PREP_ATOMS atoms
   bool cell_prep = false;         // rebuild preparation by one block per cell (k_cell_prep)
-  int *nn = nullptr, *abin = nullptr, *binned = nullptr, *bin_cell = nullptr, *sort_tmp = nullptr;
+  int *nn = nullptr, *abin = nullptr, *binned = nullptr, *bkey = nullptr;
   int *bcount = nullptr, *bstart = nullptr, *bnum = nullptr, *bfill = nullptr;
-  // rebuild work list (k_rebuild_work): cells, prefix sums of their tiles and chunks, three counts
-  int *work_cells = nullptr, *work_tstart = nullptr, *work_kstart = nullptr, *work_count = nullptr;
+  // rebuild work list: cells, prefix sums of their tiles, packed counts
+  int *work_cells = nullptr, *work_tstart = nullptr;
+  unsigned long long* work_pack = nullptr;
   CellDev* cells = nullptr;
   Tile* tiles = nullptr;
   Part* parts = nullptr;
@@ -102,16 +103,17 @@ void drop_graphs(rcell_ctx* c) {
     if (c->graph[q]) { (void)hipGraphExecDestroy(c->graph[q]); c->graph[q] = nullptr; }
 }
 
-// the bin sort stages twice the expected keys of its 64 bins in LDS (a fuller wave falls back to
-// the slower paths); a change of that size invalidates the captured graphs
+// Waves of the list build per bin: one up to ~10 atoms per bin (Kremer-Grest: 4-6), where a bin's
+// candidates fit in registers and are read once; more for fuller bins, whose atoms are shared out so
+// that a cell still gives enough waves.  A change invalidates the captured graphs.
 void set_occupancy(rcell_ctx* c, int cell, double atoms_per_bin) {
   c->occ[cell] = atoms_per_bin;
   double m = 0.0;
   for (double o : c->occ) m = std::max(m, o);
-  const int cap = (int)std::min<double>(SORT_LDS_MAX, std::max(256.0, 2.0 * 64.0 * std::ceil(m) + 64.0));
-  if (cap != c->sort_cap) {
+  const int lp = m <= 10.0 ? 0 : m <= 24.0 ? 1 : 3;
+  if (lp != c->build_lparts) {
     drop_graphs(c);
-    c->sort_cap = cap;
+    c->build_lparts = lp;
   }
 }
 
@@ -213,10 +215,8 @@ MDArgs make_args(const rcell_ctx* c) {
   a.cells = c->cells; a.tiles = c->tiles; a.parts = c->parts; a.ntiles = c->ntiles; a.ncells = c->ncells;
   a.abin = c->abin; a.bcount = c->bcount; a.bstart = c->bstart; a.bnum = c->bnum; a.bfill = c->bfill;
   a.binned = c->binned;
-  a.sort_tmp = c->sort_tmp;
-  a.bins_total = c->bins_total;
-  a.work_cells = c->work_cells; a.work_tstart = c->work_tstart; a.work_kstart = c->work_kstart;
-  a.work_count = c->work_count;
+  a.bkey = c->bkey;
+  a.work_cells = c->work_cells; a.work_tstart = c->work_tstart; a.work_pack = c->work_pack;
   a.bin_factor = c->bin_factor;
   const rcell_params& p = c->p;
   // integrator constants: the same expressions, in the same order, as the method's definition
@@ -325,9 +325,9 @@ void launch_force(rcell_ctx* c, int mode, int lanes = -1) {
   launch_force_args(c, make_args(c), mode, lanes > 0 ? lanes : c->lanes);
 }
 
-void launch_reduce(rcell_ctx* c, int mode) {
+void launch_reduce(rcell_ctx* c, int mode, int fill = 0) {
   const MDArgs a = make_args(c);
-  hipLaunchKernelGGL(k_reduce, dim3(c->ncells), dim3(RED_NT), 0, c->stream, a, mode);
+  hipLaunchKernelGGL(k_reduce, dim3(c->ncells), dim3(RED_NT), 0, c->stream, a, mode, fill);
 }
 
 // blocks of the block-strided rebuild phases: enough to fill the GPU when many cells rebuild,
@@ -336,12 +336,14 @@ constexpr int WORK_BLOCKS = 2048;
 unsigned round8(int blocks) { return (unsigned)((std::max(1, blocks) + 7) / 8 * 8); }
 
 // reduce_mode >= 0: the per-cell reduction of that mode runs first, fused into the preparation
-// launch when the cells are small enough for it
+// launch when the cells are small enough for it, and enters the cells that it flags into the work list
+// (emptied by the force pass, k_start or k_fire_move before it); otherwise k_rebuild_work makes the list
 void launch_build(rcell_ctx* c, int reduce_mode = -1) {
   TraceRange tr("rcell: reduce + neighbour rebuild");
   const MDArgs a = make_args(c);
-  const dim3 gt(tile_grid(c->ntiles)), bt(TILE), gc(c->ncells), bc(SCAN_NT);
-  if (c->cell_prep) {              // small cells: the six preparation phases in one launch
+  const dim3 gc(c->ncells), bc(SCAN_NT);
+  if (reduce_mode < 0) hipLaunchKernelGGL(k_rebuild_work, dim3(1), dim3(SCAN_NT), 0, c->stream, a);
+  if (c->cell_prep) {              // small cells: the preparation phases in one launch
     if (reduce_mode >= 0) {
       if (c->fp64) hipLaunchKernelGGL(k_reduce_prep<FP64>, gc, bc, 0, c->stream, a, reduce_mode);
       else hipLaunchKernelGGL(k_reduce_prep<Mixed>, gc, bc, 0, c->stream, a, reduce_mode);
@@ -351,36 +353,25 @@ void launch_build(rcell_ctx* c, int reduce_mode = -1) {
     }
   } else {
     // the phases walk the work list of the cells that rebuild: small grids, block-strided
-    if (reduce_mode >= 0) launch_reduce(c, reduce_mode);
-    hipLaunchKernelGGL(k_rebuild_work, dim3(1), dim3(SCAN_NT), 0, c->stream, a);
+    if (reduce_mode >= 0) launch_reduce(c, reduce_mode, 1);
     // grids of whole multiples of 8 blocks: the loops share the work out per XCD (XcdLoop)
     const dim3 gw(round8(std::min(WORK_BLOCKS, (c->ntiles + WORK_WAVES - 1) / WORK_WAVES))), bw(TILE * WORK_WAVES);
     const dim3 gs(round8(std::min(c->ncells, WORK_BLOCKS / 8)));
-    const dim3 gk(round8((int)std::min<long long>(4 * WORK_BLOCKS, c->bins_total / 64)));
     if (c->fp64) hipLaunchKernelGGL(k_bin<FP64>, gw, bw, 0, c->stream, a);
     else hipLaunchKernelGGL(k_bin<Mixed>, gw, bw, 0, c->stream, a);
     hipLaunchKernelGGL(k_bin_scan, gs, bc, 0, c->stream, a);
     hipLaunchKernelGGL(k_bin_fill, gw, bw, 0, c->stream, a);
-    hipLaunchKernelGGL(k_bin_sort, gk, dim3(64), sizeof(int) * c->sort_cap, c->stream, a,
-                       (const int*)c->bin_cell, c->sort_cap);
-    // the reorder's scatter runs inside the list build (build_tile)
+    // the reorder's scatter runs inside the list build 
     if (c->fp64) hipLaunchKernelGGL(k_reorder_gather<FP64>, gw, bw, 0, c->stream, a);
     else hipLaunchKernelGGL(k_reorder_gather<Mixed>, gw, bw, 0, c->stream, a);
   }
-  const int use_work = c->cell_prep ? 0 : 1;
-  if (use_work) {                  // large rebuild sets: one lane per atom
-    const dim3 gl(round8(std::min(WORK_BLOCKS, (c->ntiles + BUILD_WAVES - 1) / BUILD_WAVES))), bl(TILE * BUILD_WAVES);
-    if (c->fp64) hipLaunchKernelGGL((k_build_list<FP64, int>), gl, bl, 0, c->stream, a);
-    else if (c->list16) hipLaunchKernelGGL((k_build_list<Mixed, uint16_t>), gl, bl, 0, c->stream, a);
-    else hipLaunchKernelGGL((k_build_list<Mixed, int>), gl, bl, 0, c->stream, a);
-  }
-  // small rebuild sets, and every build after the one-block-per-cell preparation: the same lists
-  // with several lanes per atom
-  const dim3 gs2(use_work ? round8(std::min(WORK_BLOCKS, c->ntiles)) : (unsigned)tile_grid(c->ntiles)),
-      bs2(TILE * BUILD_LPA);
-  if (c->fp64) hipLaunchKernelGGL((k_build_list_lanes<FP64, int>), gs2, bs2, 0, c->stream, a, use_work);
-  else if (c->list16) hipLaunchKernelGGL((k_build_list_lanes<Mixed, uint16_t>), gs2, bs2, 0, c->stream, a, use_work);
-  else hipLaunchKernelGGL((k_build_list_lanes<Mixed, int>), gs2, bs2, 0, c->stream, a, use_work);
+  // the lists, one wave per bin or run of bins (more for full bins: set_occupancy)
+  const int scatter = c->cell_prep ? 0 : 1, lp = c->build_lparts;
+  const long long items = (long long)c->ntiles << (lp ? 3 : 4);
+  const dim3 gl(round8((int)std::min<long long>(WORK_BLOCKS, (items + BLD_WAVES - 1) / BLD_WAVES))), bl(64 * BLD_WAVES);
+  if (c->fp64) hipLaunchKernelGGL((k_build_list<FP64, int>), gl, bl, 0, c->stream, a, scatter, lp);
+  else if (c->list16) hipLaunchKernelGGL((k_build_list<Mixed, uint16_t>), gl, bl, 0, c->stream, a, scatter, lp);
+  else hipLaunchKernelGGL((k_build_list<Mixed, int>), gl, bl, 0, c->stream, a, scatter, lp);
 }
 
 void launch_start(rcell_ctx* c) {
@@ -462,28 +453,22 @@ int layout_bins(rcell_ctx* c, const std::vector<int>& need) {
   long long total = 0;
   std::vector<int> off(c->ncells), cap(c->ncells);
   for (int k = 0; k < c->ncells; ++k) {
-    // whole 64-bin chunks per cell: the bin sort works on chunks of one cell each
+    // whole 64-entry pieces per cell
     cap[k] = (std::max(need[k], c->bin_cap.empty() ? 0 : c->bin_cap[k]) + 63) / 64 * 64;
     off[k] = (int)total;
     total += cap[k];
   }
   if (total > (1ll << 31) - 1) return fail(c, RCELL_ERR_OOM, "too many neighbour bins");
   if (total > c->bins_alloc) {
-    dfree(c, c->bcount); dfree(c, c->bstart); dfree(c, c->bnum); dfree(c, c->bfill); dfree(c, c->bin_cell);
-    c->bcount = c->bstart = c->bnum = c->bfill = c->bin_cell = nullptr;
+    dfree(c, c->bcount); dfree(c, c->bstart); dfree(c, c->bnum); dfree(c, c->bfill);
+    c->bcount = c->bstart = c->bnum = c->bfill = nullptr;
     int st;
     if ((st = dalloc(c, &c->bcount, total)) || (st = dalloc(c, &c->bstart, total)) ||
-        (st = dalloc(c, &c->bnum, total)) || (st = dalloc(c, &c->bfill, total)) ||
-        (st = dalloc(c, &c->bin_cell, total)))
+        (st = dalloc(c, &c->bnum, total)) || (st = dalloc(c, &c->bfill, total)))
       return st;
     HIPCHK(c, hipMemsetAsync(c->bcount, 0, sizeof(int) * total, c->stream));
     c->bins_alloc = total;
   }
-  c->bins_total = total;
-  std::vector<int> owner(total);
-  for (int k = 0; k < c->ncells; ++k)
-    for (int b = 0; b < cap[k]; ++b) owner[off[k] + b] = k;
-  HIPCHK(c, hipMemcpyAsync(c->bin_cell, owner.data(), sizeof(int) * total, hipMemcpyHostToDevice, c->stream));
   c->bin_off = off;
   c->bin_cap = cap;
   return push_bin_layout(c);
@@ -682,23 +667,23 @@ int rcell_create(const rcell_params* params, const rcell_cell_init* cells, int32
   const size_t fsz = sizeof(double);
   const size_t ssz = c->fp64 ? sizeof(S64) : sizeof(int4);
   int e;
-  char *f0, *s0, *s1, *bondp;
+  char *f0, *f1, *f2, *s0, *s1, *bondp;
   if ((e = dalloc(c, &c->x, N)) || (e = dalloc(c, &c->y, N)) || (e = dalloc(c, &c->z, N)) ||
       (e = dalloc(c, &c->vx, N)) || (e = dalloc(c, &c->vy, N)) || (e = dalloc(c, &c->vz, N)) ||
-      (e = dalloc(c, &f0, 3 * fsz * N)) || (e = dalloc(c, &s0, ssz * N)) || (e = dalloc(c, &s1, ssz * N)) ||
+      (e = dalloc(c, &f0, fsz * N)) || (e = dalloc(c, &f1, fsz * N)) || (e = dalloc(c, &f2, fsz * N)) ||
+      (e = dalloc(c, &s0, ssz * N)) || (e = dalloc(c, &s1, ssz * N)) ||
       (e = dalloc(c, &c->sb, N)) || (e = dalloc(c, &bondp, (c->list16 ? 8 : 16) * (size_t)N)) ||
       (e = dalloc(c, &c->bond0, N)) ||
       (e = dalloc(c, &c->gid, N)) || (e = dalloc(c, &c->pos_of, N)) ||
       (e = dalloc(c, &c->pscr, (6 * sizeof(double) + ssz + 2 * sizeof(int)) * (size_t)c->npad)) ||
       (e = dalloc(c, &c->nn, N)) ||
-      (e = dalloc(c, &c->abin, N)) || (e = dalloc(c, &c->binned, N)) || (e = dalloc(c, &c->sort_tmp, N)) ||
+      (e = dalloc(c, &c->abin, N)) || (e = dalloc(c, &c->binned, N)) || (e = dalloc(c, &c->bkey, N)) ||
       (e = dalloc(c, &c->cells, ncells)) || (e = dalloc(c, &c->tiles, ntiles)) || (e = dalloc(c, &c->parts, ntiles)) ||
       (e = dalloc(c, &c->stage, ncells)) || (e = dalloc(c, &c->dscratch, (size_t)17 * ncells)) || (e = dalloc(c, &c->dscratch2, (size_t)6 * ncells)) ||
       (e = dalloc(c, &c->iscratch, (size_t)2 * ncells)) || (e = dalloc(c, &c->lscratch, (size_t)2 * ncells)) ||
-      (e = dalloc(c, &c->work_cells, ncells)) || (e = dalloc(c, &c->work_tstart, ncells + 1)) ||
-      (e = dalloc(c, &c->work_kstart, ncells + 1)) || (e = dalloc(c, &c->work_count, 4)))
+      (e = dalloc(c, &c->work_cells, ncells)) || (e = dalloc(c, &c->work_tstart, ncells)) || (e = dalloc(c, &c->work_pack, 1)))
     return bail(e);
-  c->fx = f0; c->fy = f0 + fsz * N; c->fz = f0 + 2 * fsz * N;
+  c->fx = f0; c->fy = f1; c->fz = f2;
   c->s[0] = s0; c->s[1] = s1; c->bond = bondp;
   if ((e = ensure_list_capacity(c, list_capacity(dens, rcs)))) return bail(e);
 
@@ -753,7 +738,8 @@ int rcell_create(const rcell_params* params, const rcell_cell_init* cells, int32
       hipMemcpyAsync(c->bond0, hb.data(), sizeof(int4) * N, hipMemcpyHostToDevice, c->stream) ||
       hipMemcpyAsync(c->tiles, tl.data(), sizeof(Tile) * ntiles, hipMemcpyHostToDevice, c->stream) ||
       hipMemcpyAsync(c->cells, hc.data(), sizeof(CellDev) * ncells, hipMemcpyHostToDevice, c->stream) ||
-      hipMemsetAsync(f0, 0, 3 * fsz * N, c->stream) || hipMemsetAsync(s0, 0, ssz * N, c->stream) ||
+      hipMemsetAsync(f0, 0, fsz * N, c->stream) || hipMemsetAsync(f1, 0, fsz * N, c->stream) ||
+      hipMemsetAsync(f2, 0, fsz * N, c->stream) || hipMemsetAsync(s0, 0, ssz * N, c->stream) ||
       hipMemsetAsync(s1, 0, ssz * N, c->stream) || hipStreamSynchronize(c->stream))
     return bail(fail(c, RCELL_ERR_DEVICE, "initial upload failed"));
   if ((e = layout_bins(c, need_bins))) return bail(e);
@@ -912,8 +898,7 @@ int rcell_minimize(rcell_ctx* c, int32_t max_iter, double ftol, int32_t* iters) 
     const MDArgs a = make_args(c);
     if (c->fp64) hipLaunchKernelGGL(k_fire_move<FP64>, dim3(tile_grid(c->ntiles)), dim3(TILE), 0, c->stream, a);
     else hipLaunchKernelGGL(k_fire_move<Mixed>, dim3(tile_grid(c->ntiles)), dim3(TILE), 0, c->stream, a);
-    launch_reduce(c, RED_MOVE);
-    launch_build(c);
+    launch_build(c, RED_MOVE);
     if (it % 16 == 15 || it == max_iter) {
       hipLaunchKernelGGL(k_fire_iters, dim3((nc + 63) / 64), dim3(64), 0, c->stream, c->cells, nc, d_it, d_done);
       HIPCHK(c, hipMemcpyAsync(done.data(), d_done, sizeof(int) * nc, hipMemcpyDeviceToHost, c->stream));
