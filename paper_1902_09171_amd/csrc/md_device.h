@@ -15,6 +15,8 @@
 //               of B = 8 (Kremer-Grest) or 16 (Sutton-Chen), the blocks of entries [b B, (b+1) B) of
 //               all atoms side by side (list_index), so a lane loads its UNR entries of a trip with
 //               one vector load
+//   pl, pn      pruned list: the entries of nbr within a little more than rc, rewritten every few steps
+//               by a force pass and walked by the passes between (PruneWalk)
 //   bond        up to four FENE partners per atom (cell-local positions; the atom's own position marks an
 //               empty slot), 16-bit slots when the list entries are 16-bit, else 32-bit
 //   gid         original cell-local index of the atom stored at each position; pos_of inverts it;
@@ -40,7 +42,7 @@ constexpr int NBLK_MAX = 16;     // list blocks: 2^lblk consecutive entries of o
 constexpr double TWO32 = 4294967296.0;
 constexpr double TWOM32 = 1.0 / 4294967296.0;
 
-enum Mode : int { MODE_PRIME = 0, MODE_STEP = 1, MODE_LAST = 2, MODE_DRY = 3, MODE_STATIC = 4 };
+enum Mode : int { MODE_PRIME = 0, MODE_STEP = 1, MODE_LAST = 2, MODE_STATIC = 4 };
 enum RedMode : int { RED_START = 0, RED_PRIME = 1, RED_STEP = 2, RED_LAST = 3, RED_STATIC = 4, RED_MOVE = 5 };
 enum Status : int { ST_OK = 0, ST_BOND = -4, ST_CAP = -8, ST_BOX = -3, ST_BAD_F = -2 };
 
@@ -74,6 +76,8 @@ struct CellDev {
   float dmax2;                    // largest squared measured displacement since the last build, as last reduced
   float qeps;                     // bound on the error of a measured displacement: the 16-bit build reference
   float list_lo2, list_hi2;       // list build: |d|^2 from FP32 offsets surely below / above (rc + skin)^2
+  float pmove;                    // bound on how far any atom has moved since the pruned list was written
+  int prune;                      // the next force pass walks the full list and writes the pruned one
   // molecular statics (FIRE): time step, mixing parameter, the velocity update of this iteration
   // (v = fa v + fb f, or zero when frozen), iterations since the power last turned negative,
   // converged flag and iterations used
@@ -113,7 +117,8 @@ struct Part {                     // one tile's contribution
   double pe;
   long long xi[3];
   float maxd2;
-  int status;
+  float step2;                    // largest squared displacement of this step
+  int status, pad;
 };
 
 struct Stage {                    // set_deformation staging, one per cell
@@ -139,6 +144,12 @@ struct MDArgs {
   long long npad;
   int maxnb;
   int lblk;                        // list blocks of 2^lblk entries (list_index)
+  // pruned list (PruneWalk): entries and, per lane of every atom, their number; null: not in use
+  void* pl;
+  unsigned short* pn;
+  double prune_rc2;                // entries within this squared distance are kept
+  float prune_move;                // and serve while no atom has moved further than this
+  int prune_mode;                  // 0: as the cells' flags say, 1: every pass writes it, 2: no pass does
   CellDev* cells;
   const Tile* tiles;
   Part* parts;
@@ -184,6 +195,12 @@ __device__ __forceinline__ void noise_units(const MDArgs& a, int gid, int cell, 
   k[0] = (int)(w[0] >> 8) - (1 << 23);
   k[1] = (int)(w[1] >> 8) - (1 << 23);
   k[2] = (int)(w[2] >> 8) - (1 << 23);
+}
+
+// squared displacement of one drift, rounded up (FP32: three squares and two sums, each within 2^-24)
+__device__ __forceinline__ float drift2(double dt, double vx, double vy, double vz) {
+  const float ux = (float)(dt * vx), uy = (float)(dt * vy), uz = (float)(dt * vz);
+  return 1.000001f * (ux * ux + uy * uy + uz * uz);
 }
 
 // ------------------------------------------------------------------ precision policies
@@ -320,7 +337,8 @@ struct FP64 {
 // S = H^-1 x for upper-triangular H^-1, reduced to its fractional part
 // (explicit fused multiply-adds: every caller rounds identically, so the fixed-point coordinates
 // that the Kremer-Grest force pass recomputes from x equal the stored ones bit for bit)
-__device__ __forceinline__ void scaled_frac(const CellDev& C, double x, double y, double z, double f[3]) {
+template <class Box>
+__device__ __forceinline__ void scaled_frac(const Box& C, double x, double y, double z, double f[3]) {
   const double s0 = fma(C.Hi[0], x, fma(C.Hi[1], y, C.Hi[2] * z));
   const double s1 = fma(C.Hi[4], y, C.Hi[5] * z);
   const double s2 = C.Hi[8] * z;
@@ -329,8 +347,8 @@ __device__ __forceinline__ void scaled_frac(const CellDev& C, double x, double y
   f[2] = s2 - floor(s2);
 }
 
-template <class P>
-__device__ __forceinline__ typename P::S fixed_pos(const CellDev& C, double x, double y, double z) {
+template <class P, class Box>
+__device__ __forceinline__ typename P::S fixed_pos(const Box& C, double x, double y, double z) {
   double f[3];
   scaled_frac(C, x, y, z, f);
   return P::make(f[0], f[1], f[2]);
@@ -444,23 +462,74 @@ __device__ __forceinline__ T lane_sum(T v) {
 }
 
 // ------------------------------------------------------------------ per-atom integration tail
+// The fields of a cell that a force pass needs, read before its first store: the compiler then loads
+// them once through the scalar cache, where loads behind stores went through the vector memory path
+// one round trip after another at the end of every wave.
+template <class P>
+struct CellK {
+  double Hi[9], xm[3];
+  typename P::Geo g;
+  long long step;
+  __device__ explicit CellK(const CellDev& C) : g(P::geo(C)), step(C.step) {
+#pragma unroll
+    for (int q = 0; q < 9; ++q) Hi[q] = C.Hi[q];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) xm[q] = C.xi_mean[q];
+  }
+};
+
 // Completes the time level of atom i after its conservative force fc is known:
 //   Langevin (drag + noise with the per-cell mean removed), second half kick (v_full), the
 //   kinetic stress term, and in MODE_STEP the next first half kick and drift with the new
 //   fixed-point position, displacement check and the next level's noise sums.
+struct TailIn {                   // the atom's own data, requested ahead of the last gathers of its forces
+  double x[3], v[3];
+  int gid;
+  uint2 sb;
+  __device__ void load(const MDArgs& a, long long i, bool step) {
+    v[0] = a.vx[i]; v[1] = a.vy[i]; v[2] = a.vz[i];
+    gid = a.gid[i];
+    if (step) sb = a.sb[i];
+  }
+};
+// The same for a block of one wave (its pass is short of waves, ~5 per SIMD), copied from memory straight into LDS while the pair loop runs: no
+// registers are held for it, and its round trip to memory is over when the pairs are.  Every piece
+// is read as 16 bytes per lane, two arrays at a time; the arrays have room for the few elements
+// past a ragged tile's end.
+struct TileLds {
+  double vx[TILE], vy[TILE], vz[TILE];
+  uint2 sb[TILE], bond[TILE];
+  int gid[2 * TILE];
+  double x[3][TILE];
+};
+__device__ __forceinline__ void lds_copy(const void* src, void* dst, bool on) {
+  if (on)
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                     (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+}
+__device__ __forceinline__ void tile_prefetch(const MDArgs& a, const Tile& t, TileLds& L) {
+  const int ln = (int)threadIdx.x, h = ln & 31;
+  const bool hi = ln >= 32, on = 2 * h < t.count;          // 16 bytes: two elements of 8
+  const size_t o = (size_t)t.begin * 8 + 16 * (size_t)h;
+  lds_copy((const char*)(hi ? a.vy : a.vx) + o, L.vx, on);
+  lds_copy((hi ? (const char*)a.sb : (const char*)a.vz) + o, L.vz, on);
+  lds_copy(hi ? (const char*)a.gid + (size_t)t.begin * 4 + 16 * (size_t)h : (const char*)a.bond + o, L.bond,
+           hi ? 4 * h < t.count : on);
+}
+
 struct TailOut {
   double K[6];
-  float maxd2;
-  long long xi[3];
+  float maxd2, step2;
+  int xi[3];
 };
 
 template <class P>
-__device__ __forceinline__ void atom_tail(const MDArgs& a, const CellDev& C, int cell, long long i,
-                                          double fcx, double fcy, double fcz, int mode, TailOut& o,
-                                          const double* xin = nullptr) {
-  double vx = a.vx[i], vy = a.vy[i], vz = a.vz[i];
-  const int gid = a.gid[i];
+__device__ __forceinline__ void atom_tail(const MDArgs& a, const CellK<P>& C, int cell, long long i,
+                                          double fcx, double fcy, double fcz, int mode, TailOut& o, const TailIn& in) {
+  double vx = in.v[0], vy = in.v[1], vz = in.v[2];
+  const int gid = in.gid;
   double f0 = fcx, f1 = fcy, f2 = fcz;
+  o.step2 = 0.f;
   if (mode == MODE_STATIC) {
     // statics: keep the conservative force and report f.v, |f|^2, |v|^2 and max |f|^2 (FIRE)
     ((typename P::Fst*)a.fx)[i] = (typename P::Fst)f0;
@@ -482,9 +551,9 @@ __device__ __forceinline__ void atom_tail(const MDArgs& a, const CellDev& C, int
     if (a.gamma_on) {
       int k[3];
       noise_units(a, gid, cell, C.step + 1, k);
-      f0 = (f0 + a.drag * vx) + a.c24 * ((double)k[0] - C.xi_mean[0]);
-      f1 = (f1 + a.drag * vy) + a.c24 * ((double)k[1] - C.xi_mean[1]);
-      f2 = (f2 + a.drag * vz) + a.c24 * ((double)k[2] - C.xi_mean[2]);
+      f0 = (f0 + a.drag * vx) + a.c24 * ((double)k[0] - C.xm[0]);
+      f1 = (f1 + a.drag * vy) + a.c24 * ((double)k[1] - C.xm[1]);
+      f2 = (f2 + a.drag * vz) + a.c24 * ((double)k[2] - C.xm[2]);
     }
     vx += a.h * f0;  // v(t + dt) from the half-step velocity
     vy += a.h * f1;
@@ -503,20 +572,16 @@ __device__ __forceinline__ void atom_tail(const MDArgs& a, const CellDev& C, int
     vx += a.h * f0;  // first half kick of the next step
     vy += a.h * f1;
     vz += a.h * f2;
-    const double x0 = xin ? xin[0] : a.x[i], y0 = xin ? xin[1] : a.y[i], z0 = xin ? xin[2] : a.z[i];
-    const double x = x0 + a.dt * vx, y = y0 + a.dt * vy, z = z0 + a.dt * vz;
+    const double x = in.x[0] + a.dt * vx, y = in.x[1] + a.dt * vy, z = in.x[2] + a.dt * vz;
     a.vx[i] = vx; a.vy[i] = vy; a.vz[i] = vz;
     a.x[i] = x; a.y[i] = y; a.z[i] = z;
+    o.step2 = drift2(a.dt, vx, vy, vz);
     const typename P::S sn = fixed_pos<P>(C, x, y, z);
     P::store_xyz(a.s_nxt, i, sn);
     typename P::R d[3];
-    P::disp(sn, a.sb[i], P::geo(C), d);
+    P::disp(sn, in.sb, C.g, d);
     o.maxd2 = (float)(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-    if (a.gamma_on) {
-      int k[3];
-      noise_units(a, gid, cell, C.step + 2, k);
-      o.xi[0] = k[0]; o.xi[1] = k[1]; o.xi[2] = k[2];
-    }
+    if (a.gamma_on) noise_units(a, gid, cell, C.step + 2, o.xi);
   }
 }
 
@@ -551,85 +616,117 @@ __device__ __forceinline__ int wave_inclusive_scan(int v) {
   return v;
 }
 
-// the same trees over the lanes whose index is a multiple of L only (the other lanes hold zeros):
-// lane 0 receives the result
-template <int L, class T>
-__device__ __forceinline__ T wave_sum_from(T v) {
-#pragma unroll
-  for (int o = 32; o >= L; o >>= 1) v += __shfl_xor(v, o);
+// Sums over a wave by halving: at the first two levels two values share the work, one half of the lanes
+// taking over each (a register swap between lane halves, then one addition), the last four levels run
+// inside the 16-lane rows (DPP).  Six doubles take 39 register operations, where a tree of shuffles per
+// value took 108 and as many trips through the LDS crossbar.  Fixed pattern: deterministic.
+// sums2x / sums4x: values a, b (, c, d) of every lane; afterwards the rows of 16 lanes hold, in every
+// lane, the sums of a, c, b, d (row 0, 1, 2, 3).
+__device__ __forceinline__ void half_swap(int& a, int& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap((unsigned)a, (unsigned)b, false, false);
+  a = (int)r[0]; b = (int)r[1];
+}
+__device__ __forceinline__ void row_swap(int& a, int& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap((unsigned)a, (unsigned)b, false, false);
+  a = (int)r[0]; b = (int)r[1];
+}
+__device__ __forceinline__ void half_swap(double& a, double& b) {
+  int al = __double2loint(a), ah = __double2hiint(a), bl = __double2loint(b), bh = __double2hiint(b);
+  half_swap(al, bl); half_swap(ah, bh);
+  a = __hiloint2double(ah, al); b = __hiloint2double(bh, bl);
+}
+__device__ __forceinline__ void row_swap(double& a, double& b) {
+  int al = __double2loint(a), ah = __double2hiint(a), bl = __double2loint(b), bh = __double2hiint(b);
+  row_swap(al, bl); row_swap(ah, bh);
+  a = __hiloint2double(ah, al); b = __hiloint2double(bh, bl);
+}
+__device__ __forceinline__ void half_swap(float& a, float& b) {
+  int x = __float_as_int(a), y = __float_as_int(b);
+  half_swap(x, y);
+  a = __int_as_float(x); b = __int_as_float(y);
+}
+__device__ __forceinline__ void row_swap(float& a, float& b) {
+  int x = __float_as_int(a), y = __float_as_int(b);
+  row_swap(x, y);
+  a = __int_as_float(x); b = __int_as_float(y);
+}
+// rotation of a 16-lane row by N lanes
+template <int N>
+__device__ __forceinline__ int row_ror(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x120 + N, 0xf, 0xf, false); }
+template <int N>
+__device__ __forceinline__ double row_ror(double v) {
+  return __hiloint2double(row_ror<N>(__double2hiint(v)), row_ror<N>(__double2loint(v)));
+}
+template <int N>
+__device__ __forceinline__ float row_ror(float v) { return __int_as_float(row_ror<N>(__float_as_int(v))); }
+template <class T>
+__device__ __forceinline__ T row_sum(T v) {
+  v += row_ror<8>(v); v += row_ror<4>(v); v += row_ror<2>(v); v += row_ror<1>(v);
   return v;
 }
-template <int L>
-__device__ __forceinline__ float wave_max_from(float v) {
-#pragma unroll
-  for (int o = 32; o >= L; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-  return v;
+template <class T>
+__device__ __forceinline__ T sums4x(T a, T b, T c, T d) {
+  half_swap(a, b); half_swap(c, d);
+  T u = a + b, w = c + d;          // lower half of the lanes: sums of a and c, upper half: of b and d
+  row_swap(u, w);                  // rows 0, 2: u; rows 1, 3: w
+  return row_sum(u + w);
 }
-template <int L>
-__device__ __forceinline__ int wave_min_from(int v) {
-#pragma unroll
-  for (int o = 32; o >= L; o >>= 1) v = min(v, __shfl_xor(v, o));
-  return v;
+template <class T>
+__device__ __forceinline__ T sums2x(T a, T b) { return sums4x(a, b, (T)0, (T)0); }
+// the larger value over the wave of a in the lower half of the lanes, of b in the upper half
+__device__ __forceinline__ float maxs2x(float a, float b) {
+  half_swap(a, b);
+  float u = fmaxf(a, b), w = u;
+  row_swap(u, w);
+  u = fmaxf(u, w);
+  u = fmaxf(u, row_ror<8>(u)); u = fmaxf(u, row_ror<4>(u)); u = fmaxf(u, row_ror<2>(u));
+  return fmaxf(u, row_ror<1>(u));
 }
 
 template <int NW>
-struct PartShared {
-  double d[NW][7];
-  int l[NW][3];
-  float f[NW];
-  int i[NW];
-};
+struct PartShared { Part w[NW]; };
 
-// Reduce one tile's contributions (every thread of the block calls this) and write its Part.  Only
-// the first of each atom's TPA lanes holds values, so the shuffle tree of each wave runs over those
-// lanes only; a wave's noise sum (at most 64 integers below 2^23 in magnitude) fits 32 bits.  The
-// energy is reduced only where it is reported (with_pe, uniform over the block).  Thread 0 then
-// adds the NW wave results in order.
-template <int NT, int TPA>
+// Reduce one tile's contributions (every thread of the block calls this) and write its Part: each wave
+// its sums, then, in a block of several waves, the wave results in order.  A wave's noise sum (at most
+// 64 integers below 2^23 in magnitude) fits 32 bits.  The energy is reduced only where it is reported
+// (with_pe, uniform over the block).
+template <int NT>
 __device__ __forceinline__ void write_part(Part* parts, int part, const double V[6], double pe, bool with_pe,
-                                           const long long xi[3], float maxd2, int status,
+                                           const int xi[3], float maxd2, float step2, int status,
                                            PartShared<NT / 64>& sh) {
-  const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
-  double r[7];
-#pragma unroll
-  for (int q = 0; q < 6; ++q) r[q] = wave_sum_from<TPA>(V[q]);
-  r[6] = with_pe ? wave_sum_from<TPA>(pe) : 0.0;
-  int x[3];
-#pragma unroll
-  for (int q = 0; q < 3; ++q) x[q] = wave_sum_from<TPA>((int)xi[q]);
-  const float m = wave_max_from<TPA>(maxd2);
-  const int st = wave_min_from<TPA>(status);
-  if (ln == 0) {
-#pragma unroll
-    for (int q = 0; q < 7; ++q) sh.d[wv][q] = r[q];
-#pragma unroll
-    for (int q = 0; q < 3; ++q) sh.l[wv][q] = x[q];
-    sh.f[wv] = m;
-    sh.i[wv] = st;
+  constexpr int NW = NT / 64;
+  const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63, row = ln >> 4;
+  const double v0 = sums4x(V[0], V[1], V[2], V[3]), v1 = sums2x(V[4], V[5]);
+  const double e = with_pe ? wave_sum(pe) : 0.0;
+  const int x = sums4x(xi[0], xi[1], xi[2], 0);
+  const float m = maxs2x(maxd2, step2);
+  const int st = __any(status != 0) ? wave_min(status) : 0;
+  Part& p = NW == 1 ? parts[part] : sh.w[wv];
+  const int q = ((row & 1) << 1) | (row >> 1);     // which of four values this row holds
+  if ((ln & 15) == 0) {
+    p.V[q] = v0;
+    if (q < 3) p.xi[q] = x;
+    if ((row & 1) == 0) p.V[4 + (row >> 1)] = v1;
+    if (row == 0) { p.pe = e; p.maxd2 = m; p.status = st; }
+    if (row == 2) p.step2 = m;
   }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    Part& p = parts[part];
-    double acc[7];
-    long long la[3] = {0, 0, 0};
-    float mm = 0.f;
-    int ss = 0;
+  if constexpr (NW > 1) {
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      Part r = sh.w[0];
+      for (int w = 1; w < NW; ++w) {
+        const Part& o = sh.w[w];
 #pragma unroll
-    for (int q = 0; q < 7; ++q) acc[q] = 0.0;
-    for (int w = 0; w < NT / 64; ++w) {
+        for (int k = 0; k < 6; ++k) r.V[k] += o.V[k];
+        r.pe += o.pe;
 #pragma unroll
-      for (int q = 0; q < 7; ++q) acc[q] += sh.d[w][q];
-#pragma unroll
-      for (int q = 0; q < 3; ++q) la[q] += sh.l[w][q];
-      mm = fmaxf(mm, sh.f[w]);
-      ss = min(ss, sh.i[w]);
+        for (int k = 0; k < 3; ++k) r.xi[k] += o.xi[k];
+        r.maxd2 = fmaxf(r.maxd2, o.maxd2);
+        r.step2 = fmaxf(r.step2, o.step2);
+        r.status = min(r.status, o.status);
+      }
+      parts[part] = r;
     }
-#pragma unroll
-    for (int q = 0; q < 6; ++q) p.V[q] = acc[q];
-    p.pe = acc[6];
-    p.xi[0] = la[0]; p.xi[1] = la[1]; p.xi[2] = la[2];
-    p.maxd2 = mm;
-    p.status = ss;
   }
 }
 
@@ -672,6 +769,12 @@ struct ListVec {
       w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
     }
   }
+  // the entries are waited for here whether or not they are used, so that the compiler does not put
+  // off their request until it has seen the list's length
+  __device__ void arrived() {
+#pragma unroll
+    for (int q = 0; q < W; ++q) asm volatile("" : "+v"(w[q]));
+  }
   __device__ int get(int u) const {
     if constexpr (sizeof(LT) == 2) return (int)((w[u >> 1] >> ((u & 1) * 16)) & 0xffffu);
     else return (int)w[u];
@@ -682,7 +785,7 @@ static_assert(8 % UNR == 0, "a trip's entries must lie in one list block");
 // One lane's walk over atom i's list.  Per trip the lane takes UNR consecutive entries (one vector
 // load) and the TPA lanes of the atom take consecutive groups of UNR.  The next trip's entries are
 // requested right after this trip's gathers are issued, so a trip waits for one memory round trip
-// (the gathers), not two.  Entries at or past nn gather the cell's first atom and come back with
+// (the gathers), not two.  Entries at or past the end gather the cell's first atom and come back with
 // ok = false: the pair loops run straight-line code and mask those slots out.  sc points at the
 // cell's first atom.
 template <class P, int TPA, class LT>
@@ -691,63 +794,190 @@ struct NbrWalk {
   unsigned np, ii;
   int nn, k0, lb;
   ListVec<LT> nx;
-  __device__ NbrWalk(const MDArgs& a, long long i, int nn_, int lane)
-      : list((const LT*)a.nbr), np((unsigned)a.npad), ii((unsigned)i), nn(nn_), k0(lane * UNR), lb(a.lblk), nx{} {
-    if (k0 < nn) nx.load(list + list_index((unsigned)k0, np, ii, lb));
+  __device__ NbrWalk(const MDArgs& a, long long i, int lane)
+      : list((const LT*)a.nbr), np((unsigned)a.npad), ii((unsigned)i), nn(a.nn[i]), k0(lane * UNR), lb(a.lblk), nx{} {
+    // not waiting for the length
+    if (k0 < a.maxnb) nx.load(list + list_index((unsigned)k0, np, ii, lb));
   }
   __device__ bool more() const { return k0 < nn; }
-  __device__ void next(const typename P::S* sc, typename P::S sj[UNR], bool ok[UNR]) {
+  __device__ void next(const typename P::S* sc, typename P::S sj[UNR], bool ok[UNR], int j[UNR]) {
 #pragma unroll
     for (int u = 0; u < UNR; ++u) {
       ok[u] = k0 + u < nn;
-      sj[u] = P::load_rel(sc, ok[u] ? nx.get(u) : 0);
+      j[u] = ok[u] ? nx.get(u) : 0;
+      sj[u] = P::load_rel(sc, j[u]);
     }
     k0 += UNR * TPA;
     if (k0 < nn) nx.load(list + list_index((unsigned)k0, np, ii, lb));
   }
 };
 
-// Kremer-Grest: LJ truncated and shifted at rc on every listed pair + FENE on bonds; then the
-// integration tail.  TPA lanes share one atom's neighbour list.
+// The pruned list: of the full list's entries, which reach to rc + skin, those that were within
+// sqrt(prune_rc2) when a pass last walked the full list, kept for each of the atom's TPA lanes apart and
+// in order.  A lane therefore adds the same pairs in the same order from either list - the entries left
+// out add exact zeros - and the forces do not depend on which list a step walked.  Trip t of lane l of
+// atom i: UNR entries at ((t npad + i) TPA + l) UNR, so a wave reads its trips in one piece.
+// A pair left out was at least sqrt(prune_rc2) apart, so the list is complete while no atom has moved
+// further than (sqrt(prune_rc2) - rc) / 2 since: every step adds its largest displacement to the
+// cell's pmove, and past prune_move the cell's next pass prunes again (reduce_cell).
+// Kremer-Grest lists shrink from ~21 entries to ~9 this way, copper's from 237 to ~140.  A pass over 5.1 M
+// Kremer-Grest beads takes 269 us on the pruned list and 450 where it writes it, 330 on the average of a
+// run, against 398 on the full list; copper's two passes over 512 000 atoms 105 + 152 against 129 + 194.
+// Pruning in a walk of its own before the forces (FP32 distances only) was slower: 590 us.
 template <class P, int TPA, class LT>
-__global__ __launch_bounds__(TILE * TPA) void k_force_kg(MDArgs a, int mode) {
+struct PruneWalk {
+  const LT* p;
+  size_t stride;
+  int n, k;
+  ListVec<LT> nx;
+  __device__ PruneWalk(const MDArgs& a, long long i, int lane)
+      : p((const LT*)a.pl + ((size_t)i * TPA + lane) * UNR), stride((size_t)a.npad * TPA * UNR), n(a.pn[(size_t)i * TPA + lane]), k(0), nx{} {
+    nx.load(p);                    // not waiting for the length
+  }
+  __device__ bool more() const { return k < n; }
+  __device__ void next(const typename P::S* sc, typename P::S sj[UNR], bool ok[UNR], int j[UNR]) {
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) {
+      ok[u] = k + u < n;
+      j[u] = ok[u] ? nx.get(u) : 0;
+      sj[u] = P::load_rel(sc, j[u]);
+    }
+    k += UNR;
+    p += stride;
+    if (k < n) nx.load(p);
+  }
+};
+// The writer: a lane's kept entries are collected in LDS, four trips deep, and go out as whole trips
+// when some lane of the wave has three of them (a branch and a store per entry took copper's density
+// pass from 127 to 319 us where it prunes).
+template <int NT, class LT>
+struct PruneBuf { LT e[4][NT][UNR]; };
+template <int TPA, class LT>
+struct PruneWriter {
+  static constexpr int NT = TILE * TPA;
+  PruneBuf<NT, LT>& buf;
+  LT* p;
+  size_t stride;
+  unsigned n = 0, out = 0;         // entries kept, trips stored
+  __device__ PruneWriter(const MDArgs& a, long long i, int lane, PruneBuf<NT, LT>& b)
+      : buf(b), p((LT*)a.pl + ((size_t)i * TPA + lane) * UNR), stride((size_t)a.npad * TPA * UNR) {}
+  __device__ void keep(bool yes, int j) {
+    if (yes) buf.e[(n / UNR) & 3][threadIdx.x][n % UNR] = (LT)j;
+    n += yes ? 1u : 0u;
+  }
+  __device__ void store() {
+    struct alignas(sizeof(LT) * UNR) Trip { LT e[UNR]; };
+    *(Trip*)p = *(const Trip*)buf.e[out & 3][threadIdx.x];
+    p += stride;
+    ++out;
+  }
+  // after a trip: at most 2 whole trips and 3 entries stay, and the next adds at most UNR
+  __device__ void trip() {
+    if (__any(n / UNR - out >= 3u))
+      while (n / UNR > out) store();
+  }
+  __device__ void done(const MDArgs& a, long long i, int lane) {
+    a.pn[(size_t)i * TPA + lane] = (unsigned short)n;
+    while (n > out * UNR) store();               // the last one perhaps partly filled
+  }
+};
+struct NoWriter {
+  __device__ void keep(bool, int) {}
+  __device__ void trip() {}
+};
+// whether this pass over a cell walks the full list and writes the pruned one
+__device__ __forceinline__ bool prune_now(const MDArgs& a, const CellDev& C) {
+  return a.pl && (a.prune_mode == 0 ? C.prune != 0 : a.prune_mode == 1);
+}
+// The end of both force passes: the lanes' sums of each atom, its integration tail (first lane) and the
+// tile's Part.
+template <class P, int TPA>
+__device__ __forceinline__ void finish_atoms(const MDArgs& a, const CellK<P>& ck, const Tile& t, int tb, long long i, int lane,
+                                             bool active, int mode, const typename P::R f[3], const double w[6], double PE,
+                                             const TailIn& in, int status, PartShared<TPA>& psh) {
+  double W[6], K[6] = {0, 0, 0, 0, 0, 0};
+#pragma unroll
+  for (int q = 0; q < 6; ++q) W[q] = 0.5 * lane_sum<TPA>(w[q]);
+  const double fc0 = (double)lane_sum<TPA>(f[0]), fc1 = (double)lane_sum<TPA>(f[1]), fc2 = (double)lane_sum<TPA>(f[2]);
+  TailOut o;
+  o.maxd2 = o.step2 = 0.f;
+  o.xi[0] = o.xi[1] = o.xi[2] = 0;
+  if (lane != 0) {
+#pragma unroll
+    for (int q = 0; q < 6; ++q) W[q] = 0.0;
+    PE = 0.0;
+  }
+  if (active && lane == 0) {
+    atom_tail<P>(a, ck, t.cell, i, fc0, fc1, fc2, mode, o, in);
+#pragma unroll
+    for (int q = 0; q < 6; ++q) K[q] = o.K[q];
+  }
+  double V[6];
+  part_values(a, mode, W, K, V);
+  write_part<TILE * TPA>(a.parts, tb, V, PE, mode != MODE_STEP, o.xi, o.maxd2, o.step2, status, psh);
+  work_clear(a);                   // here and not earlier: a store ahead of the loads would keep them off the scalar cache
+}
+
+// Kremer-Grest: LJ truncated and shifted at rc on every listed pair + FENE on bonds; then the
+// integration tail.  TPA lanes share one atom's neighbour list.  MID: the middle steps of a run
+// (MODE_STEP), where no energy is reported: neither its terms nor the logarithm of the bonds are
+// evaluated.
+template <class P, int TPA, class LT, bool MID>
+__global__ __launch_bounds__(TILE * TPA) void k_force_kg(MDArgs a, int mode_) {
   using R = typename P::R;
   constexpr int NT = TILE * TPA;
+  constexpr bool LDS_TAIL = TPA == 1 && sizeof(LT) == 2;
   __shared__ PartShared<NT / 64> psh;
-  work_clear(a);
+  __shared__ __attribute__((aligned(16))) char tile_mem[LDS_TAIL ? sizeof(TileLds) : 16];
+  TileLds& L = *(TileLds*)tile_mem;
+  __shared__ __attribute__((aligned(16))) PruneBuf<NT, LT> pbuf;
+  const int mode = MID ? (int)MODE_STEP : mode_;
   const int tb = block_tile_xcd(a.ntiles, blockIdx.x);
   if (tb >= a.ntiles) return;
   const Tile t = a.tiles[tb];
   const CellDev& C = a.cells[t.cell];
+  const CellK<P> ck(C);
+  const int coff = C.off;
+  const bool prune = prune_now(a, C);
   const int slot = threadIdx.x / TPA, lane = threadIdx.x % TPA;
-  const bool skip = (mode == MODE_PRIME && !C.pending) || (mode == MODE_STATIC && C.fdone);
+  const bool skip = !MID && ((mode == MODE_PRIME && !C.pending) || (mode == MODE_STATIC && C.fdone));
   const bool active = slot < t.count && !skip;
   const long long i = (long long)t.begin + slot;
   R f[3] = {0, 0, 0}, pe = 0;
   double w[6] = {0, 0, 0, 0, 0, 0};
-  double xi[3] = {0.0, 0.0, 0.0};
+  TailIn in;
   int status = 0;
+  if constexpr (LDS_TAIL) {
+    if (!skip) tile_prefetch(a, t, L);
+  }
   if (active) {
     // the atom's own fixed-point coordinates are recomputed from its position (they are stored only
     // for the neighbours' gathers): the position is read here for the drift anyway
-    xi[0] = a.x[i]; xi[1] = a.y[i]; xi[2] = a.z[i];
-    const typename P::S si = fixed_pos<P>(C, xi[0], xi[1], xi[2]);
-    const int nn = a.nn[i];
-    const R rc2 = (R)a.rc2, sig2 = (R)a.lj_sig2, e24 = (R)(24.0 * a.lj_eps), e4 = (R)(4.0 * a.lj_eps), sh = (R)a.lj_shift;
-    const typename P::Geo g = P::geo(C);
-    const typename P::S* sc = (const typename P::S*)a.s_cur + C.off;
-    // the pair energy is summed only where it is reported: not in the middle steps of a run
-    auto pairs = [&](auto with_pe) {
-      for (NbrWalk<P, TPA, LT> walk(a, i, nn, lane); walk.more();) {
+    in.x[0] = a.x[i]; in.x[1] = a.y[i]; in.x[2] = a.z[i];
+    const R rc2 = (R)a.rc2, rp2 = (R)a.prune_rc2, sig2 = (R)a.lj_sig2, e24 = (R)(24.0 * a.lj_eps), e4 = (R)(4.0 * a.lj_eps), sh = (R)a.lj_shift;
+    const typename P::Geo& g = ck.g;
+    const typename P::S* sc = (const typename P::S*)a.s_cur + coff;
+    typename P::S si;
+    // the walk comes with its length and first entries requested, beside the position: one round trip
+    auto pairs = [&](auto&& walk, auto&& out) {
+      si = fixed_pos<P>(ck, in.x[0], in.x[1], in.x[2]);
+      walk.nx.arrived();
+      if constexpr (LDS_TAIL) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) L.x[q][slot] = in.x[q];
+      }
+      while (walk.more()) {
         typename P::S sj[UNR];
         bool ok[UNR];
-        walk.next(sc, sj, ok);
+        int j[UNR];
+        walk.next(sc, sj, ok, j);
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
           R d[3];
           double dd[3];
           P::sep2(sj[u], si, g, d, dd);
           const R r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+          out.keep(ok[u] && r2 < rp2, j[u]);
           const bool in = ok[u] && r2 < rc2;
           const R r2i = P::rcp(r2);
           const R s2 = sig2 * r2i;
@@ -755,62 +985,66 @@ __global__ __launch_bounds__(TILE * TPA) void k_force_kg(MDArgs a, int mode) {
           const R gr = in ? -e24 * (s6 * ((R)2 * s6 - (R)1)) * r2i : (R)0;   // (dU/dr) / r
           f[0] += gr * d[0]; f[1] += gr * d[1]; f[2] += gr * d[2];
           add_virial(w, (double)gr, dd);
-          if constexpr (decltype(with_pe)::value) pe += in ? (R)0.5 * (e4 * s6 * (s6 - (R)1) - sh) : (R)0;
+          if constexpr (!MID) pe += in ? (R)0.5 * (e4 * s6 * (s6 - (R)1) - sh) : (R)0;
         }
+        out.trip();
       }
     };
-    if (mode == MODE_STEP || mode == MODE_DRY) pairs(std::false_type{});
-    else pairs(std::true_type{});
+    if (prune) {
+      PruneWriter<TPA, LT> out(a, i, lane, pbuf);
+      pairs(NbrWalk<P, TPA, LT>(a, i, lane), out);
+      out.done(a, i, lane);
+    } else if (a.pl) {
+      pairs(PruneWalk<P, TPA, LT>(a, i, lane), NoWriter());
+    } else {
+      pairs(NbrWalk<P, TPA, LT>(a, i, lane), NoWriter());
+    }
     if (lane == 0) {
-      const int li = (int)(i - C.off);
+      const int li = (int)(i - coff);
       int bp[4];
+      if constexpr (LDS_TAIL) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): the copies into LDS have landed
+      else in.load(a, i, mode == MODE_STEP);
       if constexpr (sizeof(LT) == 2) {
-        const uint2 b = ((const uint2*)a.bond)[i];
+        const uint2 b = LDS_TAIL ? L.bond[slot] : ((const uint2*)a.bond)[i];
         bp[0] = (int)(b.x & 0xffffu); bp[1] = (int)(b.x >> 16); bp[2] = (int)(b.y & 0xffffu); bp[3] = (int)(b.y >> 16);
       } else {
         const int4 b = ((const int4*)a.bond)[i];
         bp[0] = b.x; bp[1] = b.y; bp[2] = b.z; bp[3] = b.w;
       }
       const R K = (R)a.fene_K, R02 = (R)a.fene_R02;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (bp[q] == li) continue;               // empty slot
+      auto fene = [&](int b, const typename P::S& sb) {
+        if (b == li) return;                     // empty slot
         R d[3];
         double dd[3];
-        P::sep2(P::load_rel(sc, bp[q]), si, g, d, dd);
+        P::sep2(sb, si, g, d, dd);
         const R r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
         const R tt = r2 / R02;
-        if (!(tt < (R)1)) { status = ST_BOND; continue; }
+        if (!(tt < (R)1)) { status = ST_BOND; return; }
         const R gr = K / ((R)1 - tt);
         f[0] += gr * d[0]; f[1] += gr * d[1]; f[2] += gr * d[2];
         add_virial(w, (double)gr, dd);
-        pe += (R)(-0.25 * a.fene_K * a.fene_R02) * (R)log((double)((R)1 - tt));
+        if constexpr (!MID) pe += (R)(-0.25 * a.fene_K * a.fene_R02) * (R)log((double)((R)1 - tt));
+      };
+      // both partners of a chain's bead requested together (an empty slot reads the atom itself);
+      // branch points have more
+      const typename P::S b0 = P::load_rel(sc, bp[0]), b1 = P::load_rel(sc, bp[1]);
+      fene(bp[0], b0);
+      fene(bp[1], b1);
+      if (bp[2] != li || bp[3] != li) {
+        const typename P::S b2 = P::load_rel(sc, bp[2]), b3 = P::load_rel(sc, bp[3]);
+        fene(bp[2], b2);
+        fene(bp[3], b3);
+      }
+      if constexpr (LDS_TAIL) {
+        in.v[0] = L.vx[slot]; in.v[1] = L.vy[slot]; in.v[2] = L.vz[slot];
+        in.sb = L.sb[slot];
+        in.gid = L.gid[slot];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) in.x[q] = L.x[q][slot];
       }
     }
   }
-  double W[6], K[6] = {0, 0, 0, 0, 0, 0};
-#pragma unroll
-  for (int q = 0; q < 6; ++q) W[q] = 0.5 * lane_sum<TPA>(w[q]);
-  double PE = (double)lane_sum<TPA>(pe);
-  const double fc0 = (double)lane_sum<TPA>(f[0]), fc1 = (double)lane_sum<TPA>(f[1]), fc2 = (double)lane_sum<TPA>(f[2]);
-  long long nz[3] = {0, 0, 0};
-  float maxd2 = 0.f;
-  if (lane != 0) {
-#pragma unroll
-    for (int q = 0; q < 6; ++q) W[q] = 0.0;
-    PE = 0.0;
-  }
-  if (active && lane == 0 && mode != MODE_DRY) {
-    TailOut o;
-    atom_tail<P>(a, C, t.cell, i, fc0, fc1, fc2, mode, o, xi);
-#pragma unroll
-    for (int q = 0; q < 6; ++q) K[q] = o.K[q];
-    nz[0] = o.xi[0]; nz[1] = o.xi[1]; nz[2] = o.xi[2];
-    maxd2 = o.maxd2;
-  }
-  double V[6];
-  part_values(a, mode, W, K, V);
-  write_part<NT, TPA>(a.parts, tb, V, PE, mode != MODE_STEP, nz, maxd2, status, psh);
+  finish_atoms<P, TPA>(a, ck, t, tb, i, lane, active, mode, f, w, MID ? 0.0 : (double)lane_sum<TPA>(pe), in, status, psh);
 }
 
 // Sutton-Chen with n = 9, m = 6 is evaluated in powers of s3 = r^-3: with t = a / r,
@@ -828,10 +1062,11 @@ __device__ __forceinline__ double sc_fscale(const MDArgs& a) {
 }
 
 // Sutton-Chen pass 1: host density rho_i and F'(rho_i) = -eps c / (2 sqrt(rho_i)), stored in s.w
-// (times sc_fscale)
+// (times sc_fscale).  Where the cell prunes, this pass writes the pruned list that pass 2 walks.
 template <class P, int TPA, int SN, int SM, class LT>
 __global__ __launch_bounds__(TILE * TPA) void k_eam_rho(MDArgs a, int mode) {
   using R = typename P::R;
+  __shared__ __attribute__((aligned(16))) PruneBuf<TILE * TPA, LT> pbuf;
   const int tb = block_tile_xcd(a.ntiles, blockIdx.x);
   if (tb >= a.ntiles) return;
   const Tile t = a.tiles[tb];
@@ -842,30 +1077,43 @@ __global__ __launch_bounds__(TILE * TPA) void k_eam_rho(MDArgs a, int mode) {
   R rho = 0;
   if (active) {
     const typename P::S si = P::load(a.s_cur, i);
-    const int nn = a.nn[i];
     const double a3 = a.sc_a * a.sc_a * a.sc_a;
-    const R rc2 = (R)a.rc2, sa = (R)a.sc_a, sa6 = (R)(a3 * a3), rhoc = (R)a.sc_rhoc;
+    const R rc2 = (R)a.rc2, rp2 = (R)a.prune_rc2, sa = (R)a.sc_a, sa6 = (R)(a3 * a3), rhoc = (R)a.sc_rhoc;
     const typename P::Geo g = P::geo(C);
     const typename P::S* sc = (const typename P::S*)a.s_cur + C.off;
-    for (NbrWalk<P, TPA, LT> walk(a, i, nn, lane); walk.more();) {
-      typename P::S sj[UNR];
-      bool ok[UNR];
-      walk.next(sc, sj, ok);
+    auto pairs = [&](auto&& walk, auto&& out) {
+      while (walk.more()) {
+        typename P::S sj[UNR];
+        bool ok[UNR];
+        int j[UNR];
+        walk.next(sc, sj, ok, j);
 #pragma unroll
-      for (int u = 0; u < UNR; ++u) {
-        R d[3];
-        P::sep(sj[u], si, g, d);
-        const R r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
-        R tm;
-        if constexpr (SN == 9 && SM == 6) {
-          const R ri = P::rsq(r2), s3 = ri * ri * ri;
-          tm = sa6 * (s3 * s3);
-        } else {
-          R tn;
-          sc_powers<SN, SM>(sa * P::rsq(r2), a.sc_n, a.sc_m, tn, tm);
+        for (int u = 0; u < UNR; ++u) {
+          R d[3];
+          P::sep(sj[u], si, g, d);
+          const R r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+          out.keep(ok[u] && r2 < rp2, j[u]);
+          R tm;
+          if constexpr (SN == 9 && SM == 6) {
+            const R ri = P::rsq(r2), s3 = ri * ri * ri;
+            tm = sa6 * (s3 * s3);
+          } else {
+            R tn;
+            sc_powers<SN, SM>(sa * P::rsq(r2), a.sc_n, a.sc_m, tn, tm);
+          }
+          rho += (ok[u] && r2 < rc2) ? tm - rhoc : (R)0;
         }
-        rho += (ok[u] && r2 < rc2) ? tm - rhoc : (R)0;
+        out.trip();
       }
+    };
+    if (prune_now(a, C)) {
+      PruneWriter<TPA, LT> out(a, i, lane, pbuf);
+      pairs(NbrWalk<P, TPA, LT>(a, i, lane), out);
+      out.done(a, i, lane);
+    } else if (a.pl) {
+      pairs(PruneWalk<P, TPA, LT>(a, i, lane), NoWriter());
+    } else {
+      pairs(NbrWalk<P, TPA, LT>(a, i, lane), NoWriter());
     }
   }
   rho = lane_sum<TPA>(rho);
@@ -875,39 +1123,42 @@ __global__ __launch_bounds__(TILE * TPA) void k_eam_rho(MDArgs a, int mode) {
   }
 }
 
-// Sutton-Chen pass 2: pair scalar g = eps phi'(r) + (F'_i + F'_j) rho'(r), then the tail
-template <class P, int TPA, int SN, int SM, class LT>
-__global__ __launch_bounds__(TILE * TPA) void k_force_eam(MDArgs a, int mode) {
+// Sutton-Chen pass 2: pair scalar g = eps phi'(r) + (F'_i + F'_j) rho'(r), then the tail.  MID: the
+// middle steps of a run, where no energy is reported.
+template <class P, int TPA, int SN, int SM, class LT, bool MID>
+__global__ __launch_bounds__(TILE * TPA) void k_force_eam(MDArgs a, int mode_) {
   using R = typename P::R;
   constexpr int NT = TILE * TPA;
   __shared__ PartShared<NT / 64> psh;
-  work_clear(a);
+  const int mode = MID ? (int)MODE_STEP : mode_;
   const int tb = block_tile_xcd(a.ntiles, blockIdx.x);
   if (tb >= a.ntiles) return;
   const Tile t = a.tiles[tb];
   const CellDev& C = a.cells[t.cell];
+  const CellK<P> ck(C);
   const int slot = threadIdx.x / TPA, lane = threadIdx.x % TPA;
-  const bool active = slot < t.count && !(mode == MODE_PRIME && !C.pending) && !(mode == MODE_STATIC && C.fdone);
+  const bool skip = !MID && ((mode == MODE_PRIME && !C.pending) || (mode == MODE_STATIC && C.fdone));
+  const bool active = slot < t.count && !skip;
   const long long i = (long long)t.begin + slot;
   R f[3] = {0, 0, 0}, pe = 0;
   double w[6] = {0, 0, 0, 0, 0, 0};
   R fpi = 0;
+  TailIn in;
   if (active) {
     const typename P::S si = P::load(a.s_cur, i);
     fpi = P::get_w(si);
-    const int nn = a.nn[i];
     const double a3 = a.sc_a * a.sc_a * a.sc_a;
     const R rc2 = (R)a.rc2, sa = (R)a.sc_a, en = (R)(a.sc_eps * a.sc_n), m = (R)a.sc_m;
     const R eh = (R)(0.5 * a.sc_eps), phic = (R)a.sc_phic;
     const R en9 = (R)(a.sc_eps * a.sc_n * a3 * a3 * a3), eh9 = (R)(0.5 * a.sc_eps * a3 * a3 * a3);
-    const typename P::Geo g = P::geo(C);
+    const typename P::Geo& g = ck.g;
     const typename P::S* sc = (const typename P::S*)a.s_cur + C.off;
-    // the pair energy is summed only where it is reported: not in the middle steps of a run
-    auto pairs = [&](auto with_pe) {
-      for (NbrWalk<P, TPA, LT> walk(a, i, nn, lane); walk.more();) {
+    auto pairs = [&](auto&& walk, auto&& out) {
+      while (walk.more()) {
         typename P::S sj[UNR];
         bool ok[UNR];
-        walk.next(sc, sj, ok);
+        int j[UNR];
+        walk.next(sc, sj, ok, j);
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
           R d[3];
@@ -920,7 +1171,7 @@ __global__ __launch_bounds__(TILE * TPA) void k_force_eam(MDArgs a, int mode) {
           if constexpr (SN == 9 && SM == 6) {
             const R ri2 = ri * ri, s3 = ri2 * ri, s6 = s3 * s3;
             g0 = -(ri2 * s6) * (en9 * s3 + (fpi + P::get_w(sj[u])));
-            if constexpr (decltype(with_pe)::value) tn = s6 * s3;             // t^9 / a^9
+            if constexpr (!MID) tn = s6 * s3;                                 // t^9 / a^9
           } else {
             R tm;
             sc_powers<SN, SM>(sa * ri, a.sc_n, a.sc_m, tn, tm);
@@ -929,43 +1180,27 @@ __global__ __launch_bounds__(TILE * TPA) void k_force_eam(MDArgs a, int mode) {
           const R gr = in ? g0 : (R)0;
           f[0] += gr * d[0]; f[1] += gr * d[1]; f[2] += gr * d[2];
           add_virial(w, (double)gr, dd);
-          if constexpr (decltype(with_pe)::value) {
+          if constexpr (!MID) {
             if constexpr (SN == 9 && SM == 6) pe += in ? eh9 * tn - eh * phic : (R)0;
             else pe += in ? eh * (tn - phic) : (R)0;
           }
         }
       }
     };
-    if (mode == MODE_STEP || mode == MODE_DRY) pairs(std::false_type{});
-    else pairs(std::true_type{});
+    if (a.pl) pairs(PruneWalk<P, TPA, LT>(a, i, lane), NoWriter());      // pass 1 has just brought it up to date
+    else pairs(NbrWalk<P, TPA, LT>(a, i, lane), NoWriter());
+    if (lane == 0) {
+      in.load(a, i, mode == MODE_STEP);
+      if (mode == MODE_STEP) { in.x[0] = a.x[i]; in.x[1] = a.y[i]; in.x[2] = a.z[i]; }
+    }
   }
-  double W[6], K[6] = {0, 0, 0, 0, 0, 0};
-#pragma unroll
-  for (int q = 0; q < 6; ++q) W[q] = 0.5 * lane_sum<TPA>(w[q]);
-  double PE = (double)lane_sum<TPA>(pe);
-  const double fc0 = (double)lane_sum<TPA>(f[0]), fc1 = (double)lane_sum<TPA>(f[1]), fc2 = (double)lane_sum<TPA>(f[2]);
-  long long xi[3] = {0, 0, 0};
-  float maxd2 = 0.f;
-  if (lane != 0) {
-#pragma unroll
-    for (int q = 0; q < 6; ++q) W[q] = 0.0;
-    PE = 0.0;
-  } else if (active && mode != MODE_STEP && mode != MODE_DRY) {
+  double PE = MID ? 0.0 : (double)lane_sum<TPA>(pe);
+  if (!MID && active && lane == 0) {
     // embedding energy -eps c sqrt(rho) = (eps c)^2 / (2 F'(rho)), zero where rho = 0
     const double ec = a.sc_eps * a.sc_c;
     if (fpi != (R)0) PE += ec * ec * sc_fscale<SN, SM>(a) / (2.0 * (double)fpi);
   }
-  if (active && lane == 0 && mode != MODE_DRY) {
-    TailOut o;
-    atom_tail<P>(a, C, t.cell, i, fc0, fc1, fc2, mode, o);
-#pragma unroll
-    for (int q = 0; q < 6; ++q) K[q] = o.K[q];
-    xi[0] = o.xi[0]; xi[1] = o.xi[1]; xi[2] = o.xi[2];
-    maxd2 = o.maxd2;
-  }
-  double V[6];
-  part_values(a, mode, W, K, V);
-  write_part<NT, TPA>(a.parts, tb, V, PE, mode != MODE_STEP, xi, maxd2, 0, psh);
+  finish_atoms<P, TPA>(a, ck, t, tb, i, lane, active, mode, f, w, PE, in, 0, psh);
 }
 
 // First half kick and drift of a run (the remaining ones are fused into the force kernels).
@@ -978,8 +1213,8 @@ __global__ __launch_bounds__(TILE) void k_start(MDArgs a) {
   const Tile t = a.tiles[tb];
   const CellDev& C = a.cells[t.cell];
   const long long i = (long long)t.begin + threadIdx.x;
-  long long xi[3] = {0, 0, 0};
-  float maxd2 = 0.f;
+  int xi[3] = {0, 0, 0};
+  float maxd2 = 0.f, step2 = 0.f;
   if ((int)threadIdx.x < t.count) {
     const double f0 = (double)((const typename P::Fst*)a.fx)[i];
     const double f1 = (double)((const typename P::Fst*)a.fy)[i];
@@ -993,14 +1228,11 @@ __global__ __launch_bounds__(TILE) void k_start(MDArgs a) {
     typename P::R d[3];
     P::disp(sn, a.sb[i], P::geo(C), d);
     maxd2 = (float)(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-    if (a.gamma_on) {
-      int k[3];
-      noise_units(a, a.gid[i], t.cell, C.step + 1, k);
-      xi[0] = k[0]; xi[1] = k[1]; xi[2] = k[2];
-    }
+    step2 = drift2(a.dt, vx, vy, vz);
+    if (a.gamma_on) noise_units(a, a.gid[i], t.cell, C.step + 1, xi);
   }
   const double Z[6] = {0, 0, 0, 0, 0, 0};
-  write_part<TILE, 1>(a.parts, tb, Z, 0.0, false, xi, maxd2, 0, psh);
+  write_part<TILE>(a.parts, tb, Z, 0.0, false, xi, maxd2, step2, 0, psh);
 }
 
 // ------------------------------------------------------------------ initial velocities
@@ -1082,7 +1314,7 @@ __global__ __launch_bounds__(TILE) void k_fire_move(MDArgs a) {
   const Tile t = a.tiles[tb];
   const CellDev& C = a.cells[t.cell];
   const long long i = (long long)t.begin + threadIdx.x;
-  float maxd2 = 0.f;
+  float maxd2 = 0.f, step2 = 0.f;
   if ((int)threadIdx.x < t.count && !C.fdone) {
     const double f0 = (double)((const typename P::Fst*)a.fx)[i];
     const double f1 = (double)((const typename P::Fst*)a.fy)[i];
@@ -1103,10 +1335,11 @@ __global__ __launch_bounds__(TILE) void k_fire_move(MDArgs a) {
     typename P::R d[3];
     P::disp(sn, a.sb[i], P::geo(C), d);
     maxd2 = (float)(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
+    step2 = drift2(C.fdt, vx, vy, vz);
   }
   const double Z[6] = {0, 0, 0, 0, 0, 0};
-  const long long xi[3] = {0, 0, 0};
-  write_part<TILE, 1>(a.parts, tb, Z, 0.0, false, xi, maxd2, 0, psh);
+  const int xi[3] = {0, 0, 0};
+  write_part<TILE>(a.parts, tb, Z, 0.0, false, xi, maxd2, step2, 0, psh);
 }
 
 __global__ void k_fire_iters(const CellDev* cells, int ncells, int* iters, int* done) {
@@ -1143,8 +1376,8 @@ __device__ __forceinline__ void reduce_cell(const MDArgs& a, int cell, int mode,
   const int t = threadIdx.x;
   const int ntile = C.ntile, tile_off = C.tile_off;
   const int pending = C.pending, fdone = C.fdone;
-  const int cstatus = C.status, crebuild = C.rebuild, cn = C.n;
-  const float chs2 = C.hs2;
+  const int cstatus = C.status, crebuild = C.rebuild, cn = C.n, cprune = C.prune;
+  const float chs2 = C.hs2, cpmove = C.pmove;
   const double cV = C.V;
   const long long cnreb = C.nrebuild, cwcount = C.wcount, cstep = C.step;
   double cw[6];
@@ -1152,7 +1385,7 @@ __device__ __forceinline__ void reduce_cell(const MDArgs& a, int cell, int mode,
   for (int q = 0; q < 6; ++q) cw[q] = C.wsum[q];
   double V[6] = {0, 0, 0, 0, 0, 0}, pe = 0;
   long long xi[3] = {0, 0, 0};
-  float m = 0.f;
+  float m = 0.f, m2 = 0.f;
   int st = 0;
   for (int k = t; k < (t < RED_NT ? ntile : 0); k += RED_NT) {
     const Part& p = a.parts[tile_off + k];
@@ -1161,6 +1394,7 @@ __device__ __forceinline__ void reduce_cell(const MDArgs& a, int cell, int mode,
     pe += p.pe;
     xi[0] += p.xi[0]; xi[1] += p.xi[1]; xi[2] += p.xi[2];
     m = fmaxf(m, p.maxd2);
+    m2 = fmaxf(m2, p.step2);
     st = min(st, p.status);
   }
   if (mode == RED_PRIME && !pending) return;                              // uniform over the block
@@ -1172,7 +1406,7 @@ __device__ __forceinline__ void reduce_cell(const MDArgs& a, int cell, int mode,
 #pragma unroll
     for (int q = 0; q < 3; ++q) col[7 + q][t] = __longlong_as_double(xi[q]);
   }
-  const float md = wave_max(m);
+  const float md = wave_max(m), md2 = wave_max(m2);
   st = wave_min(st);
   __syncthreads();
   if (t < RED_NT) {
@@ -1202,6 +1436,13 @@ __device__ __forceinline__ void reduce_cell(const MDArgs& a, int cell, int mode,
             __double_as_longlong(grp[2][7 + q]) + __double_as_longlong(grp[3][7 + q]);
   const long long x0 = xs[0], x1 = xs[1], x2 = xs[2];
   if (st != 0 && cstatus == 0) C.status = st;
+  // the pruned list: a force pass just run has rewritten it if it was asked to; a drift uses up its margin
+  const bool moved = mode == RED_MOVE || mode == RED_START || mode == RED_STEP;
+  const bool passed = mode != RED_MOVE && mode != RED_START;
+  float pm = passed && cprune ? 0.f : cpmove;
+  if (moved) pm += 1.000001f * sqrtf(md2);
+  C.pmove = pm;
+  C.prune = (!passed && cprune) || pm > a.prune_move || (moved && md > chs2);
   if (fill && md > chs2) work_add(a, cell, ntile);
   if (mode == RED_MOVE) {                // statics: positions moved; rebuild when they left the skin
     C.rebuild = md > chs2;
@@ -2087,6 +2328,7 @@ __global__ void k_qr_commit(CellDev* cells, const Stage* st, int ncells, double 
     C.hs2 = hs2m;
   }
   C.pending = 1;
+  C.prune = 1;
 }
 
 // x <- Delta R x for every atom (affine remap, Eq. 6 applied incrementally), with the fixed-point
@@ -2116,6 +2358,7 @@ __global__ void k_set_box(CellDev* cells, int first, int count, double bw) {
   C.wcount = 0;
   C.rebuild = 1;
   C.pending = 1;
+  C.prune = 1;
 }
 
 // ------------------------------------------------------------------ stress return (Eqs. 7, 8)
@@ -2222,7 +2465,16 @@ __global__ void k_set_bin_width(CellDev* cells, int ncells, double bw) {
 
 __global__ void k_set_pending(CellDev* cells, int first, int count) {
   const int c = first + blockIdx.x * blockDim.x + threadIdx.x;
-  if (c < first + count) { cells[c].rebuild = 1; cells[c].pending = 1; }
+  if (c < first + count) { cells[c].rebuild = 1; cells[c].pending = 1; cells[c].prune = 1; }
+}
+
+// the next force pass of every cell prunes (the list's lanes per atom have changed), and, with
+// `rebuild`, builds first (the list itself has moved)
+__global__ void k_set_prune(CellDev* cells, int ncells, int rebuild) {
+  const int c = blockIdx.x * blockDim.x + threadIdx.x;
+  if (c >= ncells) return;
+  cells[c].prune = 1;
+  if (rebuild) cells[c].rebuild = 1;
 }
 
 }  // namespace rcell

@@ -67,6 +67,10 @@ struct rcell_ctx {
   int *gid = nullptr, *pos_of = nullptr;
   char* pscr = nullptr;           // reorder scratch rows
   void* nbr = nullptr;
+  void* pl = nullptr;             // pruned list and its lengths (null: not worth it, or no memory for it)
+  unsigned short* pn = nullptr;
+  double prune_skin = 0.0;        // it reaches to rc + prune_skin; 0: not used
+  int prune_cap = 0;              // list capacity that pl was allocated for
   bool list16 = false;            // 16-bit list entries (every cell has at most 65536 atoms, mixed)
   bool small_cells = false;       // every cell has at most PREP_ATOMS atoms
   bool cell_prep = false;         // rebuild preparation by one block per cell (k_cell_prep)
@@ -219,6 +223,11 @@ MDArgs make_args(const rcell_ctx* c) {
   a.work_cells = c->work_cells; a.work_tstart = c->work_tstart; a.work_pack = c->work_pack;
   a.bin_factor = c->bin_factor;
   const rcell_params& p = c->p;
+  // entries are kept a little beyond rc + prune_skin and served a little short of half of it: the
+  // FP32 rounding of the distance test and of the summed displacements stays inside that margin
+  a.pl = c->pl; a.pn = c->pn;
+  a.prune_rc2 = (p.rc + c->prune_skin) * (p.rc + c->prune_skin) * (1.0 + 1e-5);
+  a.prune_move = (float)(0.5 * c->prune_skin - 1e-6 * p.rc);
   // integrator constants: the same expressions, in the same order, as the method's definition
   a.dt = p.dt;
   a.fire_ftol2 = c->fire_ftol2;
@@ -289,13 +298,16 @@ template <class P, int TPA, int SN, int SM, class LT>
 void force_eam_t(rcell_ctx* c, const MDArgs& a, int mode) {
   const dim3 grid(tile_grid(c->ntiles)), block(TILE * TPA);
   LAUNCH_PASS(c, 1, (k_eam_rho<P, TPA, SN, SM, LT>), grid, block, a, mode);
-  LAUNCH_PASS(c, 0, (k_force_eam<P, TPA, SN, SM, LT>), grid, block, a, mode);
+  if (mode == MODE_STEP) LAUNCH_PASS(c, 0, (k_force_eam<P, TPA, SN, SM, LT, true>), grid, block, a, mode);
+  else LAUNCH_PASS(c, 0, (k_force_eam<P, TPA, SN, SM, LT, false>), grid, block, a, mode);
 }
 
 template <class P, int TPA, class LT>
 void force_t(rcell_ctx* c, const MDArgs& a, int mode) {
   if (c->p.potential == RCELL_POT_KG) {
-    LAUNCH_PASS(c, 0, (k_force_kg<P, TPA, LT>), dim3(tile_grid(c->ntiles)), dim3(TILE * TPA), a, mode);
+    const dim3 grid(tile_grid(c->ntiles)), block(TILE * TPA);
+    if (mode == MODE_STEP) LAUNCH_PASS(c, 0, (k_force_kg<P, TPA, LT, true>), grid, block, a, mode);
+    else LAUNCH_PASS(c, 0, (k_force_kg<P, TPA, LT, false>), grid, block, a, mode);
   } else if (a.sc_n == 9 && a.sc_m == 6) {      // copper, nickel: exponents fixed at compile time
     force_eam_t<P, TPA, 9, 6, LT>(c, a, mode);
   } else {
@@ -492,6 +504,46 @@ int ensure_list_capacity(rcell_ctx* c, int need) {
   return RCELL_OK;
 }
 
+// The pruned list's reach beyond rc.  A pass over it costs ((rc + s) / (rc + skin))^3 of a pass over the full
+// list; pruning costs about 1.2 passes and serves until the fastest atom (~5 thermal speeds) has come
+// s / 2 along.  s minimises the sum (one step of the fixed point of its derivative); where the sum saves
+// less than a tenth of the pair work (glassy cells: rc = 2.5, skin = 0.3), the full list is walked.
+double prune_reach(const rcell_params& p) {
+  const double rcs = p.rc + p.skin;
+  const double step = 5.0 * p.dt * std::sqrt(p.kB * p.temperature / (p.mass * p.mvv2e));
+  if (!(step > 0.0) || !std::isfinite(step)) return 0.3 * p.skin > 1e-3 * p.rc ? 0.3 * p.skin : 0.0;
+  const double k = 0.8 * step * rcs * rcs * rcs;
+  const double s0 = std::sqrt(k) / p.rc, s = std::sqrt(k) / (p.rc + s0);
+  const double cost = std::pow((p.rc + s) / rcs, 3.0) + 1.2 * 2.0 * step / s;
+  return s < p.skin && s > 1e-3 * p.rc && cost < 0.9 ? s : 0.0;
+}
+
+// room for the pruned list beside a full list of the present capacity; without the memory for it (or
+// beyond its 16-bit lengths) the passes walk the full list
+void ensure_pruned(rcell_ctx* c) {
+  if (c->prune_skin <= 0.0 || c->prune_cap == c->maxnb) return;
+  drop_graphs(c);
+  dfree(c, c->pl); dfree(c, c->pn);
+  char* q = nullptr;
+  unsigned short* n = nullptr;
+  const std::string err = c->err;
+  // the lanes of an atom fill whole trips of their own: up to 16 lanes x UNR entries
+  const size_t cap = ((size_t)c->maxnb + 16 * UNR - 1) / (16 * UNR) * (16 * UNR);
+  if (c->maxnb > 65535 || dalloc(c, &n, (size_t)16 * c->npad) ||
+      dalloc(c, &q, cap * c->npad * (c->list16 ? sizeof(uint16_t) : sizeof(int)))) {
+    if (n) dfree(c, n);
+    n = nullptr; q = nullptr;
+    c->err = err;
+  }
+  c->pl = q;
+  c->pn = q ? n : nullptr;
+  c->prune_cap = c->maxnb;
+}
+
+void set_prune(rcell_ctx* c, int rebuild) {
+  hipLaunchKernelGGL(k_set_prune, dim3((c->ncells + 63) / 64), dim3(64), 0, c->stream, c->cells, c->ncells, rebuild);
+}
+
 void destroy_all(rcell_ctx* c) {
   if (c->stream) (void)hipStreamSynchronize(c->stream);
   drop_graphs(c);
@@ -533,6 +585,7 @@ int deformation_common(rcell_ctx* c, const double* F_dev) {
   const int cap = list_capacity(dens, rcs);
   const int relist = cap > c->maxnb;               // a reallocated list must be rebuilt everywhere
   if ((e = ensure_list_capacity(c, cap))) return e;
+  ensure_pruned(c);
   hipLaunchKernelGGL(k_qr_commit, dim3((nc + 63) / 64), dim3(64), 0, c->stream, c->cells, c->stage, nc, c->p.rc,
                      rcs, bin_width(c), relist);
   const MDArgs a = make_args(c);
@@ -668,13 +721,14 @@ int rcell_create(const rcell_params* params, const rcell_cell_init* cells, int32
   const size_t ssz = c->fp64 ? sizeof(S64) : sizeof(int4);
   int e;
   char *f0, *f1, *f2, *s0, *s1, *bondp;
+  const long long Nr = N + 4;      // room for the 16-byte reads at a ragged tile's end (tile_prefetch)
   if ((e = dalloc(c, &c->x, N)) || (e = dalloc(c, &c->y, N)) || (e = dalloc(c, &c->z, N)) ||
-      (e = dalloc(c, &c->vx, N)) || (e = dalloc(c, &c->vy, N)) || (e = dalloc(c, &c->vz, N)) ||
+      (e = dalloc(c, &c->vx, Nr)) || (e = dalloc(c, &c->vy, Nr)) || (e = dalloc(c, &c->vz, Nr)) ||
       (e = dalloc(c, &f0, fsz * N)) || (e = dalloc(c, &f1, fsz * N)) || (e = dalloc(c, &f2, fsz * N)) ||
       (e = dalloc(c, &s0, ssz * N)) || (e = dalloc(c, &s1, ssz * N)) ||
-      (e = dalloc(c, &c->sb, N)) || (e = dalloc(c, &bondp, (c->list16 ? 8 : 16) * (size_t)N)) ||
+      (e = dalloc(c, &c->sb, Nr)) || (e = dalloc(c, &bondp, (c->list16 ? 8 : 16) * (size_t)Nr)) ||
       (e = dalloc(c, &c->bond0, N)) ||
-      (e = dalloc(c, &c->gid, N)) || (e = dalloc(c, &c->pos_of, N)) ||
+      (e = dalloc(c, &c->gid, Nr)) || (e = dalloc(c, &c->pos_of, N)) ||
       (e = dalloc(c, &c->pscr, (6 * sizeof(double) + ssz + 2 * sizeof(int)) * (size_t)c->npad)) ||
       (e = dalloc(c, &c->nn, N)) ||
       (e = dalloc(c, &c->abin, N)) || (e = dalloc(c, &c->binned, N)) || (e = dalloc(c, &c->bkey, N)) ||
@@ -743,6 +797,8 @@ int rcell_create(const rcell_params* params, const rcell_cell_init* cells, int32
       hipMemsetAsync(s1, 0, ssz * N, c->stream) || hipStreamSynchronize(c->stream))
     return bail(fail(c, RCELL_ERR_DEVICE, "initial upload failed"));
   if ((e = layout_bins(c, need_bins))) return bail(e);
+  c->prune_skin = prune_reach(p);
+  ensure_pruned(c);
   hipLaunchKernelGGL(k_reset_order, dim3(tile_grid(c->ntiles)), dim3(TILE), 0, c->stream, make_args(c), 0, ncells);
   if (std::any_of(mb.begin(), mb.end(), [](int f) { return f != 0; })) {   // Maxwell-Boltzmann from the seed
     int* dflag = c->iscratch;
@@ -983,7 +1039,12 @@ int rcell_set_state(rcell_ctx* c, int32_t cell, const double* x, const double* v
   set_occupancy(c, cell, (double)n / bins_exact(H, bin_width(c)));
   int e;
   if (need[cell] > c->bin_cap[cell] && (e = layout_bins(c, need))) return e;
+  const int cap0 = c->maxnb;
   if ((e = ensure_list_capacity(c, list_capacity(n / (H[0] * H[4] * H[8]), rcs)))) return e;
+  if (c->maxnb != cap0) {          // the list has moved: the other cells build theirs again too
+    ensure_pruned(c);
+    set_prune(c, 1);
+  }
   std::vector<double> buf(6 * n);
   for (long long i = 0; i < n; ++i)
     for (int q = 0; q < 3; ++q) { buf[q * n + i] = x[3 * i + q]; buf[(3 + q) * n + i] = v[3 * i + q]; }
@@ -1067,6 +1128,7 @@ int rcell_set_lanes(rcell_ctx* c, int32_t lanes) {
   drop_graphs(c);
   if (lanes == 1 || lanes == 2 || lanes == 4 || lanes == 8 || lanes == 16) {
     c->lanes = lanes;
+    set_prune(c, 0);               // the pruned list is kept per lane
     return RCELL_OK;
   }
   if (lanes != 0) return fail(c, RCELL_ERR_ARG, "lanes must be 0, 1, 2, 4, 8 or 16");
@@ -1098,7 +1160,9 @@ int rcell_set_lanes(rcell_ctx* c, int32_t lanes) {
   a.fx = d[6]; a.fy = d[7]; a.fz = d[8];
   for (int round = 0; round < 3 && e == hipSuccess; ++round)
     for (int v = 0; v < NV && e == hipSuccess; ++v) {
+      a.prune_mode = 1;            // this variant's pruned list, then the passes that walk it
       launch_force_args(c, a, MODE_STEP, var[v]);
+      a.prune_mode = 2;
       e = hipEventRecord(t0, c->stream);
       for (int r = 0; r < 5 && e == hipSuccess; ++r) launch_force_args(c, a, MODE_STEP, var[v]);
       if (e == hipSuccess) e = hipEventRecord(t1, c->stream);
@@ -1111,6 +1175,7 @@ int rcell_set_lanes(rcell_ctx* c, int32_t lanes) {
   if (t0) (void)hipEventDestroy(t0);
   if (t1) (void)hipEventDestroy(t1);
   (void)hipFree(tmp);
+  set_prune(c, 0);
   if (e != hipSuccess) return fail(c, RCELL_ERR_DEVICE, std::string("autotune: ") + hipGetErrorString(e));
   int best = 0;
   for (int v = 1; v < NV; ++v)
