@@ -72,8 +72,8 @@ struct rsur_ctx {
   std::string err;
   float *p = nullptr, *g = nullptr, *m1 = nullptr, *m2 = nullptr;   // K x P
   bf16* pb = nullptr;                                               // K x P (weights used)
-  bf16* pbt = nullptr;                                              // K x P, weights transposed
-  bool pbt_stale = true;                                            // pbt behind pb
+  bf16* pbf = nullptr;                                              // K x P, weights by fragments
+  bool pbf_stale = true;                                            // pbf behind pb
   std::vector<bf16*> act;                    // act[l]: K x Mp x dp[l] (act[0] shared: Mp x dp[0])
   std::vector<float*> Z;                     // Z[l]: K x Mp x dp[l + 1], hidden layers
   float* out = nullptr;                      // K x Mp x dp[L]
@@ -225,7 +225,7 @@ int rsur_create(int32_t din, int32_t width, int32_t depth, int32_t dout, int32_t
   const long long KP = (long long)c->K * c->P;
   int e;
   if ((e = ralloc(c, &c->p, KP)) || (e = ralloc(c, &c->g, KP)) || (e = ralloc(c, &c->m1, KP)) ||
-      (e = ralloc(c, &c->m2, KP)) || (e = ralloc(c, &c->pb, KP)) || (e = ralloc(c, &c->pbt, KP)))
+      (e = ralloc(c, &c->m2, KP)) || (e = ralloc(c, &c->pb, KP)) || (e = ralloc(c, &c->pbf, KP)))
     return bail(e);
   c->act.resize(c->L);
   c->Z.resize(std::max(c->L - 1, 0));
@@ -293,7 +293,7 @@ int rsur_set_params(rsur_ctx* c, int32_t member, const float* w) {
                      c->pb + off, c->P);
   RCHK(c, hipStreamSynchronize(c->stream));
   c->t[member] = 0;
-  c->pbt_stale = true;
+  c->pbf_stale = true;
   return RCELL_OK;
 }
 
@@ -338,41 +338,45 @@ int rsur_fit_norm(rsur_ctx* c, const void* X_dev, const void* Y_dev, int32_t n) 
   return RCELL_OK;
 }
 
-// inference: every layer in one fused kernel when the padded widths allow it and the batch gives
-// enough (row block, member) pairs to fill the GPU; small batches run layer by layer, whose
-// per-layer grids spread the same work over more blocks
-constexpr int FUSED_MIN_BLOCKS = 512;
+// inference: every layer in one fused kernel when the padded widths allow it.  128 rows per block read
+// the weights least often; small batches take 32 rows per block, four times as many blocks, each done
+// sooner.  The two meet at ~4000 rows of 5 members (one call, us, 128 against 32 rows per block: 1024
+// rows 33.7 / 19.7, 2048 34.4 / 26.1, 4096 37.9 / 38.8, 8192 56 / 60, 16 384 85 / 109).
+constexpr int FUSED_MIN_BLOCKS = 160;
 static bool fused_shape(const rsur_ctx* c) {
   return *std::max_element(c->dp.begin(), c->dp.end()) <= FW && c->L <= MAXL;
 }
 
-// the fused forward of every member for Mp rows into out (K x Mp x dp[L], member stride sOut)
-static void forward_fused(rsur_ctx* c, const float* X, int B, int Mp, float* out, long long sOut) {
-  if (c->pbt_stale) {
+// the fused forward of every member for B rows into out (K x Mp x dp[L], member stride sOut)
+static void forward_fused(rsur_ctx* c, const float* X, int B, float* out, long long sOut) {
+  if (c->pbf_stale) {
     for (int l = 0; l < c->L; ++l) {
-      const long long n = (long long)c->dp[l] * c->dp[l + 1];
-      hipLaunchKernelGGL(k_transpose_w, dim3((unsigned)((n + 255) / 256), c->K), dim3(256), 0, c->stream, c->pb,
-                         c->pbt, c->P, c->woff[l], c->dp[l], c->dp[l + 1]);
+      const int n = c->dp[l] / 8 * c->dp[l + 1];
+      hipLaunchKernelGGL(k_frag_w, dim3((n + 255) / 256, c->K), dim3(256), 0, c->stream, c->pb, c->pbf, c->P, c->woff[l],
+                         c->dp[l], c->dp[l + 1]);
     }
-    c->pbt_stale = false;
+    c->pbf_stale = false;
   }
   MlpArgs g{};
   g.X = X; g.B = B; g.din = c->din; g.xmu = c->xmu; g.xsd = c->xsd;
-  g.wt = c->pbt; g.sW = c->P; g.p = c->p; g.sP = c->P;
-  g.L = c->L;
+  g.wf = c->pbf; g.sW = c->P; g.p = c->p; g.sP = c->P;
+  g.L = c->L; g.dout = c->dout;
   for (int l = 0; l <= c->L; ++l) g.dp[l] = c->dp[l];
   for (int l = 0; l < c->L; ++l) { g.woff[l] = c->woff[l]; g.boff[l] = c->boff[l]; }
   g.out = out; g.sOut = sOut; g.ldo = c->dp[c->L];
-  hipLaunchKernelGGL(k_mlp_forward, dim3(Mp / 64, c->K), dim3(256), 0, c->stream, g);
+  if ((long long)((B + 127) / 128) * c->K >= FUSED_MIN_BLOCKS)
+    hipLaunchKernelGGL((k_mlp_forward<4, 8>), dim3((B + 127) / 128, c->K), dim3(512), 0, c->stream, g);
+  else
+    hipLaunchKernelGGL((k_mlp_forward<1, 8>), dim3((B + 31) / 32, c->K), dim3(512), 0, c->stream, g);
 }
 
 static void forward_infer(rsur_ctx* c, const float* X, int B, int Mp) {
-  if (!fused_shape(c) || (long long)(Mp / 64) * c->K < FUSED_MIN_BLOCKS) {
+  if (!fused_shape(c)) {
     normalise_inputs(c, X, B, Mp);
     forward_layers(c, Mp);
     return;
   }
-  forward_fused(c, X, B, Mp, c->out, (long long)c->Mp * c->dp[c->L]);
+  forward_fused(c, X, B, c->out, (long long)c->Mp * c->dp[c->L]);
 }
 
 static int forward_common(rsur_ctx* c, const void* X_dev, int32_t B, float* mean, float* var, float* members) {
@@ -403,7 +407,7 @@ int rsur_forward_static(rsur_ctx* c, const void* X_dev, int32_t B, void* mean_de
   if (static_scratch_ptr(&out) != RCELL_OK) return rfail(c, RCELL_ERR_DEVICE, "static scratch address");
   const int Mp = pad64(B);
   const long long sOut = (long long)Mp * c->dp[c->L];
-  forward_fused(c, (const float*)X_dev, B, Mp, out, sOut);
+  forward_fused(c, (const float*)X_dev, B, out, sOut);
   const long long n = (long long)B * c->dout;
   hipLaunchKernelGGL(k_ensemble, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, out, sOut,
                      c->dp[c->L], c->K, B, c->dout, c->ymu, c->ysd, (float*)mean_dev, (float*)var_dev, (float*)nullptr);
@@ -474,7 +478,7 @@ int rsur_train_step(rsur_ctx* c, const void* X_dev, const void* Y_dev, int32_t B
   const long long n = (long long)c->K * c->P;
   hipLaunchKernelGGL(k_adam, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, c->p, c->g, c->m1, c->m2,
                      c->pb, c->P, c->K, c->c1, c->c2, lr, 0.9f, 0.999f, 1e-8f);
-  c->pbt_stale = true;
+  c->pbf_stale = true;
   RCHK(c, hipGetLastError());
   if (loss) {
     RCHK(c, hipMemcpyAsync(loss, c->loss, sizeof(float) * c->K, hipMemcpyDeviceToHost, c->stream));

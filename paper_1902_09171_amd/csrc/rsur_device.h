@@ -105,96 +105,221 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
 }
 
 // ------------------------------------------------------------------ fused inference
-// Every layer of one member for 64 rows in one block: the activations stay in LDS (one buffer,
-// overwritten in place between two barriers per layer), the weights are read from L2 in a
-// transposed copy (WT[n][k], so a lane's 8 consecutive k are one 16-byte load) straight into the
-// matrix-core B operand, and the first layer normalises the raw inputs itself.  Wave w computes
-// output columns [64 w, 64 w + 64) of a layer as 2 x 2 tiles of v_mfma_f32_32x32x16_bf16 over k
-// in steps of 16 - the operand layout and k order of k_gemm, so the outputs equal the layer-wise
-// forward bit for bit.  Padded widths up to FW.
+// Every layer of one member for 32 RT rows in one block of NW waves: the activations stay in LDS (one
+// buffer, overwritten in place between two barriers per layer) and the first layer normalises the raw
+// inputs itself.  A wave computes the transposed product: 32 output features of the weights (operand A)
+// by 32 rows of activations (operand B) per v_mfma_f32_32x32x16_bf16, so an accumulator's four
+// consecutive registers are four consecutive features of one row - one 8-byte LDS store after the
+// activation, where the row-major product took four 2-byte ones.  Over k in steps of 16 from zero, the
+// order of k_gemm, so the outputs equal the layer-wise forward bit for bit.
+//
+// The weights come from a copy laid out by fragments (k_frag_w): the 64 lanes of a wave read one
+// operand as 1 KB of consecutive memory (a transposed copy gave 32 pieces of 32 bytes).  They are read
+// once per block, so the large variant takes 128 rows per block (64 before); the small one spreads 32
+// rows over 8 waves and requests a layer's whole operand at once, since a small batch waits for latency.
+//
+// Bound: per block of 128 rows the matrix products take ~16 000 cycles of every SIMD (32 each) and SiLU
+// ~25 000 (12 instructions, two of them transcendental, per 64 elements); two blocks per CU run them side by
+// side.  Measured (one MI355X, 153 -> 4 x 256 -> 6, 5 members): 60 001 rows 255 us, 683 with 64 rows per block,
+// a transposed weight copy, a full division and inputs normalised one load at a time (304 us with four
+// waves of two tiles instead of eight of one, 288 in the end); 256 rows 15.8 us, ~44 layer by layer in
+// six launches.
 constexpr int FW = 256, FLD = FW + 8, MAXL = 8;
 
 struct MlpArgs {
   const float* X; int B, din;
   const float *xmu, *xsd;
-  const bf16* wt; long long sW;              // transposed BF16 weights, member stride
+  const bf16* wf; long long sW;              // BF16 weights by fragments, member stride
   const float* p; long long sP;              // FP32 parameters (biases), member stride
-  int L;
+  int L, dout;
   int dp[MAXL + 1];
   long long woff[MAXL], boff[MAXL];
   float* out; long long sOut; int ldo;       // K x Mp x dp[L]
 };
 
-__global__ __launch_bounds__(256, 2) void k_mlp_forward(MlpArgs g) {
-  __shared__ __attribute__((aligned(16))) bf16 act[64 * FLD];
-  const int mem = blockIdx.y;
-  const int m0 = blockIdx.x * 64;
-  const int t = threadIdx.x, w = t >> 6, l = t & 63;
-  const int d0 = g.dp[0];
-  for (int e = t; e < 64 * d0; e += 256) {
-    const int r = e / d0, k = e % d0, m = m0 + r;
-    act[r * FLD + k] = (m < g.B && k < g.din) ? (bf16)((g.X[(long long)m * g.din + k] - g.xmu[k]) / g.xsd[k])
-                                              : (bf16)0.0f;
-  }
-  __syncthreads();
-  const bf16* Wm = g.wt + mem * g.sW;
+// Element offset of weight (k, n) in a layer's fragment copy: features in tiles of 32, k in steps of 16;
+// lane l of a fragment holds feature l % 32 and the 8 consecutive k from 8 (l / 32).
+__host__ __device__ inline long long frag_index(int k, int n, int Kd) {
+  const int lane = (n & 31) + 32 * ((k >> 3) & 1);
+  return (((long long)(n >> 5) * (Kd >> 4) + (k >> 4)) * 64 + lane) * 8 + (k & 7);
+}
+
+// z / (1 + e^-z), the quotient rounded as by a division: the residual of a first quotient, exact by a
+// fused multiply-add, corrects it.  A non-finite z, or one so negative that e^-z overflows, gives NaN
+// here: the caller redoes those by silu().
+__device__ __forceinline__ float silu_fast(float z) {
+  const float d = 1.0f + __builtin_amdgcn_exp2f(z * -1.442695041f);
+  const float r = __builtin_amdgcn_rcpf(d), q = z * r;
+  return fmaf(fmaf(-d, q, z), r, q);
+}
+
+template <int RT, int NW>
+__global__ __launch_bounds__(64 * NW, RT == 1 ? 2 : 4) void k_mlp_forward(MlpArgs g) {
+  constexpr int NT = 64 * NW, ROWS = 32 * RT, FT = (FW / 32) / NW;   // FT feature tiles per wave at most
+  __shared__ __attribute__((aligned(16))) bf16 act[ROWS * FLD];
+  const int mem = blockIdx.y, m0 = blockIdx.x * ROWS;
+  const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = t & 63;
+  const int lr = l & 31, lk = 8 * (l >> 5), lf = 4 * (l >> 5);
+  const bf16* Wm = g.wf + mem * g.sW;
   const float* Pm = g.p + mem * g.sP;
-  const int ka = 8 * (l >> 5), ra = l & 31;
-  for (int L = 0; L < g.L; ++L) {
-    const int K = g.dp[L], N = g.dp[L + 1];
-    const int nc = 64 * w;
-    const bool on = nc < N;
-    v16f acc[2][2];
+  // RT = 1: a layer's whole operand of this wave, requested while the layer before is being activated
+  constexpr int KM = RT == 1 ? FW / 16 : 1;
+  v8bf pre[FT][KM];
+  auto request_layer = [&](int L) {
+    const int KS = g.dp[L] >> 4, NF = L + 1 < g.L ? g.dp[L + 1] >> 5 : (g.dout + 31) >> 5;
+    const bf16* W0 = Wm + g.woff[L] + ((long long)w * KS * 64 + l) * 8;
 #pragma unroll
-    for (int q = 0; q < 2; ++q)
+    for (int k = 0; k < KM; ++k)
 #pragma unroll
-      for (int c = 0; c < 2; ++c)
+      for (int f = 0; f < FT; ++f)
+        if (k < KS && w + NW * f < NF) pre[f][k] = *(const v8bf*)(W0 + ((long long)NW * f * KS + k) * 512);
+  };
+  if constexpr (RT == 1) request_layer(0);
+  // normalised inputs: a lane keeps its column's statistics and has RB rows' loads on the way at once (row
+  // by row, this took 77 000 of a block's 200 000 cycles)
+  constexpr int WROWS = ROWS / NW, RB = WROWS < 16 ? WROWS : 16;
+  for (int k = l; k < g.dp[0]; k += 64) {
+    const int kc = min(k, g.din - 1);
+    const float mu = g.xmu[kc], sd = g.xsd[kc];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[q][c][r] = 0.0f;
-    if (on) {
-      const bf16* WT0 = Wm + g.woff[L] + (long long)(nc + ra) * K + ka;
-      const bf16* WT1 = WT0 + 32LL * K;
-#pragma unroll 2
-      for (int k0 = 0; k0 < K; k0 += 16) {
-        const v8bf b0 = *(const v8bf*)(WT0 + k0);
-        const v8bf b1 = *(const v8bf*)(WT1 + k0);
-        const v8bf a0 = *(const v8bf*)&act[ra * FLD + k0 + ka];
-        const v8bf a1 = *(const v8bf*)&act[(32 + ra) * FLD + k0 + ka];
-        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b0, acc[0][0], 0, 0, 0);
-        acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b1, acc[0][1], 0, 0, 0);
-        acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b0, acc[1][0], 0, 0, 0);
-        acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b1, acc[1][1], 0, 0, 0);
+    for (int r0 = 0; r0 < WROWS; r0 += RB) {
+      float x[RB];
+#pragma unroll
+      for (int r = 0; r < RB; ++r) x[r] = g.X[(long long)min(m0 + w * WROWS + r0 + r, g.B - 1) * g.din + kc];
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        const int row = w * WROWS + r0 + r;
+        act[row * FLD + k] = (m0 + row < g.B && k < g.din) ? (bf16)((x[r] - mu) / sd) : (bf16)0.0f;
       }
     }
-    __syncthreads();                             // every wave has read this layer's input
-    if (on) {
-      const bool last = L == g.L - 1;
+  }
+  __syncthreads();
+  const bf16* arow = act + lr * FLD + lk;
+  for (int L = 0; L < g.L - 1; ++L) {
+    const int KS = g.dp[L] >> 4, NF = g.dp[L + 1] >> 5;
+    v16f acc[FT][RT];
 #pragma unroll
-      for (int q = 0; q < 2; ++q)
+    for (int f = 0; f < FT; ++f)
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const int col = nc + 32 * c + (l & 31);
-          const float bias = Pm[g.boff[L] + col];
+      for (int c = 0; c < RT; ++c)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int row = 32 * q + (r >> 2) * 8 + (l >> 5) * 4 + (r & 3);
-            const float z = acc[q][c][r] + bias;
-            if (!last) act[row * FLD + col] = (bf16)silu(z);
-            else g.out[mem * g.sOut + (long long)(m0 + row) * g.ldo + col] = z;
+        for (int r = 0; r < 16; ++r) acc[f][c][r] = 0.0f;
+    // feature tiles w, w + NW, ...; a layer narrower than the block leaves its last waves idle
+    const bf16* W0 = Wm + g.woff[L] + ((long long)w * KS * 64 + l) * 8;
+    const long long wstep = (long long)NW * KS * 512;
+    if (w < NF) {
+      if constexpr (RT == 1) {
+#pragma unroll
+        for (int k = 0; k < KM; ++k)
+          if (k < KS) {
+            const v8bf b = *(const v8bf*)(arow + 16 * k);
+#pragma unroll
+            for (int f = 0; f < FT; ++f)
+              if (w + NW * f < NF) acc[f][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pre[f][k], b, acc[f][0], 0, 0, 0);
+          }
+      } else {
+        // the operands of four steps ahead: 32 products (1024 cycles) cover their way from the L2
+        const bool two = FT > 1 && w + NW < NF;     // uniform: the wave has all its tiles, or the first alone
+        v8bf a[2][4][FT];
+        auto request = [&](v8bf (&to)[4][FT], int k) {
+#pragma unroll
+          for (int h = 0; h < 4; ++h)
+#pragma unroll
+            for (int f = 0; f < FT; ++f)
+              if (f == 0 || two) to[h][f] = *(const v8bf*)(W0 + f * wstep + (k + h) * 512);
+        };
+        auto steps = [&](const v8bf (&from)[4][FT], int k) {
+#pragma unroll
+          for (int h = 0; h < 4; ++h) {
+            v8bf b[RT];
+#pragma unroll
+            for (int c = 0; c < RT; ++c) b[c] = *(const v8bf*)(arow + c * 32 * FLD + 16 * (k + h));
+#pragma unroll
+            for (int f = 0; f < FT; ++f)
+              if (f == 0 || two)
+#pragma unroll
+                for (int c = 0; c < RT; ++c)
+                  acc[f][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(from[h][f], b[c], acc[f][c], 0, 0, 0);
+          }
+        };
+        request(a[0], 0);                           // KS is a multiple of 4 (padded widths are of 64)
+        for (int k = 0; k < KS; k += 8) {
+          if (k + 4 < KS) request(a[1], k + 4);
+          steps(a[0], k);
+          if (k + 4 < KS) {
+            if (k + 8 < KS) request(a[0], k + 8);
+            steps(a[1], k + 4);
           }
         }
+      }
     }
+    if constexpr (RT == 1) request_layer(L + 1);
+    __syncthreads();                             // every wave has read this layer's input
+    auto activate = [&](auto&& fn) {             // features 32 ft + 8 q + lf + 0..3 of row 32 c + lr
+#pragma unroll
+      for (int f = 0; f < FT; ++f) {
+        const int ft = w + NW * f;
+        if (ft >= NF) break;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int n = 32 * ft + 8 * q + lf;
+          const float4 bias = *(const float4*)(Pm + g.boff[L] + n);
+#pragma unroll
+          for (int c = 0; c < RT; ++c) {
+            typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
+            const v4bf o = {(bf16)fn(acc[f][c][4 * q] + bias.x), (bf16)fn(acc[f][c][4 * q + 1] + bias.y),
+                            (bf16)fn(acc[f][c][4 * q + 2] + bias.z), (bf16)fn(acc[f][c][4 * q + 3] + bias.w)};
+            *(v4bf*)(act + (32 * c + lr) * FLD + n) = o;
+          }
+        }
+      }
+    };
+    float bad = 0.0f;                            // NaN once any result is
+    activate([&](float z) { const float y = silu_fast(z); bad = fmaf(y, 0.0f, bad); return y; });
+    if (__any(!(bad == 0.0f))) activate([](float z) { return silu(z); });
     __syncthreads();
+  }
+  // the linear output: only the tiles that hold real outputs, shared out by row tiles
+  const int KS = g.dp[g.L - 1] >> 4, NF = (g.dout + 31) >> 5;
+  for (int it = w; it < NF * RT; it += NW) {
+    const int ft = it / RT, c = it % RT;
+    const bf16* W0 = Wm + g.woff[g.L - 1] + ((long long)ft * KS * 64 + l) * 8;
+    v16f acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+    if constexpr (RT == 1) {                     // tile `it` is this wave's: NF <= NW
+#pragma unroll
+      for (int k = 0; k < KM; ++k)
+        if (k < KS) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pre[0][k], *(const v8bf*)(arow + 16 * k), acc, 0, 0, 0);
+    } else {
+#pragma unroll 4
+      for (int k = 0; k < KS; ++k)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const v8bf*)(W0 + k * 512), *(const v8bf*)(arow + c * 32 * FLD + 16 * k), acc, 0, 0, 0);
+    }
+    const int m = m0 + 32 * c + lr;
+    if (m < g.B) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int n = 32 * ft + 8 * q + lf;
+        if (n < g.dout) {
+          const float4 bias = *(const float4*)(Pm + g.boff[g.L - 1] + n);
+          *(float4*)(g.out + mem * g.sOut + (long long)m * g.ldo + n) =
+              make_float4(acc[4 * q] + bias.x, acc[4 * q + 1] + bias.y, acc[4 * q + 2] + bias.z, acc[4 * q + 3] + bias.w);
+        }
+      }
+    }
   }
 }
 
-// transposed BF16 copy of one layer's weights for every member: WT[n][k] = W[k][n]
-__global__ void k_transpose_w(const bf16* pb, bf16* pbt, long long P, long long off, int Kd, int Nd) {
-  const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const int mem = blockIdx.y;
-  if (e >= (long long)Kd * Nd) return;
-  const int n = (int)(e / Kd), k = (int)(e % Kd);
-  pbt[mem * P + off + e] = pb[mem * P + off + (long long)k * Nd + n];
+// the fragment copy of one layer's BF16 weights for every member; one thread per 8 consecutive k
+__global__ void k_frag_w(const bf16* pb, bf16* pbf, long long P, long long off, int Kd, int Nd) {
+  const int e = blockIdx.x * blockDim.x + threadIdx.x, mem = blockIdx.y;
+  if (e >= (Kd >> 3) * Nd) return;
+  const int n = e % Nd, k = 8 * (e / Nd);
+  v8bf v;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) v[q] = pb[mem * P + off + (long long)(k + q) * Nd + n];
+  *(v8bf*)(pbf + mem * P + off + frag_index(k, n, Kd)) = v;
 }
 
 // raw inputs (B x din, FP32) -> normalised BF16 rows of width dp0, zero padding
