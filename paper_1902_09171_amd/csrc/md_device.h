@@ -746,10 +746,11 @@ __device__ __forceinline__ void add_virial(double w[6], double gr, const double 
   w[3] = fma(t0, dd[1], w[3]); w[4] = fma(t0, dd[2], w[4]); w[5] = fma(t1, dd[2], w[5]);
 }
 
-// an empty list, by the kernel that runs before the reduction that fills it
-__device__ __forceinline__ void work_clear(const MDArgs& a) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) *a.work_pack = 0;
+// an empty list, by the kernel that runs before the one that fills it
+__device__ __forceinline__ void work_clear(unsigned long long* pack) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *pack = 0;
 }
+__device__ __forceinline__ void work_clear(const MDArgs& a) { work_clear(a.work_pack); }
 // ------------------------------------------------------------------ force kernels
 // List entries of one trip: UNR consecutive entries of one list block, as 32-bit words loaded with
 // one vector load (the trip's first entry is a multiple of UNR, so they are aligned).
@@ -1535,27 +1536,35 @@ __device__ __forceinline__ int wave_run_add(int* ctr, int key, bool valid) {
   return __shfl(old, head) + (lane - head);
 }
 
+// an atom wrapped into the box (x updated), its fixed-point coordinates and packed bin; returns the bin
 template <class P>
-__device__ __forceinline__ int bin_one(const MDArgs& a, const CellDev& C, long long i) {
-  double x = a.x[i], y = a.y[i], z = a.z[i];
-  const double s0 = C.Hi[0] * x + C.Hi[1] * y + C.Hi[2] * z, s1 = C.Hi[4] * y + C.Hi[5] * z, s2 = C.Hi[8] * z;
+__device__ __forceinline__ int place_atom(const CellDev& C, double x[3], typename P::S& sv, int& packed) {
+  const double s0 = C.Hi[0] * x[0] + C.Hi[1] * x[1] + C.Hi[2] * x[2], s1 = C.Hi[4] * x[1] + C.Hi[5] * x[2], s2 = C.Hi[8] * x[2];
   const double k0 = floor(s0), k1 = floor(s1), k2 = floor(s2);
   if (k0 != 0.0 || k1 != 0.0 || k2 != 0.0) {       // x -= H k (a lattice vector), H upper triangular
-    x -= C.H[0] * k0 + C.H[1] * k1 + C.H[2] * k2;
-    y -= C.H[4] * k1 + C.H[5] * k2;
-    z -= C.H[8] * k2;
-    a.x[i] = x; a.y[i] = y; a.z[i] = z;
+    x[0] -= C.H[0] * k0 + C.H[1] * k1 + C.H[2] * k2;
+    x[1] -= C.H[4] * k1 + C.H[5] * k2;
+    x[2] -= C.H[8] * k2;
   }
   double f[3];
-  scaled_frac(C, x, y, z, f);
-  const typename P::S sv = P::make(f[0], f[1], f[2]);
-  P::store_xyz(a.s_cur, i, sv);
-  a.sb[i] = P::quant(sv);
+  scaled_frac(C, x[0], x[1], x[2], f);
+  sv = P::make(f[0], f[1], f[2]);
   int b[3];
 #pragma unroll
   for (int q = 0; q < 3; ++q) b[q] = min((int)(f[q] * C.nb[q]), C.nb[q] - 1);
-  const int bin = (b[0] * C.nb[1] + b[1]) * C.nb[2] + b[2];
-  a.abin[i] = b[0] | (b[1] << BIN_BITS) | (b[2] << (2 * BIN_BITS));   // packed bin coordinates
+  packed = b[0] | (b[1] << BIN_BITS) | (b[2] << (2 * BIN_BITS));
+  return (b[0] * C.nb[1] + b[1]) * C.nb[2] + b[2];
+}
+template <class P>
+__device__ __forceinline__ int bin_one(const MDArgs& a, const CellDev& C, long long i) {
+  double x[3] = {a.x[i], a.y[i], a.z[i]};
+  typename P::S sv;
+  int packed;
+  const int bin = place_atom<P>(C, x, sv, packed);
+  a.x[i] = x[0]; a.y[i] = x[1]; a.z[i] = x[2];
+  P::store_xyz(a.s_cur, i, sv);
+  a.sb[i] = P::quant(sv);
+  a.abin[i] = packed;
   return bin;
 }
 
@@ -1654,17 +1663,20 @@ __device__ __forceinline__ void list_band(const MDArgs& a, CellDev& C) {
   C.list_hi2 = (float)(a.rcs2 + band);
 }
 
+// the cell's fields for a list about to be built, which will hold every pair within rc + skin
+__device__ __forceinline__ void begin_build(const MDArgs& a, CellDev& C) {
+  const int up[6] = {0, 1, 2, 4, 5, 8};
+  for (int q = 0; q < 6; ++q) C.Hb[q] = C.H[up[q]];
+  C.hs2 = measured_threshold(a.half_skin2, C.qeps);
+  C.dmax2 = 0.f;
+  list_band(a, C);
+}
+
 // exclusive scan of one cell's histogram by a block of SCAN_NT threads (sh: at least 16 ints of LDS)
 __device__ __forceinline__ void scan_cell(const MDArgs& a, CellDev& C, int* sh) {
   const int nbins = C.nb[0] * C.nb[1] * C.nb[2];
   const int t = threadIdx.x;
-  if (t == 0) {                    // the list about to be built holds every pair within rc + skin
-    const int up[6] = {0, 1, 2, 4, 5, 8};
-    for (int q = 0; q < 6; ++q) C.Hb[q] = C.H[up[q]];
-    C.hs2 = measured_threshold(a.half_skin2, C.qeps);
-    C.dmax2 = 0.f;
-    list_band(a, C);
-  }
+  if (t == 0) begin_build(a, C);
   int carry = 0;
   for (int base = 0; base < nbins; base += SCAN_NT) {   // coalesced chunks of SCAN_NT bins
     const int b = base + t;
@@ -1779,18 +1791,19 @@ __device__ __forceinline__ void reorder_gather_atom(const MDArgs& a, const CellD
 // sort of the whole bin in a launch of its own: 12.6 us per MD step for 100 cells of 10^4 beads at ~5
 // atoms per bin, 48 us for 50 glassy cells at ~19, against nothing and +1 us of this kernel.
 template <class P>
+__device__ __forceinline__ void rank_gather_atom(const MDArgs& a, const CellDev& C, long long q) {
+  const long long src = C.off + a.binned[q];
+  const int v = a.bkey[q];
+  const int bin = C.bin_off + bin_index(C, a.abin[src]);
+  const int beg = a.bstart[bin], m = a.bnum[bin];
+  const int* key = a.bkey + C.off + beg;
+  int rank = 0;
+  for (int e = 0; e < m; ++e) rank += key[e] < v;
+  reorder_gather_atom<P>(a, C, src, (long long)C.off + beg + rank);
+}
+template <class P>
 __global__ __launch_bounds__(TILE * WORK_WAVES) void k_reorder_gather(MDArgs a) {
-  for_work_tiles(a, [&](const Tile& t, long long q) {
-    const CellDev& C = a.cells[t.cell];
-    const long long src = C.off + a.binned[q];
-    const int v = a.bkey[q];
-    const int bin = C.bin_off + bin_index(C, a.abin[src]);
-    const int beg = a.bstart[bin], m = a.bnum[bin];
-    const int* key = a.bkey + C.off + beg;
-    int rank = 0;
-    for (int e = 0; e < m; ++e) rank += key[e] < v;
-    reorder_gather_atom<P>(a, C, src, (long long)C.off + beg + rank);
-  });
+  for_work_tiles(a, [&](const Tile& t, long long q) { rank_gather_atom<P>(a, a.cells[t.cell], q); });
 }
 
 template <class P>
@@ -1811,14 +1824,95 @@ __device__ __forceinline__ void reorder_scatter_atom(const MDArgs& a, const Cell
 }
 
 
-// The six preparation phases of a rebuild (bin, scan, fill, sort, reorder gather and scatter) for
-// cells of at most PREP_ATOMS atoms: one block per cell runs them in turn, separated by block
-// barriers, so a step in which no cell rebuilds costs one launch instead of six.  Same results as
-// the phase kernels: the bins are ordered by original index (keys staged in LDS, each bin
-// rank-sorted by one thread; keys are distinct), so the reorder depends only on positions.
-constexpr int PREP_ATOMS = 4096;
+// The preparation phases of a rebuild for cells of at most PREP_ATOMS atoms: one block per cell, so a step
+// in which no cell rebuilds costs one launch instead of five.  Same results as the phase kernels: the
+// order is by (bin, original index), so it depends only on positions.
+//
+// A block keeps a cell to itself: its histogram, sort keys and new places are in LDS and every thread holds
+// its (up to four) atoms in registers from the one read of their rows to the one write, straight to
+// their new places once every thread has read.  What bounds it is the round trip of those rows through one CU.
+// Through global memory (prep_cell_many_bins) the reduction with a rebuilt cell of 4000 beads took ~62 us,
+// 22.1 us averaged over the steps of four such cells; so ~22 and 10.1 us.  First build of 256 copper cells
+// of 4000 atoms: 670 / 37 us.
+constexpr int PREP_ATOMS = 4096, PREP_BINS = 4096, PREP_SLOTS = PREP_ATOMS / SCAN_NT;
+struct PrepShared {
+  int scan[SCAN_NT / 64];
+  int start[PREP_BINS + 1];        // counts, then first places
+  int key[PREP_ATOMS];             // original indices by bin, unordered inside a bin
+  unsigned short pos[PREP_ATOMS];  // new place by original index
+};
 template <class P>
-__device__ __forceinline__ void prep_cell(const MDArgs& a, int cell, int* sh, int* key) {
+__device__ __forceinline__ void prep_cell(const MDArgs& a, int cell, PrepShared& sh) {
+  CellDev& C = a.cells[cell];
+  const int n = C.n, t = threadIdx.x, off = C.off, boff = C.bin_off;
+  const int nbins = C.nb[0] * C.nb[1] * C.nb[2];
+  for (int b = t; b < nbins; b += SCAN_NT) sh.start[b] = 0;
+  if (t == 0) begin_build(a, C);
+  double x[PREP_SLOTS][3], v[PREP_SLOTS][3];
+  int gid[PREP_SLOTS], bin[PREP_SLOTS], slot[PREP_SLOTS], pk[PREP_SLOTS];
+#pragma unroll
+  for (int e = 0; e < PREP_SLOTS; ++e) {
+    const long long i = off + min(t + e * SCAN_NT, n - 1);
+    x[e][0] = a.x[i]; x[e][1] = a.y[i]; x[e][2] = a.z[i];
+    v[e][0] = a.vx[i]; v[e][1] = a.vy[i]; v[e][2] = a.vz[i];
+    gid[e] = a.gid[i];
+  }
+  __syncthreads();
+  typename P::S s[PREP_SLOTS];
+#pragma unroll
+  for (int e = 0; e < PREP_SLOTS; ++e) {
+    bin[e] = place_atom<P>(C, x[e], s[e], pk[e]);
+    slot[e] = t + e * SCAN_NT < n ? atomicAdd(&sh.start[bin[e]], 1) : 0;
+  }
+  __syncthreads();
+  // exclusive scan of the counts, consecutive bins per thread
+  const int per = (nbins + SCAN_NT - 1) / SCAN_NT, b0 = min(t * per, nbins), b1 = min(b0 + per, nbins);
+  int mine = 0, tot;
+  for (int b = b0; b < b1; ++b) mine += sh.start[b];
+  int at = block_exscan(mine, sh.scan, &tot);
+  for (int b = b0; b < b1; ++b) {
+    const int c = sh.start[b];
+    sh.start[b] = at;
+    a.bstart[boff + b] = at;
+    a.bnum[boff + b] = c;
+    at += c;
+  }
+  if (t == 0) sh.start[nbins] = n;
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < PREP_SLOTS; ++e)
+    if (t + e * SCAN_NT < n) sh.key[sh.start[bin[e]] + slot[e]] = gid[e];
+  __syncthreads();
+  int dest[PREP_SLOTS];
+#pragma unroll
+  for (int e = 0; e < PREP_SLOTS; ++e) {
+    const int beg = sh.start[bin[e]], end = sh.start[bin[e] + 1];
+    int rank = 0;
+    for (int q = beg; q < end; ++q) rank += sh.key[q] < gid[e];
+    dest[e] = beg + rank;
+    if (t + e * SCAN_NT < n) sh.pos[gid[e]] = (unsigned short)dest[e];
+  }
+  __syncthreads();                 // every row has been read, every place is known
+#pragma unroll
+  for (int e = 0; e < PREP_SLOTS; ++e) {
+    if (t + e * SCAN_NT >= n) continue;
+    const long long q = off + dest[e];
+    a.x[q] = x[e][0]; a.y[q] = x[e][1]; a.z[q] = x[e][2];
+    a.vx[q] = v[e][0]; a.vy[q] = v[e][1]; a.vz[q] = v[e][2];
+    P::store_xyz(a.s_cur, q, s[e]);
+    a.sb[q] = P::quant(s[e]);
+    a.abin[q] = pk[e];
+    a.gid[q] = gid[e];
+    a.pos_of[off + gid[e]] = dest[e];
+    const int4 p = a.bond0[off + gid[e]];
+    store_bonds(a, q, p.x < 0 ? dest[e] : sh.pos[p.x], p.y < 0 ? dest[e] : sh.pos[p.y],
+                p.z < 0 ? dest[e] : sh.pos[p.z], p.w < 0 ? dest[e] : sh.pos[p.w]);
+  }
+}
+
+// The same through global memory, for a cell with more bins than fit in LDS.
+template <class P>
+__device__ __forceinline__ void prep_cell_many_bins(const MDArgs& a, int cell, PrepShared& sh) {
   CellDev& C = a.cells[cell];
   const int n = C.n, t = threadIdx.x;
   for (int l0 = 0; l0 < n; l0 += SCAN_NT) {     // whole waves: the bin counts aggregate over lanes
@@ -1826,36 +1920,29 @@ __device__ __forceinline__ void prep_cell(const MDArgs& a, int cell, int* sh, in
     bin_atom<P>(a, C, (long long)C.off + (v ? l0 + t : 0), v);
   }
   __syncthreads();
-  scan_cell(a, C, sh);                       // ends with a barrier
+  scan_cell(a, C, sh.scan);                  // ends with a barrier
   for (int l0 = 0; l0 < n; l0 += SCAN_NT) {
     const bool v = l0 + t < n;
     fill_atom(a, C, (long long)C.off + (v ? l0 + t : 0), v);
   }
   __syncthreads();
-  for (int q = t; q < n; q += SCAN_NT) key[q] = a.bkey[C.off + q];
-  __syncthreads();
-  const int nbins = C.nb[0] * C.nb[1] * C.nb[2];
-  for (int b = t; b < nbins; b += SCAN_NT) {
-    const int p0 = a.bstart[C.bin_off + b], m = a.bnum[C.bin_off + b];
-    for (int e = 0; e < m; ++e) {
-      const int v = key[p0 + e];
-      int rank = 0;
-      for (int q = 0; q < m; ++q) rank += key[p0 + q] < v;
-      a.binned[C.off + p0 + rank] = a.pos_of[C.off + v];
-    }
-  }
-  __syncthreads();
-  for (int q = t; q < n; q += SCAN_NT) reorder_gather_atom<P>(a, C, (long long)C.off + a.binned[C.off + q], (long long)C.off + q);
+  for (int q = t; q < n; q += SCAN_NT) rank_gather_atom<P>(a, C, (long long)C.off + q);
   __syncthreads();
   for (int q = t; q < n; q += SCAN_NT) reorder_scatter_atom<P>(a, C, (long long)C.off + q);
+}
+template <class P>
+__device__ __forceinline__ void prep_any(const MDArgs& a, int cell, PrepShared& sh) {
+  const CellDev& C = a.cells[cell];
+  if (C.nb[0] * C.nb[1] * C.nb[2] <= PREP_BINS) prep_cell<P>(a, cell, sh);
+  else prep_cell_many_bins<P>(a, cell, sh);
 }
 
 template <class P>
 __global__ __launch_bounds__(SCAN_NT) void k_cell_prep(MDArgs a) {
-  __shared__ int sh[SCAN_NT];
-  __shared__ int key[PREP_ATOMS];
+  __shared__ PrepShared sh;
   if (!a.cells[blockIdx.x].rebuild) return;
-  prep_cell<P>(a, blockIdx.x, sh, key);
+  if (threadIdx.x == 0) work_add(a, blockIdx.x, a.cells[blockIdx.x].ntile);
+  prep_any<P>(a, blockIdx.x, sh);
 }
 
 // The per-cell reduction of a time step followed, in the same block, by the rebuild preparation
@@ -1864,12 +1951,11 @@ __global__ __launch_bounds__(SCAN_NT) void k_cell_prep(MDArgs a) {
 template <class P>
 __global__ __launch_bounds__(SCAN_NT) void k_reduce_prep(MDArgs a, int mode) {
   __shared__ RedShared rsh;
-  __shared__ int sh[SCAN_NT];
-  __shared__ int key[PREP_ATOMS];
+  __shared__ PrepShared sh;
   reduce_cell(a, blockIdx.x, mode, rsh, 1);
   __syncthreads();
   if (!__hip_atomic_load(&a.cells[blockIdx.x].rebuild, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
-  prep_cell<P>(a, blockIdx.x, sh, key);
+  prep_any<P>(a, blockIdx.x, sh);
 }
 
 // Original order for the atoms of cells [first, first + count) (create, set_state): gid and
@@ -2336,6 +2422,7 @@ __global__ void k_qr_commit(CellDev* cells, const Stage* st, int ncells, double 
 // to rounding: the remap leaves S = H^-1 x unchanged)
 template <class P>
 __global__ __launch_bounds__(TILE) void k_remap(MDArgs a, const Stage* st) {
+  work_clear(a);
   const int tb = block_tile(a.ntiles, blockIdx.x);
   if (tb >= a.ntiles) return;
   const Tile t = a.tiles[tb];
@@ -2349,7 +2436,8 @@ __global__ __launch_bounds__(TILE) void k_remap(MDArgs a, const Stage* st) {
 }
 
 // set a cell's box from H (create / set_state) and request a rebuild + prime
-__global__ void k_set_box(CellDev* cells, int first, int count, double bw) {
+__global__ void k_set_box(CellDev* cells, int first, int count, double bw, unsigned long long* pack) {
+  work_clear(pack);
   const int c = first + blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= first + count) return;
   CellDev& C = cells[c];
@@ -2463,7 +2551,8 @@ __global__ void k_set_bin_width(CellDev* cells, int ncells, double bw) {
   if (c < ncells) set_box_fields(cells[c], bw);
 }
 
-__global__ void k_set_pending(CellDev* cells, int first, int count) {
+__global__ void k_set_pending(CellDev* cells, int first, int count, unsigned long long* pack) {
+  work_clear(pack);
   const int c = first + blockIdx.x * blockDim.x + threadIdx.x;
   if (c < first + count) { cells[c].rebuild = 1; cells[c].pending = 1; cells[c].prune = 1; }
 }

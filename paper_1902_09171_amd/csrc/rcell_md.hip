@@ -349,12 +349,13 @@ unsigned round8(int blocks) { return (unsigned)((std::max(1, blocks) + 7) / 8 * 
 
 // reduce_mode >= 0: the per-cell reduction of that mode runs first, fused into the preparation
 // launch when the cells are small enough for it, and enters the cells that it flags into the work list
-// (emptied by the force pass, k_start or k_fire_move before it); otherwise k_rebuild_work makes the list
+// (emptied by the force pass, k_start or k_fire_move before it).  Otherwise the preparation of small
+// cells enters those already flagged (the list emptied by k_remap, k_set_box or k_set_pending), and
+// before the phase kernels k_rebuild_work makes the list.
 void launch_build(rcell_ctx* c, int reduce_mode = -1) {
   TraceRange tr("rcell: reduce + neighbour rebuild");
   const MDArgs a = make_args(c);
   const dim3 gc(c->ncells), bc(SCAN_NT);
-  if (reduce_mode < 0) hipLaunchKernelGGL(k_rebuild_work, dim3(1), dim3(SCAN_NT), 0, c->stream, a);
   if (c->cell_prep) {              // small cells: the preparation phases in one launch
     if (reduce_mode >= 0) {
       if (c->fp64) hipLaunchKernelGGL(k_reduce_prep<FP64>, gc, bc, 0, c->stream, a, reduce_mode);
@@ -366,6 +367,7 @@ void launch_build(rcell_ctx* c, int reduce_mode = -1) {
   } else {
     // the phases walk the work list of the cells that rebuild: small grids, block-strided
     if (reduce_mode >= 0) launch_reduce(c, reduce_mode, 1);
+    else hipLaunchKernelGGL(k_rebuild_work, dim3(1), dim3(SCAN_NT), 0, c->stream, a);
     // grids of whole multiples of 8 blocks: the loops share the work out per XCD (XcdLoop)
     const dim3 gw(round8(std::min(WORK_BLOCKS, (c->ntiles + WORK_WAVES - 1) / WORK_WAVES))), bw(TILE * WORK_WAVES);
     const dim3 gs(round8(std::min(c->ncells, WORK_BLOCKS / 8)));
@@ -808,7 +810,7 @@ int rcell_create(const rcell_params* params, const rcell_cell_init* cells, int32
     hipLaunchKernelGGL(k_mb_velocities, dim3(ncells), dim3(MB_NT), 0, c->stream, make_args(c), (const int*)dflag, sd,
                        p.kB * p.temperature / (p.mass * p.mvv2e));
   }
-  hipLaunchKernelGGL(k_set_box, dim3((ncells + 63) / 64), dim3(64), 0, c->stream, c->cells, 0, ncells, bin_width(c));
+  hipLaunchKernelGGL(k_set_box, dim3((ncells + 63) / 64), dim3(64), 0, c->stream, c->cells, 0, ncells, bin_width(c), c->work_pack);
   if ((e = prime(c))) return bail(e);
   Gathered g;
   if ((e = gather(c, g))) return bail(e);
@@ -964,7 +966,7 @@ int rcell_minimize(rcell_ctx* c, int32_t max_iter, double ftol, int32_t* iters) 
   }
   // relaxed state: zero velocities, conservative forces and the relaxed stress as the last sample
   hipLaunchKernelGGL(k_zero_v, dim3(tile_grid(c->ntiles)), dim3(TILE), 0, c->stream, a0);
-  hipLaunchKernelGGL(k_set_pending, dim3((nc + 63) / 64), dim3(64), 0, c->stream, c->cells, 0, nc);
+  hipLaunchKernelGGL(k_set_pending, dim3((nc + 63) / 64), dim3(64), 0, c->stream, c->cells, 0, nc, c->work_pack);
   int e = prime(c);
   if (e) return e;
   hipLaunchKernelGGL(k_fire_iters, dim3((nc + 63) / 64), dim3(64), 0, c->stream, c->cells, nc, d_it, d_done);
@@ -1061,7 +1063,7 @@ int rcell_set_state(rcell_ctx* c, int32_t cell, const double* x, const double* v
   HIPCHK(c, hipMemcpyAsync(c->cells + cell, &C, sizeof(CellDev), hipMemcpyHostToDevice, c->stream));
   // the state arrives in original order: identity order, then the rebuild reorders the cell
   hipLaunchKernelGGL(k_reset_order, dim3(tile_grid(c->ntiles)), dim3(TILE), 0, c->stream, make_args(c), cell, 1);
-  hipLaunchKernelGGL(k_set_box, dim3(1), dim3(64), 0, c->stream, c->cells, cell, 1, bin_width(c));
+  hipLaunchKernelGGL(k_set_box, dim3(1), dim3(64), 0, c->stream, c->cells, cell, 1, bin_width(c), c->work_pack);
   if ((e = prime(c))) return e;
   HIPCHK(c, hipStreamSynchronize(c->stream));
   return RCELL_OK;
@@ -1261,7 +1263,7 @@ int rcell_autotune(rcell_ctx* c, int32_t use_cache, int32_t* lanes, int32_t* bin
       if ((he = copy(false)) != hipSuccess) break;
       // the restored cell table holds the bin offsets of the snapshot: the current layout again
       if ((e = push_bin_layout(c)) || (e = apply_bin_factor(c, f))) break;
-      hipLaunchKernelGGL(k_set_pending, dim3((c->ncells + 63) / 64), dim3(64), 0, c->stream, c->cells, 0, c->ncells);
+      hipLaunchKernelGGL(k_set_pending, dim3((c->ncells + 63) / 64), dim3(64), 0, c->stream, c->cells, 0, c->ncells, c->work_pack);
       if ((he = hipEventRecord(t0, c->stream)) != hipSuccess) break;
       launch_build(c);
       if ((he = hipEventRecord(t1, c->stream)) != hipSuccess) break;
