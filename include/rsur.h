@@ -29,8 +29,8 @@ typedef struct rsur_ctx rsur_ctx;
 /* Allocate a K-member ensemble for batches of up to max_batch rows on the current device.
  * Parameters start at zero: load them with rsur_set_params.  Normalisation starts as identity.
  * All device memory is allocated here (parameters, Adam moments, activations for max_batch rows,
- * and the partial sums of the training step's split reductions: 8 x K x the largest layer's
- * weights, in FP32); the forward and training calls allocate nothing. */
+ * and the partial sums of the training step's split reductions: up to 8 x K x the member's
+ * parameters in FP32, at most 256 MiB); the forward and training calls allocate nothing. */
 int rsur_create(int32_t din, int32_t width, int32_t depth, int32_t dout, int32_t ensemble,
                 int32_t max_batch, void* hip_stream, rsur_ctx** out);
 int rsur_destroy(rsur_ctx* ctx);

@@ -73,15 +73,14 @@ struct rsur_ctx {
   float *p = nullptr, *g = nullptr, *m1 = nullptr, *m2 = nullptr;   // K x P
   bf16* pb = nullptr;                                               // K x P (weights used)
   bf16* pbf = nullptr;                                              // K x P, weights by fragments
-  bool pbf_stale = true;                                            // pbf behind pb
   std::vector<bf16*> act;                    // act[l]: K x Mp x dp[l] (act[0] shared: Mp x dp[0])
   std::vector<float*> Z;                     // Z[l]: K x Mp x dp[l + 1], hidden layers
   float* out = nullptr;                      // K x Mp x dp[L]
   bf16 *dza = nullptr, *dzb = nullptr;       // K x Mp x max(dp)
   float *xmu = nullptr, *xsd = nullptr, *ymu = nullptr, *ysd = nullptr, *loss = nullptr;
-  float *c1 = nullptr, *c2 = nullptr;        // Adam bias corrections per member
-  float* split = nullptr;                    // partial sums of the split gradient reductions
-  float* lpart = nullptr;                    // K x LOSS_CHUNKS partial losses
+  int max_split = 0;                         // most ranges of a split gradient reduction; 0: never split
+  float* split = nullptr;                    // max_split x K x P: their partial sums
+  float* lpart = nullptr;                    // K x Mp / LOSS_ROWS partial losses
   std::vector<long long> t;                  // Adam steps per member
   std::vector<void*> allocs;
 };
@@ -115,13 +114,21 @@ int ralloc(rsur_ctx* c, T** out, size_t count) {
 
 int pad64(int v) { return (v + 63) / 64 * 64; }
 
+// shapes that the fused inference kernel takes
+bool fused_shape(const rsur_ctx* c) {
+  return *std::max_element(c->dp.begin(), c->dp.end()) <= FW && c->L <= MAXL;
+}
+
 // The gradient reductions over the batch (weight gradients, bias column sums) are split into S
 // ranges of at least 256 rows (S a power of two up to MAX_SPLIT dividing Mp / 64) so that enough
 // blocks work at once; S partial results are then added in order (deterministic).
+// S is bounded by the memory of the partial results too: a network whose S copies would be larger than
+// SPLIT_FLOATS has blocks enough without (64 x 64 weights each).
 constexpr int MAX_SPLIT = 8;
-int batch_splits(int Mp) {
+constexpr long long SPLIT_FLOATS = 1LL << 26;
+int batch_splits(const rsur_ctx* c, int Mp) {
   int S = 1;
-  while (S < MAX_SPLIT && (Mp / 64) % (2 * S) == 0 && Mp / (2 * S) >= 256) S *= 2;
+  while (2 * S <= c->max_split && (Mp / 64) % (2 * S) == 0 && Mp / (2 * S) >= 256) S *= 2;
   return S;
 }
 
@@ -223,6 +230,9 @@ int rsur_create(int32_t din, int32_t width, int32_t depth, int32_t dout, int32_t
     c->own_stream = true;
   }
   const long long KP = (long long)c->K * c->P;
+  int ms = 1;
+  while (2 * ms <= MAX_SPLIT && c->Mp / (2 * ms) >= 256 && 2 * ms * KP <= SPLIT_FLOATS) ms *= 2;
+  c->max_split = ms > 1 ? ms : 0;
   int e;
   if ((e = ralloc(c, &c->p, KP)) || (e = ralloc(c, &c->g, KP)) || (e = ralloc(c, &c->m1, KP)) ||
       (e = ralloc(c, &c->m2, KP)) || (e = ralloc(c, &c->pb, KP)) || (e = ralloc(c, &c->pbf, KP)))
@@ -234,21 +244,16 @@ int rsur_create(int32_t din, int32_t width, int32_t depth, int32_t dout, int32_t
   for (int l = 0; l < c->L - 1; ++l)
     if ((e = ralloc(c, &c->Z[l], (size_t)c->K * c->Mp * c->dp[l + 1]))) return bail(e);
   const int dmax = *std::max_element(c->dp.begin(), c->dp.end());
-  {
-    size_t mn = (size_t)dmax;
-    for (int l = 0; l < c->L; ++l) mn = std::max(mn, (size_t)c->dp[l] * c->dp[l + 1]);
-    if ((e = ralloc(c, &c->split, (size_t)MAX_SPLIT * c->K * mn))) return bail(e);
-  }
+  if ((e = ralloc(c, &c->split, (size_t)c->max_split * KP))) return bail(e);
   if ((e = ralloc(c, &c->out, (size_t)c->K * c->Mp * c->dp[c->L])) ||
       (e = ralloc(c, &c->dza, (size_t)c->K * c->Mp * dmax)) || (e = ralloc(c, &c->dzb, (size_t)c->K * c->Mp * dmax)) ||
       (e = ralloc(c, &c->xmu, din)) || (e = ralloc(c, &c->xsd, din)) || (e = ralloc(c, &c->ymu, dout)) ||
-      (e = ralloc(c, &c->ysd, dout)) || (e = ralloc(c, &c->loss, ensemble)) || (e = ralloc(c, &c->c1, ensemble)) ||
-      (e = ralloc(c, &c->c2, ensemble)) || (e = ralloc(c, &c->lpart, (size_t)ensemble * LOSS_CHUNKS)))
+      (e = ralloc(c, &c->ysd, dout)) || (e = ralloc(c, &c->loss, ensemble)) || (e = ralloc(c, &c->lpart, (size_t)ensemble * (c->Mp / LOSS_ROWS))))
     return bail(e);
   std::vector<float> zeros(std::max(din, dout), 0.0f), ones(std::max(din, dout), 1.0f);
   if (hipMemsetAsync(c->p, 0, sizeof(float) * KP, c->stream) || hipMemsetAsync(c->g, 0, sizeof(float) * KP, c->stream) ||
       hipMemsetAsync(c->m1, 0, sizeof(float) * KP, c->stream) || hipMemsetAsync(c->m2, 0, sizeof(float) * KP, c->stream) ||
-      hipMemsetAsync(c->pb, 0, sizeof(bf16) * KP, c->stream) ||
+      hipMemsetAsync(c->pb, 0, sizeof(bf16) * KP, c->stream) || hipMemsetAsync(c->pbf, 0, sizeof(bf16) * KP, c->stream) ||
       hipMemcpyAsync(c->xmu, zeros.data(), sizeof(float) * din, hipMemcpyHostToDevice, c->stream) ||
       hipMemcpyAsync(c->xsd, ones.data(), sizeof(float) * din, hipMemcpyHostToDevice, c->stream) ||
       hipMemcpyAsync(c->ymu, zeros.data(), sizeof(float) * dout, hipMemcpyHostToDevice, c->stream) ||
@@ -291,9 +296,14 @@ int rsur_set_params(rsur_ctx* c, int32_t member, const float* w) {
   RCHK(c, hipMemsetAsync(c->m2 + off, 0, sizeof(float) * c->P, c->stream));
   hipLaunchKernelGGL(k_to_bf16, dim3((unsigned)((c->P + 255) / 256)), dim3(256), 0, c->stream, c->p + off,
                      c->pb + off, c->P);
+  if (fused_shape(c))
+    for (int l = 0; l < c->L; ++l) {
+      const int n = c->dp[l] / 8 * c->dp[l + 1];
+      hipLaunchKernelGGL(k_frag_w, dim3((n + 255) / 256), dim3(256), 0, c->stream, c->pb + off + c->woff[l],
+                         c->pbf + off + c->woff[l], c->dp[l], c->dp[l + 1]);
+    }
   RCHK(c, hipStreamSynchronize(c->stream));
   c->t[member] = 0;
-  c->pbf_stale = true;
   return RCELL_OK;
 }
 
@@ -343,20 +353,9 @@ int rsur_fit_norm(rsur_ctx* c, const void* X_dev, const void* Y_dev, int32_t n) 
 // sooner.  The two meet at ~4000 rows of 5 members (one call, us, 128 against 32 rows per block: 1024
 // rows 33.7 / 19.7, 2048 34.4 / 26.1, 4096 37.9 / 38.8, 8192 56 / 60, 16 384 85 / 109).
 constexpr int FUSED_MIN_BLOCKS = 160;
-static bool fused_shape(const rsur_ctx* c) {
-  return *std::max_element(c->dp.begin(), c->dp.end()) <= FW && c->L <= MAXL;
-}
 
 // the fused forward of every member for B rows into out (K x Mp x dp[L], member stride sOut)
 static void forward_fused(rsur_ctx* c, const float* X, int B, float* out, long long sOut) {
-  if (c->pbf_stale) {
-    for (int l = 0; l < c->L; ++l) {
-      const int n = c->dp[l] / 8 * c->dp[l + 1];
-      hipLaunchKernelGGL(k_frag_w, dim3((n + 255) / 256, c->K), dim3(256), 0, c->stream, c->pb, c->pbf, c->P, c->woff[l],
-                         c->dp[l], c->dp[l + 1]);
-    }
-    c->pbf_stale = false;
-  }
   MlpArgs g{};
   g.X = X; g.B = B; g.din = c->din; g.xmu = c->xmu; g.xsd = c->xsd;
   g.wf = c->pbf; g.sW = c->P; g.p = c->p; g.sP = c->P;
@@ -432,29 +431,24 @@ int rsur_train_step(rsur_ctx* c, const void* X_dev, const void* Y_dev, int32_t B
   const long long sOut = (long long)c->Mp * c->dp[L];
   const int dmax = *std::max_element(c->dp.begin(), c->dp.end());
   const long long sdz = (long long)c->Mp * dmax;
-  hipLaunchKernelGGL(k_loss, dim3(LOSS_CHUNKS, c->K), dim3(LOSS_NT), 0, c->stream, c->out, sOut, c->dp[L],
-                     (const float*)Y_dev, B, c->dout, c->ymu, c->ysd, c->dza, sdz, Mp, c->lpart);
-  hipLaunchKernelGGL(k_loss_total, dim3((c->K + 63) / 64), dim3(64), 0, c->stream, c->lpart, c->K, 1.0f / ((float)B * (float)c->dout),
-                     c->loss);
-  const int S = batch_splits(Mp);
+  hipLaunchKernelGGL(k_loss, dim3(Mp / LOSS_ROWS, c->K), dim3(LOSS_NT), 0, c->stream, c->out, sOut, c->dp[L],
+                     (const float*)Y_dev, B, c->dout, c->ymu, c->ysd, c->dza, sdz, c->lpart);
+  if (loss)                                          // read by this call alone
+    hipLaunchKernelGGL(k_loss_total, dim3(c->K), dim3(64), 0, c->stream, c->lpart, Mp / LOSS_ROWS,
+                       1.0f / ((float)B * (float)c->dout), c->loss);
+  const int S = batch_splits(c, Mp);
+  const long long n = (long long)c->K * c->P;
+  float* grads = S > 1 ? c->split : c->g;            // k_adam adds the ranges up
   bf16 *dz = c->dza, *dzn = c->dzb;
   for (int l = L - 1; l >= 0; --l) {
     GemmArgs w{};                                    // dW_l = act_l^T dZ_l
     w.A = c->act[l]; w.lda = c->dp[l]; w.sA = l == 0 ? 0 : (long long)c->Mp * c->dp[l];
     w.B = dz; w.ldb = c->dp[l + 1]; w.sB = sdz;
     w.M = c->dp[l]; w.N = c->dp[l + 1]; w.K = Mp;
-    w.Z = c->g + c->woff[l]; w.ldz = c->dp[l + 1]; w.sZ = c->P;
-    w.ksplit = S; w.Zs = c->split;
+    w.Z = grads + c->woff[l]; w.ldz = c->dp[l + 1]; w.sZ = c->P;
+    w.ksplit = S; w.sRange = n;
+    w.colsum = grads + c->boff[l]; w.sCol = c->P;    // and db_l, the column sums of dZ_l
     gemm<true, false, EPI_BWD_DW>(c, w);
-    const long long nw = (long long)c->K * w.M * w.N, nb = (long long)c->K * c->dp[l + 1];
-    if (S > 1)
-      hipLaunchKernelGGL(k_sum_splits, dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, c->stream, c->split, S, c->K,
-                         w.M, w.N, c->g + c->woff[l], (long long)w.N, c->P);
-    hipLaunchKernelGGL(k_colsum, dim3((c->dp[l + 1] + 63) / 64, c->K, S), dim3(64 * COLSUM_RG), 0, c->stream, dz, sdz,
-                       Mp, c->dp[l + 1], c->g + c->boff[l], c->P, S, c->split);
-    if (S > 1)
-      hipLaunchKernelGGL(k_sum_splits, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, c->stream, c->split, S, c->K,
-                         1, c->dp[l + 1], c->g + c->boff[l], (long long)c->dp[l + 1], c->P);
     if (l > 0) {                                     // dZ_{l-1} = (dZ_l W_l^T) * SiLU'(Z_{l-1})
       GemmArgs d{};
       d.A = dz; d.lda = c->dp[l + 1]; d.sA = sdz;
@@ -467,18 +461,23 @@ int rsur_train_step(rsur_ctx* c, const void* X_dev, const void* Y_dev, int32_t B
     }
   }
   // Adam with per-member bias corrections
-  std::vector<float> h1(c->K), h2(c->K);
-  for (int k = 0; k < c->K; ++k) {
-    c->t[k] += 1;
-    h1[k] = (float)(1.0 - std::pow(0.9, (double)c->t[k]));
-    h2[k] = (float)(1.0 - std::pow(0.999, (double)c->t[k]));
+  FragMap map{};
+  if (fused_shape(c)) {
+    map.L = L;
+    for (int l = 0; l <= L; ++l) map.dp[l] = c->dp[l];
+    for (int l = 0; l < L; ++l) map.woff[l] = c->woff[l];
   }
-  RCHK(c, hipMemcpyAsync(c->c1, h1.data(), sizeof(float) * c->K, hipMemcpyHostToDevice, c->stream));
-  RCHK(c, hipMemcpyAsync(c->c2, h2.data(), sizeof(float) * c->K, hipMemcpyHostToDevice, c->stream));
-  const long long n = (long long)c->K * c->P;
-  hipLaunchKernelGGL(k_adam, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, c->p, c->g, c->m1, c->m2,
-                     c->pb, c->P, c->K, c->c1, c->c2, lr, 0.9f, 0.999f, 1e-8f);
-  c->pbf_stale = true;
+  for (int k0 = 0; k0 < c->K; k0 += ADAM_MEM) {
+    AdamBias bias{};
+    const int nk = std::min(ADAM_MEM, c->K - k0);
+    for (int k = 0; k < nk; ++k) {
+      c->t[k0 + k] += 1;
+      bias.c1[k] = (float)(1.0 - std::pow(0.9, (double)c->t[k0 + k]));
+      bias.c2[k] = (float)(1.0 - std::pow(0.999, (double)c->t[k0 + k]));
+    }
+    hipLaunchKernelGGL(k_adam, dim3((unsigned)((c->P + 255) / 256), nk), dim3(256), 0, c->stream, c->p, c->g,
+                       (const float*)c->split, S, n, c->m1, c->m2, c->pb, c->pbf, map, c->P, k0, bias, lr, 0.9f, 0.999f, 1e-8f);
+  }
   RCHK(c, hipGetLastError());
   if (loss) {
     RCHK(c, hipMemcpyAsync(loss, c->loss, sizeof(float) * c->K, hipMemcpyDeviceToHost, c->stream));
