@@ -72,15 +72,16 @@ struct rsur_ctx {
   std::string err;
   float *p = nullptr, *g = nullptr, *m1 = nullptr, *m2 = nullptr;   // K x P
   bf16* pb = nullptr;                                               // K x P (weights used)
-  bf16* pbf = nullptr;                                              // K x P, weights by fragments
+  bf16 *pbf = nullptr, *pbt = nullptr;                              // K x P, weights by fragments, and transposed
   std::vector<bf16*> act;                    // act[l]: K x Mp x dp[l] (act[0] shared: Mp x dp[0])
   std::vector<float*> Z;                     // Z[l]: K x Mp x dp[l + 1], hidden layers
   float* out = nullptr;                      // K x Mp x dp[L]
-  bf16 *dza = nullptr, *dzb = nullptr;       // K x Mp x max(dp)
+  std::vector<bf16*> dz;                     // fused pass: dz[l]: K x Mp x dp[l + 1], output gradients
+  bf16 *dza = nullptr, *dzb = nullptr;       // layer by layer: K x Mp x max(dp), two of them in turn
   float *xmu = nullptr, *xsd = nullptr, *ymu = nullptr, *ysd = nullptr, *loss = nullptr;
   int max_split = 0;                         // most ranges of a split gradient reduction; 0: never split
   float* split = nullptr;                    // max_split x K x P: their partial sums
-  float* lpart = nullptr;                    // K x Mp / LOSS_ROWS partial losses
+  float* lpart = nullptr;                    // partial losses, up to K x Mp / 32
   std::vector<long long> t;                  // Adam steps per member
   std::vector<void*> allocs;
 };
@@ -235,7 +236,8 @@ int rsur_create(int32_t din, int32_t width, int32_t depth, int32_t dout, int32_t
   c->max_split = ms > 1 ? ms : 0;
   int e;
   if ((e = ralloc(c, &c->p, KP)) || (e = ralloc(c, &c->g, KP)) || (e = ralloc(c, &c->m1, KP)) ||
-      (e = ralloc(c, &c->m2, KP)) || (e = ralloc(c, &c->pb, KP)) || (e = ralloc(c, &c->pbf, KP)))
+      (e = ralloc(c, &c->m2, KP)) || (e = ralloc(c, &c->pb, KP)) || (e = ralloc(c, &c->pbf, KP)) ||
+      (e = ralloc(c, &c->pbt, KP)))
     return bail(e);
   c->act.resize(c->L);
   c->Z.resize(std::max(c->L - 1, 0));
@@ -244,16 +246,23 @@ int rsur_create(int32_t din, int32_t width, int32_t depth, int32_t dout, int32_t
   for (int l = 0; l < c->L - 1; ++l)
     if ((e = ralloc(c, &c->Z[l], (size_t)c->K * c->Mp * c->dp[l + 1]))) return bail(e);
   const int dmax = *std::max_element(c->dp.begin(), c->dp.end());
+  if (fused_shape(c)) {
+    c->dz.resize(c->L);
+    for (int l = 0; l < c->L; ++l)
+      if ((e = ralloc(c, &c->dz[l], (size_t)c->K * c->Mp * c->dp[l + 1]))) return bail(e);
+  } else if ((e = ralloc(c, &c->dza, (size_t)c->K * c->Mp * dmax)) || (e = ralloc(c, &c->dzb, (size_t)c->K * c->Mp * dmax))) {
+    return bail(e);
+  }
   if ((e = ralloc(c, &c->split, (size_t)c->max_split * KP))) return bail(e);
   if ((e = ralloc(c, &c->out, (size_t)c->K * c->Mp * c->dp[c->L])) ||
-      (e = ralloc(c, &c->dza, (size_t)c->K * c->Mp * dmax)) || (e = ralloc(c, &c->dzb, (size_t)c->K * c->Mp * dmax)) ||
       (e = ralloc(c, &c->xmu, din)) || (e = ralloc(c, &c->xsd, din)) || (e = ralloc(c, &c->ymu, dout)) ||
-      (e = ralloc(c, &c->ysd, dout)) || (e = ralloc(c, &c->loss, ensemble)) || (e = ralloc(c, &c->lpart, (size_t)ensemble * (c->Mp / LOSS_ROWS))))
+      (e = ralloc(c, &c->ysd, dout)) || (e = ralloc(c, &c->loss, ensemble)) || (e = ralloc(c, &c->lpart, (size_t)ensemble * (c->Mp / 32))))
     return bail(e);
   std::vector<float> zeros(std::max(din, dout), 0.0f), ones(std::max(din, dout), 1.0f);
   if (hipMemsetAsync(c->p, 0, sizeof(float) * KP, c->stream) || hipMemsetAsync(c->g, 0, sizeof(float) * KP, c->stream) ||
       hipMemsetAsync(c->m1, 0, sizeof(float) * KP, c->stream) || hipMemsetAsync(c->m2, 0, sizeof(float) * KP, c->stream) ||
       hipMemsetAsync(c->pb, 0, sizeof(bf16) * KP, c->stream) || hipMemsetAsync(c->pbf, 0, sizeof(bf16) * KP, c->stream) ||
+      hipMemsetAsync(c->pbt, 0, sizeof(bf16) * KP, c->stream) ||
       hipMemcpyAsync(c->xmu, zeros.data(), sizeof(float) * din, hipMemcpyHostToDevice, c->stream) ||
       hipMemcpyAsync(c->xsd, ones.data(), sizeof(float) * din, hipMemcpyHostToDevice, c->stream) ||
       hipMemcpyAsync(c->ymu, zeros.data(), sizeof(float) * dout, hipMemcpyHostToDevice, c->stream) ||
@@ -300,7 +309,7 @@ int rsur_set_params(rsur_ctx* c, int32_t member, const float* w) {
     for (int l = 0; l < c->L; ++l) {
       const int n = c->dp[l] / 8 * c->dp[l + 1];
       hipLaunchKernelGGL(k_frag_w, dim3((n + 255) / 256), dim3(256), 0, c->stream, c->pb + off + c->woff[l],
-                         c->pbf + off + c->woff[l], c->dp[l], c->dp[l + 1]);
+                         c->pbf + off + c->woff[l], c->pbt + off + c->woff[l], c->dp[l], c->dp[l + 1]);
     }
   RCHK(c, hipStreamSynchronize(c->stream));
   c->t[member] = 0;
@@ -354,19 +363,54 @@ int rsur_fit_norm(rsur_ctx* c, const void* X_dev, const void* Y_dev, int32_t n) 
 // rows 33.7 / 19.7, 2048 34.4 / 26.1, 4096 37.9 / 38.8, 8192 56 / 60, 16 384 85 / 109).
 constexpr int FUSED_MIN_BLOCKS = 160;
 
-// the fused forward of every member for B rows into out (K x Mp x dp[L], member stride sOut)
-static void forward_fused(rsur_ctx* c, const float* X, int B, float* out, long long sOut) {
+static MlpArgs mlp_args(const rsur_ctx* c, const float* X, int B) {
   MlpArgs g{};
   g.X = X; g.B = B; g.din = c->din; g.xmu = c->xmu; g.xsd = c->xsd;
   g.wf = c->pbf; g.sW = c->P; g.p = c->p; g.sP = c->P;
   g.L = c->L; g.dout = c->dout;
   for (int l = 0; l <= c->L; ++l) g.dp[l] = c->dp[l];
   for (int l = 0; l < c->L; ++l) { g.woff[l] = c->woff[l]; g.boff[l] = c->boff[l]; }
+  return g;
+}
+
+// the fused forward of every member for B rows into out (K x Mp x dp[L], member stride sOut)
+static void forward_fused(rsur_ctx* c, const float* X, int B, float* out, long long sOut) {
+  MlpArgs g = mlp_args(c, X, B);
   g.out = out; g.sOut = sOut; g.ldo = c->dp[c->L];
   if ((long long)((B + 127) / 128) * c->K >= FUSED_MIN_BLOCKS)
     hipLaunchKernelGGL((k_mlp_forward<4, 8>), dim3((B + 127) / 128, c->K), dim3(512), 0, c->stream, g);
   else
     hipLaunchKernelGGL((k_mlp_forward<1, 8>), dim3((B + 31) / 32, c->K), dim3(512), 0, c->stream, g);
+}
+
+// forward, loss and the output gradients of every layer; returns the partial losses per member
+static int train_pass(rsur_ctx* c, const float* X, const float* Y, int B, int Mp) {
+  TrainArgs h{};
+  h.Y = Y; h.ymu = c->ymu; h.ysd = c->ysd; h.wt = c->pbt;
+  for (int l = 0; l < c->L; ++l) { h.act[l] = c->act[l]; h.dz[l] = c->dz[l]; }
+  for (int l = 0; l < c->L - 1; ++l) h.Z[l] = c->Z[l];
+  h.lpart = c->lpart; h.Mp = Mp; h.rows = c->Mp; h.inv = 1.0f / ((float)B * (float)c->dout);
+  const MlpArgs g = mlp_args(c, X, B);
+  // 32 rows per block while two of them per CU hold the whole batch, 64 (the weights read half as often)
+  // beyond.  A step of 5 members, us, 32 / 64 / 128 rows per block: 256 rows 56 / 70 / 98, 2048 96 / 102 /
+  // 128, 3072 108 / 117 / 143, 4096 151 / 142 / 159, 8192 285 / 298 / 333, 60 000 1840 / 1719 / 2000.
+  const bool small = (long long)(Mp / 32) * c->K <= 512;
+  const dim3 grid(Mp / (small ? 32 : 64), c->K);
+  if (small) hipLaunchKernelGGL((k_mlp_train<1, 8>), grid, dim3(512), 0, c->stream, g, h);
+  else hipLaunchKernelGGL((k_mlp_train<2, 8>), grid, dim3(512), 0, c->stream, g, h);
+  return (int)grid.x;
+}
+
+// the arguments of layer l's weight and bias gradients over Mp rows in S ranges
+static GemmArgs dw_args(const rsur_ctx* c, int l, const bf16* dz, long long sdz, int Mp, int S, float* grads) {
+  GemmArgs w{};                                      // dW_l = act_l^T dZ_l
+  w.A = c->act[l]; w.lda = c->dp[l]; w.sA = l == 0 ? 0 : (long long)c->Mp * c->dp[l];
+  w.B = dz; w.ldb = c->dp[l + 1]; w.sB = sdz;
+  w.M = c->dp[l]; w.N = c->dp[l + 1]; w.K = Mp;
+  w.Z = grads + c->woff[l]; w.ldz = c->dp[l + 1]; w.sZ = c->P;
+  w.nmem = c->K; w.ksplit = S; w.sRange = (long long)c->K * c->P;
+  w.colsum = grads + c->boff[l]; w.sCol = c->P;      // and db_l, the column sums of dZ_l
+  return w;
 }
 
 static void forward_infer(rsur_ctx* c, const float* X, int B, int Mp) {
@@ -425,41 +469,44 @@ int rsur_train_step(rsur_ctx* c, const void* X_dev, const void* Y_dev, int32_t B
   int e = check_batch(c, B);
   if (e) return e;
   const int Mp = pad64(B), L = c->L;
-  normalise_inputs(c, (const float*)X_dev, B, Mp);
-  forward_layers(c, Mp);
-  // loss and dLoss/dOutput of every member
-  const long long sOut = (long long)c->Mp * c->dp[L];
-  const int dmax = *std::max_element(c->dp.begin(), c->dp.end());
-  const long long sdz = (long long)c->Mp * dmax;
-  hipLaunchKernelGGL(k_loss, dim3(Mp / LOSS_ROWS, c->K), dim3(LOSS_NT), 0, c->stream, c->out, sOut, c->dp[L],
-                     (const float*)Y_dev, B, c->dout, c->ymu, c->ysd, c->dza, sdz, c->lpart);
-  if (loss)                                          // read by this call alone
-    hipLaunchKernelGGL(k_loss_total, dim3(c->K), dim3(64), 0, c->stream, c->lpart, Mp / LOSS_ROWS,
-                       1.0f / ((float)B * (float)c->dout), c->loss);
   const int S = batch_splits(c, Mp);
   const long long n = (long long)c->K * c->P;
   float* grads = S > 1 ? c->split : c->g;            // k_adam adds the ranges up
-  bf16 *dz = c->dza, *dzn = c->dzb;
-  for (int l = L - 1; l >= 0; --l) {
-    GemmArgs w{};                                    // dW_l = act_l^T dZ_l
-    w.A = c->act[l]; w.lda = c->dp[l]; w.sA = l == 0 ? 0 : (long long)c->Mp * c->dp[l];
-    w.B = dz; w.ldb = c->dp[l + 1]; w.sB = sdz;
-    w.M = c->dp[l]; w.N = c->dp[l + 1]; w.K = Mp;
-    w.Z = grads + c->woff[l]; w.ldz = c->dp[l + 1]; w.sZ = c->P;
-    w.ksplit = S; w.sRange = n;
-    w.colsum = grads + c->boff[l]; w.sCol = c->P;    // and db_l, the column sums of dZ_l
-    gemm<true, false, EPI_BWD_DW>(c, w);
-    if (l > 0) {                                     // dZ_{l-1} = (dZ_l W_l^T) * SiLU'(Z_{l-1})
-      GemmArgs d{};
-      d.A = dz; d.lda = c->dp[l + 1]; d.sA = sdz;
-      d.B = c->pb + c->woff[l]; d.ldb = c->dp[l + 1]; d.sB = c->P;
-      d.M = Mp; d.N = c->dp[l]; d.K = c->dp[l + 1];
-      d.Zp = c->Z[l - 1]; d.ldzp = c->dp[l]; d.sZp = (long long)c->Mp * c->dp[l];
-      d.O = dzn; d.ldo = c->dp[l]; d.sO = sdz;
-      gemm<false, true, EPI_BWD_DA>(c, d);
-      std::swap(dz, dzn);
+  int chunks;                                        // partial losses per member
+  if (fused_shape(c)) {
+    chunks = train_pass(c, (const float*)X_dev, (const float*)Y_dev, B, Mp);
+    DwArgs d{};
+    for (int l = 0; l < L; ++l) {
+      d.g[l] = dw_args(c, l, c->dz[l], (long long)c->Mp * c->dp[l + 1], Mp, S, grads);
+      d.first[l + 1] = d.first[l] + d.g[l].M / TM * (d.g[l].N / TN);
+    }
+    hipLaunchKernelGGL(k_dw, dim3(d.first[L], c->K * S), dim3(256), 0, c->stream, d);
+  } else {
+    normalise_inputs(c, (const float*)X_dev, B, Mp);
+    forward_layers(c, Mp);
+    const long long sOut = (long long)c->Mp * c->dp[L];
+    const long long sdz = (long long)c->Mp * *std::max_element(c->dp.begin(), c->dp.end());
+    chunks = Mp / LOSS_ROWS;
+    hipLaunchKernelGGL(k_loss, dim3(chunks, c->K), dim3(LOSS_NT), 0, c->stream, c->out, sOut, c->dp[L],
+                       (const float*)Y_dev, B, c->dout, c->ymu, c->ysd, c->dza, sdz, c->lpart);
+    bf16 *dz = c->dza, *dzn = c->dzb;
+    for (int l = L - 1; l >= 0; --l) {
+      gemm<true, false, EPI_BWD_DW>(c, dw_args(c, l, dz, sdz, Mp, S, grads));
+      if (l > 0) {                                   // dZ_{l-1} = (dZ_l W_l^T) * SiLU'(Z_{l-1})
+        GemmArgs d{};
+        d.A = dz; d.lda = c->dp[l + 1]; d.sA = sdz;
+        d.B = c->pb + c->woff[l]; d.ldb = c->dp[l + 1]; d.sB = c->P;
+        d.M = Mp; d.N = c->dp[l]; d.K = c->dp[l + 1];
+        d.Zp = c->Z[l - 1]; d.ldzp = c->dp[l]; d.sZp = (long long)c->Mp * c->dp[l];
+        d.O = dzn; d.ldo = c->dp[l]; d.sO = sdz;
+        gemm<false, true, EPI_BWD_DA>(c, d);
+        std::swap(dz, dzn);
+      }
     }
   }
+  if (loss)                                          // read by this call alone
+    hipLaunchKernelGGL(k_loss_total, dim3(c->K), dim3(64), 0, c->stream, c->lpart, chunks,
+                       1.0f / ((float)B * (float)c->dout), c->loss);
   // Adam with per-member bias corrections
   FragMap map{};
   if (fused_shape(c)) {
@@ -476,7 +523,7 @@ int rsur_train_step(rsur_ctx* c, const void* X_dev, const void* Y_dev, int32_t B
       bias.c2[k] = (float)(1.0 - std::pow(0.999, (double)c->t[k0 + k]));
     }
     hipLaunchKernelGGL(k_adam, dim3((unsigned)((c->P + 255) / 256), nk), dim3(256), 0, c->stream, c->p, c->g,
-                       (const float*)c->split, S, n, c->m1, c->m2, c->pb, c->pbf, map, c->P, k0, bias, lr, 0.9f, 0.999f, 1e-8f);
+                       (const float*)c->split, S, n, c->m1, c->m2, c->pb, c->pbf, c->pbt, map, c->P, k0, bias, lr, 0.9f, 0.999f, 1e-8f);
   }
   RCHK(c, hipGetLastError());
   if (loss) {

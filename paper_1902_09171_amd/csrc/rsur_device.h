@@ -77,17 +77,16 @@ __device__ __forceinline__ float silu_grad(float z) {
 // Measured at that size, TK = 32 and no request ahead / now: forward 19.4 / 15.9 us, output gradient
 // 12.3 / 11.4, weight gradient 24.8 (its transposed tiles stored to LDS element by element) / 13.4
 // including the column sums, which took 9.7 in a kernel of their own.
+struct GemmLds { __attribute__((aligned(16))) bf16 a[TM * LDK], b[TN * LDK]; };
 template <bool AT, bool BT, int EPI>
-__global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
-  __shared__ __attribute__((aligned(16))) bf16 sa[TM * LDK];
-  __shared__ __attribute__((aligned(16))) bf16 sb[TN * LDK];
-  // blockIdx.z = member + nmem * range: the weight gradient's reduction over the batch is split
+__device__ __forceinline__ void gemm_tile(const GemmArgs& g, int m0, int n0, int z, GemmLds& sh) {
+  bf16 *sa = sh.a, *sb = sh.b;
+  // z = member + nmem * range: the weight gradient's reduction over the batch is split
   // into ksplit consecutive ranges of K / ksplit (a multiple of TK), each block taking one
-  const int mem = blockIdx.z % g.nmem, ks = blockIdx.z / g.nmem;
+  const int mem = z % g.nmem, ks = z / g.nmem;
   const int kc = g.K / g.ksplit;
   const bf16* A = g.A + mem * g.sA;
   const bf16* B = g.B + mem * g.sB;
-  const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
   const int t = threadIdx.x, w = t >> 6, l = t & 63;
   const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
   v16f acc;
@@ -95,7 +94,7 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
   for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
   // the first row of blocks of the weight gradient adds up the columns of B as they pass by: wave w takes
   // the rows k with k % COL_G in [4 w, 4 w + 4), a sum each, lane l column n0 + l
-  const bool cols = EPI == EPI_BWD_DW && blockIdx.y == 0;
+  const bool cols = EPI == EPI_BWD_DW && m0 == 0;
   float col_acc[4] = {0, 0, 0, 0};
   TileLoad<!AT> la;
   TileLoad<BT> lb;
@@ -159,7 +158,26 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
   }
 }
 
-// ------------------------------------------------------------------ fused inference
+template <bool AT, bool BT, int EPI>
+__global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
+  __shared__ GemmLds sh;
+  gemm_tile<AT, BT, EPI>(g, blockIdx.y * TM, blockIdx.x * TN, blockIdx.z, sh);
+}
+
+constexpr int MAXL = 8;            // most layers of the fused kernels
+// The weight gradients of all layers in one launch: 64 tiles of five members in 8 ranges are 2560 blocks, one
+// launch of them without the gaps and half-empty ends of five: 51 us for 4096 rows, 67 in five launches.
+// LDS reads bound it: a wave reads two operands per product of 32 cycles.
+struct DwArgs { GemmArgs g[MAXL]; int first[MAXL + 1]; };   // layer l: tiles first[l] ... first[l + 1]
+__global__ __launch_bounds__(256) void k_dw(DwArgs d) {
+  __shared__ GemmLds sh;
+  int l = 0;
+  while ((int)blockIdx.x >= d.first[l + 1]) ++l;
+  const int e = blockIdx.x - d.first[l], nx = d.g[l].N / TN;
+  gemm_tile<true, false, EPI_BWD_DW>(d.g[l], e / nx * TM, e % nx * TN, blockIdx.y, sh);
+}
+
+// ------------------------------------------------------------------ fused inference and training pass
 // Every layer of one member for 32 RT rows in one block of NW waves: the activations stay in LDS (one
 // buffer, overwritten in place between two barriers per layer) and the first layer normalises the raw
 // inputs itself.  A wave computes the transposed product: 32 output features of the weights (operand A)
@@ -179,7 +197,7 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
 // a transposed weight copy, a full division and inputs normalised one load at a time (304 us with four
 // waves of two tiles instead of eight of one, 288 in the end); 256 rows 15.8 us, ~44 layer by layer in
 // six launches.
-constexpr int FW = 256, FLD = FW + 8, MAXL = 8;
+constexpr int FW = 256, FLD = FW + 8;
 
 struct MlpArgs {
   const float* X; int B, din;
@@ -208,10 +226,49 @@ __device__ __forceinline__ float silu_fast(float z) {
   return fmaf(fmaf(-d, q, z), r, q);
 }
 
-template <int RT, int NW>
-__global__ __launch_bounds__(64 * NW, RT == 1 ? 2 : 4) void k_mlp_forward(MlpArgs g) {
-  constexpr int NT = 64 * NW, ROWS = 32 * RT, FT = (FW / 32) / NW;   // FT feature tiles per wave at most
-  __shared__ __attribute__((aligned(16))) bf16 act[ROWS * FLD];
+// The training pass keeps going where inference ends: the block turns its outputs into their gradient and
+// walks the layers back with the transposed weights (their own copy by fragments).  Activations and output
+// gradients are written row by row for the weight gradients; a pre-activation is read again by the lane
+// that wrote it, so these go out and come in as whole accumulators, 1 KB per wave and access.  Layer by layer
+// every product read its input and the pre-activations in rows and wrote them again.  Bound by memory: 4096
+// rows of 5 members move 260 MB, 50 us at 5.2 TB/s; 76 us (64 rows per block), 131 and the gaps between 11
+// launches before.
+struct TrainArgs {
+  const float *Y, *ymu, *ysd;
+  const bf16* wt;                            // BF16 transposed weights by fragments, member stride sW
+  bf16 *act[MAXL], *dz[MAXL];                // normalised input and activations; output gradients of the layers
+  float* Z[MAXL];                            // pre-activations in accumulator order
+  float* lpart;                              // [member][block] squared-error sums
+  int Mp, rows;                              // padded rows of this batch; rows of a member in the buffers
+  float inv;
+};
+
+// rows of a block's LDS buffer to / from memory, dp <= FW columns, two rows per wave at a time
+template <int ROWS, int NW, bool OUT>
+__device__ __forceinline__ void mlp_rows(bf16* lds, bf16* mem, int dp, int nrows) {
+  const int l = threadIdx.x & 63, k = 8 * (l & 31);
+  for (int r = 2 * (threadIdx.x >> 6) + (l >> 5); r < ROWS; r += 2 * NW) {
+    if (k >= dp) continue;
+    if constexpr (OUT) {
+      if (r < nrows) *(v8bf*)(mem + (long long)r * dp + k) = *(const v8bf*)(lds + r * FLD + k);
+    } else {
+      v8bf v = {};
+      if (r < nrows) v = *(const v8bf*)(mem + (long long)r * dp + k);
+      *(v8bf*)(lds + r * FLD + k) = v;
+    }
+  }
+}
+
+// SiLU'(z) with the logistic function as silu_fast's quotient; NaN where that is
+__device__ __forceinline__ float silu_grad_fast(float z) {
+  const float d = 1.0f + __builtin_amdgcn_exp2f(z * -1.442695041f);
+  const float r = __builtin_amdgcn_rcpf(d), s = fmaf(fmaf(-d, r, 1.0f), r, r);
+  return s * (1.0f + z * (1.0f - s));
+}
+
+template <int RT, int NW, bool TRAIN>
+__device__ __forceinline__ void mlp_block(const MlpArgs& g, const TrainArgs& h, bf16* act) {
+  constexpr int ROWS = 32 * RT, FT = (FW / 32) / NW;   // FT feature tiles per wave at most
   const int mem = blockIdx.y, m0 = blockIdx.x * ROWS;
   const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = t & 63;
   const int lr = l & 31, lk = 8 * (l >> 5), lf = 4 * (l >> 5);
@@ -220,14 +277,16 @@ __global__ __launch_bounds__(64 * NW, RT == 1 ? 2 : 4) void k_mlp_forward(MlpArg
   // RT = 1: a layer's whole operand of this wave, requested while the layer before is being activated
   constexpr int KM = RT == 1 ? FW / 16 : 1;
   v8bf pre[FT][KM];
-  auto request_layer = [&](int L) {
-    const int KS = g.dp[L] >> 4, NF = L + 1 < g.L ? g.dp[L + 1] >> 5 : (g.dout + 31) >> 5;
-    const bf16* W0 = Wm + g.woff[L] + ((long long)w * KS * 64 + l) * 8;
+  auto request_operand = [&](const bf16* W, int KS, int NF) {
+    const bf16* W0 = W + ((long long)w * KS * 64 + l) * 8;
 #pragma unroll
     for (int k = 0; k < KM; ++k)
 #pragma unroll
       for (int f = 0; f < FT; ++f)
         if (k < KS && w + NW * f < NF) pre[f][k] = *(const v8bf*)(W0 + ((long long)NW * f * KS + k) * 512);
+  };
+  auto request_layer = [&](int L) {
+    request_operand(Wm + g.woff[L], g.dp[L] >> 4, L + 1 < g.L ? g.dp[L + 1] >> 5 : (g.dout + 31) >> 5);
   };
   if constexpr (RT == 1) request_layer(0);
   // normalised inputs: a lane keeps its column's statistics and has RB rows' loads on the way at once (row
@@ -250,9 +309,8 @@ __global__ __launch_bounds__(64 * NW, RT == 1 ? 2 : 4) void k_mlp_forward(MlpArg
   }
   __syncthreads();
   const bf16* arow = act + lr * FLD + lk;
-  for (int L = 0; L < g.L - 1; ++L) {
-    const int KS = g.dp[L] >> 4, NF = g.dp[L + 1] >> 5;
-    v16f acc[FT][RT];
+  // acc = the product of one layer: KS steps of 16 over the rows in LDS, NF feature tiles
+  auto product = [&](v16f (&acc)[FT][RT], const bf16* W, int KS, int NF) {
 #pragma unroll
     for (int f = 0; f < FT; ++f)
 #pragma unroll
@@ -260,7 +318,7 @@ __global__ __launch_bounds__(64 * NW, RT == 1 ? 2 : 4) void k_mlp_forward(MlpArg
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[f][c][r] = 0.0f;
     // feature tiles w, w + NW, ...; a layer narrower than the block leaves its last waves idle
-    const bf16* W0 = Wm + g.woff[L] + ((long long)w * KS * 64 + l) * 8;
+    const bf16* W0 = W + ((long long)w * KS * 64 + l) * 8;
     const long long wstep = (long long)NW * KS * 512;
     if (w < NF) {
       if constexpr (RT == 1) {
@@ -308,6 +366,37 @@ __global__ __launch_bounds__(64 * NW, RT == 1 ? 2 : 4) void k_mlp_forward(MlpArg
         }
       }
     }
+  };
+  const int nrows = min(ROWS, h.Mp - m0);        // training: rows of this block that the buffers hold
+#pragma unroll 1                                 // peeled, the kernel misses the instruction cache: 8.6 / 10.8 us for 256 rows
+  for (int L = 0; L < g.L - 1; ++L) {
+    const int NF = g.dp[L + 1] >> 5;
+    if constexpr (TRAIN)                         // this layer's input, the network's (alike for all members) once
+      if (L > 0 || mem == 0)
+        mlp_rows<ROWS, NW, true>(act, h.act[L] + (L > 0 ? mem * (long long)h.rows * g.dp[L] : 0) + (long long)m0 * g.dp[L],
+                                 g.dp[L], nrows);
+    v16f acc[FT][RT];
+    product(acc, Wm + g.woff[L], g.dp[L] >> 4, NF);
+    if constexpr (TRAIN) {
+      float* Z = h.Z[L] + mem * (long long)h.rows * g.dp[L + 1] + 4 * l;
+#pragma unroll
+      for (int f = 0; f < FT; ++f) {
+        const int ft = w + NW * f;
+        if (ft >= NF) break;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float4 bias = *(const float4*)(Pm + g.boff[L] + 32 * ft + 8 * q + lf);
+#pragma unroll
+          for (int c = 0; c < RT; ++c) {
+            acc[f][c][4 * q] += bias.x; acc[f][c][4 * q + 1] += bias.y;
+            acc[f][c][4 * q + 2] += bias.z; acc[f][c][4 * q + 3] += bias.w;
+            if (32 * c < nrows)
+              *(float4*)(Z + (((long long)(m0 >> 5) + c) * NF + ft) * 1024 + q * 256) =
+                  make_float4(acc[f][c][4 * q], acc[f][c][4 * q + 1], acc[f][c][4 * q + 2], acc[f][c][4 * q + 3]);
+          }
+        }
+      }
+    }
     if constexpr (RT == 1) request_layer(L + 1);
     __syncthreads();                             // every wave has read this layer's input
     auto activate = [&](auto&& fn) {             // features 32 ft + 8 q + lf + 0..3 of row 32 c + lr
@@ -318,7 +407,7 @@ __global__ __launch_bounds__(64 * NW, RT == 1 ? 2 : 4) void k_mlp_forward(MlpArg
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int n = 32 * ft + 8 * q + lf;
-          const float4 bias = *(const float4*)(Pm + g.boff[L] + n);
+          const float4 bias = TRAIN ? make_float4(0, 0, 0, 0) : *(const float4*)(Pm + g.boff[L] + n);
 #pragma unroll
           for (int c = 0; c < RT; ++c) {
             const v4bf o = {(bf16)fn(acc[f][c][4 * q] + bias.x), (bf16)fn(acc[f][c][4 * q + 1] + bias.y),
@@ -334,9 +423,21 @@ __global__ __launch_bounds__(64 * NW, RT == 1 ? 2 : 4) void k_mlp_forward(MlpArg
     __syncthreads();
   }
   // the linear output: only the tiles that hold real outputs, shared out by row tiles
-  const int KS = g.dp[g.L - 1] >> 4, NF = (g.dout + 31) >> 5;
-  for (int it = w; it < NF * RT; it += NW) {
+  const int KS = g.dp[g.L - 1] >> 4, NF = (g.dout + 31) >> 5, dpo = g.dp[g.L];
+  if constexpr (TRAIN)
+    if (g.L > 1 || mem == 0)
+      mlp_rows<ROWS, NW, true>(act, h.act[g.L - 1] + (g.L > 1 ? mem * (long long)h.rows * g.dp[g.L - 1] : 0) +
+                               (long long)m0 * g.dp[g.L - 1], g.dp[g.L - 1], nrows);
+  bf16* dzo = TRAIN ? h.dz[g.L - 1] + (mem * (long long)h.rows + m0) * dpo : nullptr;
+  float sq = 0.0f;                               // training: squared errors of this lane
+  for (int it = w; it < (TRAIN ? dpo >> 5 : NF) * RT; it += NW) {
     const int ft = it / RT, c = it % RT;
+    if (TRAIN && ft >= NF) {                     // padding columns
+      if (32 * c < nrows)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) *(v4bf*)(dzo + (32 * c + lr) * dpo + 32 * ft + 8 * q + lf) = (v4bf){};
+      continue;
+    }
     const bf16* W0 = Wm + g.woff[g.L - 1] + ((long long)ft * KS * 64 + l) * 8;
     v16f acc;
 #pragma unroll
@@ -351,7 +452,22 @@ __global__ __launch_bounds__(64 * NW, RT == 1 ? 2 : 4) void k_mlp_forward(MlpArg
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const v8bf*)(W0 + k * 512), *(const v8bf*)(arow + c * 32 * FLD + 16 * k), acc, 0, 0, 0);
     }
     const int m = m0 + 32 * c + lr;
-    if (m < g.B) {
+    if constexpr (TRAIN) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        v4bf d = {};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int n = 32 * ft + 8 * q + lf + e;
+          if (m >= g.B || n >= g.dout) continue;
+          const float yn = (h.Y[(long long)m * g.dout + n] - h.ymu[n]) / h.ysd[n];
+          const float r = acc[4 * q + e] + Pm[g.boff[g.L - 1] + n] - yn;
+          sq += r * r;
+          d[e] = (bf16)(2.0f * r * h.inv);
+        }
+        if (32 * c < nrows) *(v4bf*)(dzo + (32 * c + lr) * dpo + 32 * ft + 8 * q + lf) = d;
+      }
+    } else if (m < g.B) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int n = 32 * ft + 8 * q + lf;
@@ -363,10 +479,79 @@ __global__ __launch_bounds__(64 * NW, RT == 1 ? 2 : 4) void k_mlp_forward(MlpArg
       }
     }
   }
+  if constexpr (TRAIN) {
+    if constexpr (RT == 1)
+      if (g.L > 1) request_operand(h.wt + mem * g.sW + g.woff[g.L - 1], dpo >> 4, g.dp[g.L - 1] >> 5);
+    __shared__ float sums[NW];
+    for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
+    if (l == 0) sums[w] = sq;
+    __syncthreads();                             // the output gradient is written, the last input read
+    if (t == 0) {
+      float v = 0.0f;
+      for (int q = 0; q < NW; ++q) v += sums[q];
+      h.lpart[(long long)mem * gridDim.x + blockIdx.x] = v;
+    }
+    if (g.L > 1) mlp_rows<ROWS, NW, false>(act, dzo, dpo, nrows);
+    __syncthreads();
+#pragma unroll 1
+    for (int L = g.L - 1; L >= 1; --L) {         // dZ_{L-1} = (dZ_L W_L^T) * SiLU'(Z_{L-1})
+      const int NF = g.dp[L] >> 5;
+      const float* Z = h.Z[L - 1] + mem * (long long)h.rows * g.dp[L] + 4 * l;
+      float4 z[FT][RT][4];                       // on their way while the product is computed
+#pragma unroll
+      for (int f = 0; f < FT; ++f)
+#pragma unroll
+        for (int c = 0; c < RT; ++c)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (w + NW * f < NF && 32 * c < nrows)
+              z[f][c][q] = *(const float4*)(Z + (((long long)(m0 >> 5) + c) * NF + w + NW * f) * 1024 + q * 256);
+      v16f acc[FT][RT];
+      product(acc, h.wt + mem * g.sW + g.woff[L], g.dp[L + 1] >> 4, NF);
+      if constexpr (RT == 1)
+        if (L > 1) request_operand(h.wt + mem * g.sW + g.woff[L - 1], g.dp[L] >> 4, g.dp[L - 1] >> 5);
+      __syncthreads();                           // every wave has read dZ_L
+      auto back = [&](auto&& fn) {
+#pragma unroll
+        for (int f = 0; f < FT; ++f) {
+          const int ft = w + NW * f;
+          if (ft >= NF) break;
+#pragma unroll
+          for (int c = 0; c < RT; ++c) {
+            if (32 * c >= nrows) break;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const float4 y = z[f][c][q];
+              const v4bf o = {(bf16)(acc[f][c][4 * q] * fn(y.x)), (bf16)(acc[f][c][4 * q + 1] * fn(y.y)),
+                              (bf16)(acc[f][c][4 * q + 2] * fn(y.z)), (bf16)(acc[f][c][4 * q + 3] * fn(y.w))};
+              *(v4bf*)(act + (32 * c + lr) * FLD + 32 * ft + 8 * q + lf) = o;
+            }
+          }
+        }
+      };
+      float bad = 0.0f;
+      back([&](float y) { const float d = silu_grad_fast(y); bad = fmaf(d, 0.0f, bad); return d; });
+      if (__any(!(bad == 0.0f))) back([](float y) { return silu_grad(y); });
+      __syncthreads();
+      mlp_rows<ROWS, NW, true>(act, h.dz[L - 1] + (mem * (long long)h.rows + m0) * g.dp[L], g.dp[L], nrows);
+    }
+  }
 }
 
-// the fragment copy of one layer's BF16 weights; one thread per 8 consecutive k
-__global__ void k_frag_w(const bf16* pb, bf16* pbf, int Kd, int Nd) {
+template <int RT, int NW>
+__global__ __launch_bounds__(64 * NW, RT == 1 ? 2 : 4) void k_mlp_forward(MlpArgs g) {
+  __shared__ __attribute__((aligned(16))) bf16 act[32 * RT * FLD];
+  mlp_block<RT, NW, false>(g, TrainArgs{}, act);
+}
+template <int RT, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void k_mlp_train(MlpArgs g, TrainArgs h) {
+  __shared__ __attribute__((aligned(16))) bf16 act[32 * RT * FLD];
+  mlp_block<RT, NW, true>(g, h, act);
+}
+
+// the fragment copies of one layer's BF16 weights; one thread per 8 consecutive k, and per 8 consecutive n
+// of the transposed copy
+__global__ void k_frag_w(const bf16* pb, bf16* pbf, bf16* pbt, int Kd, int Nd) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= (Kd >> 3) * Nd) return;
   const int n = e % Nd, k = 8 * (e / Nd);
@@ -374,6 +559,8 @@ __global__ void k_frag_w(const bf16* pb, bf16* pbf, int Kd, int Nd) {
 #pragma unroll
   for (int q = 0; q < 8; ++q) v[q] = pb[(long long)(k + q) * Nd + n];
   *(v8bf*)(pbf + frag_index(k, n, Kd)) = v;
+  const int k1 = e % Kd, n1 = 8 * (e / Kd);
+  *(v8bf*)(pbt + frag_index(n1, k1, Nd)) = *(const v8bf*)(pb + (long long)k1 * Nd + n1);
 }
 
 // raw inputs (B x din, FP32) -> normalised BF16 rows of width dp0, zero padding
@@ -434,14 +621,14 @@ __global__ __launch_bounds__(64) void k_loss_total(const float* part, int chunks
 }
 
 // Adam on every padded parameter of every member: the gradient is the sum, in order, of the S ranges'
-// partial sums (S = 1: gr itself); refreshes the BF16 weights and their copy by fragments.  Padding
+// partial sums (S = 1: gr itself); refreshes the BF16 weights and their copies by fragments.  Padding
 // stays zero: its gradient is zero.  Bound by memory: 8 ranges of 5 x 263 000 parameters are 85 MB in and
 // out, 19.7 us (9 us before, and 10 launches of 4.8 that added the ranges up into a buffer of their own).
 constexpr int ADAM_MEM = 16;
 struct AdamBias { float c1[ADAM_MEM], c2[ADAM_MEM]; };   // bias corrections of members mem0 .. of this launch
 struct FragMap { int L; int dp[MAXL + 1]; long long woff[MAXL]; };   // L = 0: no fragment copy
 __global__ void k_adam(float* p, float* gr, const float* part, int S, long long sRange, float* m1, float* m2, bf16* pb,
-                       bf16* pbf, FragMap map, long long P, int mem0, AdamBias bias, float lr, float b1, float b2,
+                       bf16* pbf, bf16* pbt, FragMap map, long long P, int mem0, AdamBias bias, float lr, float b1, float b2,
                        float eps) {
   const long long o = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (o >= P) return;
@@ -467,7 +654,9 @@ __global__ void k_adam(float* p, float* gr, const float* part, int S, long long 
     const long long r = o - map.woff[l];
     if (r < 0 || r >= (long long)map.dp[l] * map.dp[l + 1]) continue;
     const int k = (int)r / map.dp[l + 1], n = (int)r - k * map.dp[l + 1];
-    pbf[(long long)(mem0 + q) * P + map.woff[l] + frag_index(k, n, map.dp[l])] = (bf16)w;
+    const long long base = (long long)(mem0 + q) * P + map.woff[l];
+    pbf[base + frag_index(k, n, map.dp[l])] = (bf16)w;
+    pbt[base + frag_index(n, k, map.dp[l + 1])] = (bf16)w;
   }
 }
 
