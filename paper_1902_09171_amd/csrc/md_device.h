@@ -125,6 +125,7 @@ struct Stage {                    // set_deformation staging, one per cell
   double Q[9], R[9], dR[9], Hn[9], F[9];
   double J, wmin;
   int nb[3], nbins, status;
+  int hold, go;                    // the host has to look at this cell first; the whole batch was committed
   double density;
 };
 
@@ -2309,11 +2310,7 @@ __device__ inline void tilt_reduce(double H[9]) {
 }
 
 // stage everything a deformation needs; no state is modified (bw: the bin width, (rc + skin) / f)
-__global__ void k_qr_stage(const double* Fall, const CellDev* cells, Stage* st, int ncells, double rcs, double bw) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= ncells) return;
-  Stage& S = st[c];
-  const CellDev& C = cells[c];
+__device__ inline void qr_stage_cell(const double* Fall, const CellDev& C, Stage& S, int c, double rcs, double bw) {
   for (int k = 0; k < 9; ++k) S.F[k] = Fall[9 * c + k];
   S.status = qr_gs(S.F, S.Q, S.R);
   if (S.status) return;
@@ -2332,6 +2329,20 @@ __global__ void k_qr_stage(const double* Fall, const CellDev* cells, Stage* st, 
   for (int q = 0; q < 3; ++q) S.nb[q] = min(BIN_MASK, max(1, (int)floor(w[q] / bw)));
   S.nbins = S.nb[0] * S.nb[1] * S.nb[2];
   S.density = (double)C.n / fabs(det3(S.Hn));
+}
+
+// The results that the host decides by go straight to its memory (pinned), next to the ones that the commit
+// behind this kernel reads: a cell whose F is refused, that needs more bins than it has or is denser
+// than the lists are sized for holds the whole batch back.
+__global__ void k_qr_stage(const double* Fall, const CellDev* cells, Stage* st, int ncells, double rcs, double bw,
+                           double dens_ok, int* status, int* nbins, double* density) {
+  const int c = blockIdx.x * blockDim.x + threadIdx.x;
+  if (c >= ncells) return;
+  Stage& S = st[c];
+  S.nbins = 0; S.density = 0.0;
+  qr_stage_cell(Fall, cells[c], S, c, rcs, bw);
+  S.hold = S.status != 0 || S.nbins > cells[c].bin_cap || S.density > dens_ok;
+  status[c] = S.status; nbins[c] = S.nbins; density[c] = S.density;
 }
 
 // fill the derived box fields of a cell from C.H (bw: the bin width)
@@ -2384,12 +2395,18 @@ __device__ inline float kept_list_threshold(const CellDev& C, double rc, double 
   return hs > 0.0 ? (float)(hs * hs) : -1.0f;
 }
 
-__global__ void k_qr_commit(CellDev* cells, const Stage* st, int ncells, double rc, double rcs, double bw,
-                            int force_build) {
+__global__ void k_qr_commit(CellDev* cells, Stage* st, int ncells, double rc, double rcs, double bw,
+                            int force_build, int checked) {
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
+  int hold = 0;
+  if (!checked)
+    for (int k = threadIdx.x; k < ncells; k += blockDim.x) hold |= st[k].hold;
+  hold = __syncthreads_or(hold);
   if (c >= ncells) return;
   CellDev& C = cells[c];
-  const Stage& S = st[c];
+  Stage& S = st[c];
+  S.go = !hold;
+  if (hold) return;
   for (int k = 0; k < 9; ++k) {
     C.H[k] = S.Hn[k]; C.Q[k] = S.Q[k]; C.R[k] = S.R[k]; C.Rprev[k] = S.R[k]; C.F[k] = S.F[k];
   }
@@ -2427,6 +2444,7 @@ __global__ __launch_bounds__(TILE) void k_remap(MDArgs a, const Stage* st) {
   if (tb >= a.ntiles) return;
   const Tile t = a.tiles[tb];
   if ((int)threadIdx.x >= t.count) return;
+  if (!st[t.cell].go) return;
   const double* d = st[t.cell].dR;
   const long long i = (long long)t.begin + threadIdx.x;
   const double x = a.x[i], y = a.y[i], z = a.z[i];
