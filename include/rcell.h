@@ -88,7 +88,9 @@ typedef struct rcell_ctx rcell_ctx;
  * (l, c, 0xFFFFFFFF, 0xFFFFFFFF) (a counter that the Langevin noise, whose third word is the
  * step, never reaches), mapped to (0,1) as (w + 1/2) 2^-32, two Box-Muller pairs give its three
  * Cartesian components (the fourth normal is unused); the cell's mean velocity is removed and the
- * velocities are scaled so that mvv2e sum m v.v = (3 N - 3) kB T exactly.  On failure *out is NULL
+ * velocities are scaled so that mvv2e sum m v.v = (3 N - 3) kB T exactly.  Beside the neighbour
+ * list a second, pruned list of its size plus 32 bytes per atom is kept for the steps between rebuilds;
+ * without the memory for it the cells run on the full list, with the same results.  On failure *out is NULL
  * and everything the call allocated is freed.  For tests of that path, the environment variable
  * RCELL_FAULT_ALLOC = k (k >= 1) makes the k-th device allocation of the call fail as if the device
  * were out of memory (RCELL_ERR_OOM). */
@@ -174,10 +176,10 @@ int rcell_get_rebuilds(rcell_ctx* ctx, int64_t* count);
 int rcell_set_lanes(rcell_ctx* ctx, int32_t lanes);
 /* How a neighbour rebuild prepares its cells (binning, bin order, reordering the atoms by bin):
  * mode 1 runs all of it in one launch with one block per cell (every cell must have at most 4096
- * atoms, else RCELL_ERR_ARG), mode 2 in six launches over the tiles of the cells that rebuild,
+ * atoms, else RCELL_ERR_ARG), mode 2 in four launches over the tiles of the cells that rebuild,
  * mode 0 (the default) picks 1 when every cell is small enough.  Results are identical either way;
  * mode 1 also runs the per-cell reduction of each MD step in the same launch, which makes a step
- * six launches shorter. */
+ * four launches shorter. */
 int rcell_set_build_mode(rcell_ctx* ctx, int32_t mode);
 int rcell_get_lanes(rcell_ctx* ctx, int32_t* lanes);
 /* Width of the neighbour-build bins: at least (rc + skin) / f along every perpendicular box width,
