@@ -645,7 +645,7 @@ def bench_surrogate(args, torch, rcell, configs):
     achieved = flop_eval * K * B_BIG / ev_big
     roofline = {"bound": "mfma", "achieved": achieved / 1e12, "peak": PEAK_BF16 / 1e12, "unit": "TFLOP/s",
                 "frac": achieved / PEAK_BF16, "traffic": None,
-                "kernel": "forward pass (k_norm_in, 5 k_gemm layers over the ensemble, k_ensemble)",
+                "kernel": "forward pass (k_mlp_forward over the ensemble, k_ensemble)",
                 "avg_us": ev_big * 1e6, "batch": B_BIG, "flop_per_launch": flop_eval * K * B_BIG}
     out = {"metric": "surrogate stress-evals/s (ensemble of 5)", "value": B_BAR / t_bar, "unit": "evals/s",
            "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": t_bar * 1e3,

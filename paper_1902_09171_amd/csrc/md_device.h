@@ -2221,8 +2221,8 @@ __device__ __forceinline__ void build_run(const MDArgs& a, int cell, int b0, int
 // Measured on one MI355X, per MD step, against one lane per atom (sets of 4096 tiles and more) and eight
 // lanes per atom walking the candidate ranges: 100 cells of 10^4 beads 62.6 -> 37.1 us, 50 glassy
 // cells 102 -> 54 us, 128 cells of 40 000 beads 205 -> 147 us (all 5.1 M beads at once 2.19 -> 1.57 ms).
-// Where a few of many large cells rebuild in every step (19 of 256 cells of 40 000 beads) a lane per atom was as
-// fast: 258 us then, 286 now on a card 4 % slower, ~5400 cycles of a SIMD per bin of 5.8 beads and ~157
+// Where a few of many large cells rebuild in every step (19 of 256 cells of 40 000 beads) a lane per atom was
+// faster: 226 us against 273 on the same card, ~5400 cycles of a SIMD per bin of 5.8 beads and ~157
 // candidates (three rounds, 82 % of their lanes in use).
 template <class P, class LT>
 __global__ __launch_bounds__(64 * BLD_WAVES) void k_build_list(MDArgs a, int scatter, int lparts) {

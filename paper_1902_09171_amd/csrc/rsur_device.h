@@ -167,7 +167,8 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
 constexpr int MAXL = 8;            // most layers of the fused kernels
 // The weight gradients of all layers in one launch: 64 tiles of five members in 8 ranges are 2560 blocks, one
 // launch of them without the gaps and half-empty ends of five: 51 us for 4096 rows, 67 in five launches.
-// LDS reads bound it: a wave reads two operands per product of 32 cycles.
+// Latency and the L2 bound it: parts of 32 x 64 per wave, with a quarter fewer LDS reads, took the same 51 us, and
+// the tiles of one member and range placed on one XCD 48.
 struct DwArgs { GemmArgs g[MAXL]; int first[MAXL + 1]; };   // layer l: tiles first[l] ... first[l + 1]
 __global__ __launch_bounds__(256) void k_dw(DwArgs d) {
   __shared__ GemmLds sh;

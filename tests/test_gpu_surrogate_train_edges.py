@@ -39,7 +39,7 @@ def backward(cache, dY):
 
 @pytest.mark.parametrize("rows", [1, 63, 512, 513, 1100, 4096])
 @pytest.mark.parametrize("kw, K", [(dict(din=40, width=64, depth=2, dout=3), 17), (dict(din=100, width=300, depth=1, dout=65), 2),
-                                   (dict(din=70, width=1, depth=0, dout=5), 3)])
+                                   (dict(din=70, width=1, depth=0, dout=5), 3), (dict(din=200, width=100, depth=3, dout=65), 2)])
 def test_gradients_and_updated_weights(rows, kw, K):
     import torch
     from paper_1902_09171_amd import rsur
