@@ -2578,13 +2578,10 @@ __global__ void k_set_pending(CellDev* cells, int first, int count, unsigned lon
   if (c < first + count) { cells[c].rebuild = 1; cells[c].pending = 1; cells[c].prune = 1; }
 }
 
-// the next force pass of every cell prunes (the list's lanes per atom have changed), and, with
-// `rebuild`, builds first (the list itself has moved)
-__global__ void k_set_prune(CellDev* cells, int ncells, int rebuild) {
+// the next force pass of every cell prunes (the pruned list's lanes per atom have changed, or it has moved)
+__global__ void k_set_prune(CellDev* cells, int ncells) {
   const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= ncells) return;
-  cells[c].prune = 1;
-  if (rebuild) cells[c].rebuild = 1;
+  if (c < ncells) cells[c].prune = 1;
 }
 
 }  // namespace rcell

@@ -502,7 +502,9 @@ int layout_bins(rcell_ctx* c, const std::vector<int>& need) {
   return push_bin_layout(c);
 }
 
-int ensure_list_capacity(rcell_ctx* c, int need) {
+// keep: the lists built so far move along (list_index does not depend on the capacity, so they are the
+// first blocks of the new one)
+int ensure_list_capacity(rcell_ctx* c, int need, bool keep) {
   need = (need + NBLK_MAX - 1) / NBLK_MAX * NBLK_MAX;   // whole list blocks of either length
   if (need <= c->maxnb) return RCELL_OK;
   // the pair loops address the list with 32-bit element indices
@@ -512,8 +514,13 @@ int ensure_list_capacity(rcell_ctx* c, int need) {
   // the new list is allocated before the old one is freed: on failure the context keeps its list
   // and its capacity
   char* q = nullptr;
-  const int st = dalloc(c, &q, (size_t)need * c->npad * (c->list16 ? sizeof(uint16_t) : sizeof(int)));
+  const size_t row = (size_t)c->npad * (c->list16 ? sizeof(uint16_t) : sizeof(int));
+  const int st = dalloc(c, &q, need * row);
   if (st) return st;
+  if (keep && c->nbr) {
+    HIPCHK(c, hipMemcpyAsync(q, c->nbr, c->maxnb * row, hipMemcpyDeviceToDevice, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+  }
   dfree(c, c->nbr);
   c->nbr = q;
   c->maxnb = need;
@@ -556,8 +563,8 @@ void ensure_pruned(rcell_ctx* c) {
   c->prune_cap = c->maxnb;
 }
 
-void set_prune(rcell_ctx* c, int rebuild) {
-  hipLaunchKernelGGL(k_set_prune, dim3((c->ncells + 63) / 64), dim3(64), 0, c->stream, c->cells, c->ncells, rebuild);
+void set_prune(rcell_ctx* c) {
+  hipLaunchKernelGGL(k_set_prune, dim3((c->ncells + 63) / 64), dim3(64), 0, c->stream, c->cells, c->ncells);
 }
 
 void destroy_all(rcell_ctx* c) {
@@ -619,7 +626,7 @@ int deformation_common(rcell_ctx* c, const double* F_dev) {
     if (grow && (e = layout_bins(c, std::vector<int>(h.nbins, h.nbins + nc)))) return e;
     const int cap = list_capacity(dens, rcs);
     const int relist = cap > c->maxnb;             // a reallocated list must be rebuilt everywhere
-    if ((e = ensure_list_capacity(c, cap))) return e;
+    if ((e = ensure_list_capacity(c, cap, false))) return e;
     ensure_pruned(c);
     commit_deformation(c, relist, 1);
   }
@@ -775,7 +782,7 @@ int rcell_create(const rcell_params* params, const rcell_cell_init* cells, int32
     return bail(fail(c, RCELL_ERR_DEVICE, "hipEventCreate failed"));
   c->fx = f0; c->fy = f1; c->fz = f2;
   c->s[0] = s0; c->s[1] = s1; c->bond = bondp;
-  if ((e = ensure_list_capacity(c, list_capacity(dens, rcs)))) return bail(e);
+  if ((e = ensure_list_capacity(c, list_capacity(dens, rcs), false))) return bail(e);
 
   // ---- marshal the initial state (AoS -> SoA), bonds -> per-atom partner slots
   std::vector<double> hx(N), hy(N), hz(N), hvx(N, 0.0), hvy(N, 0.0), hvz(N, 0.0);
@@ -1065,10 +1072,12 @@ int rcell_set_state(rcell_ctx* c, int32_t cell, const double* x, const double* v
   int e;
   if (need[cell] > c->bin_cap[cell] && (e = layout_bins(c, need))) return e;
   const int cap0 = c->maxnb;
-  if ((e = ensure_list_capacity(c, list_capacity(n / (H[0] * H[4] * H[8]), rcs)))) return e;
-  if (c->maxnb != cap0) {          // the list has moved: the other cells build theirs again too
+  if ((e = ensure_list_capacity(c, list_capacity(n / (H[0] * H[4] * H[8]), rcs), true))) return e;
+  if (c->maxnb != cap0) {
+    // The other cells keep their lists, their order and their forces: a build would reorder their atoms, but
+    // not their stored forces, and only a restored cell has those recomputed.
     ensure_pruned(c);
-    set_prune(c, 1);
+    set_prune(c);
   }
   std::vector<double> buf(6 * n);
   for (long long i = 0; i < n; ++i)
@@ -1153,7 +1162,7 @@ int rcell_set_lanes(rcell_ctx* c, int32_t lanes) {
   drop_graphs(c);
   if (lanes == 1 || lanes == 2 || lanes == 4 || lanes == 8 || lanes == 16) {
     c->lanes = lanes;
-    set_prune(c, 0);               // the pruned list is kept per lane
+    set_prune(c);               // the pruned list is kept per lane
     return RCELL_OK;
   }
   if (lanes != 0) return fail(c, RCELL_ERR_ARG, "lanes must be 0, 1, 2, 4, 8 or 16");
@@ -1200,7 +1209,7 @@ int rcell_set_lanes(rcell_ctx* c, int32_t lanes) {
   if (t0) (void)hipEventDestroy(t0);
   if (t1) (void)hipEventDestroy(t1);
   (void)hipFree(tmp);
-  set_prune(c, 0);
+  set_prune(c);
   if (e != hipSuccess) return fail(c, RCELL_ERR_DEVICE, std::string("autotune: ") + hipGetErrorString(e));
   int best = 0;
   for (int v = 1; v < NV; ++v)
