@@ -90,9 +90,10 @@ typedef struct rcell_ctx rcell_ctx;
  * Cartesian components (the fourth normal is unused); the cell's mean velocity is removed and the
  * velocities are scaled so that mvv2e sum m v.v = (3 N - 3) kB T exactly.  Beside the neighbour
  * list a second, pruned list of its size plus 32 bytes per atom is kept for the steps between rebuilds;
- * without the memory for it the cells run on the full list, with the same results.  On failure *out is NULL
- * and everything the call allocated is freed.  For tests of that path, the environment variable
- * RCELL_FAULT_ALLOC = k (k >= 1) makes the k-th device allocation of the call fail as if the device
+ * without the memory for it the cells run on the full list, with the same results, and it is given up
+ * when a later call would otherwise be refused for want of memory.  On failure *out is NULL
+ * and everything the call allocated is freed.  For tests of these paths, the environment variable
+ * RCELL_FAULT_ALLOC = k (k >= 1) makes the k-th device allocation of the context fail as if the device
  * were out of memory (RCELL_ERR_OOM). */
 int rcell_create(const rcell_params* params, const rcell_cell_init* cells, int32_t ncells,
                  void* hip_stream, rcell_ctx** out);

@@ -151,29 +151,44 @@ int fail(rcell_ctx* c, int code, const std::string& msg) {
       return fail((ctx), RCELL_ERR_DEVICE, std::string(#call) + ": " + hipGetErrorString(e_)); \
   } while (0)
 
-template <class T>
-int dalloc(rcell_ctx* c, T** out, size_t count, bool host = false) {   // host: pinned memory
-  void* p = nullptr;
-  const size_t bytes = std::max<size_t>(count, 1) * sizeof(T);
-  if (c && c->fault_alloc > 0 && ++c->n_alloc == c->fault_alloc)
-    return fail(c, RCELL_ERR_OOM, "injected failure of device allocation " + std::to_string(c->n_alloc) +
-                                      " (" + std::to_string(bytes) + " bytes)");
-  const hipError_t r = host ? hipHostMalloc(&p, bytes) : hipMalloc(&p, bytes);
-  if (r != hipSuccess) {
-    (void)hipGetLastError();
-    return fail(c, r == hipErrorOutOfMemory || r == hipErrorMemoryAllocation ? RCELL_ERR_OOM : RCELL_ERR_DEVICE,
-                "device allocation of " + std::to_string(bytes) + " bytes failed: " + hipGetErrorString(r));
-  }
-  (host ? c->host_allocs : c->allocs).push_back(p);
-  *out = (T*)p;
-  return RCELL_OK;
-}
-
 void dfree(rcell_ctx* c, void* p) {
   if (!p) return;
   auto it = std::find(c->allocs.begin(), c->allocs.end(), p);
   if (it != c->allocs.end()) c->allocs.erase(it);
   (void)hipFree(p);
+}
+
+// the pruned list given up; the captured graphs carry its address
+void release_pruned(rcell_ctx* c) {
+  drop_graphs(c);
+  dfree(c, c->pl); dfree(c, c->pn);
+  c->pl = nullptr; c->pn = nullptr;
+}
+
+// The cells can do without the pruned list: it gives way to whatever else does not fit beside it.
+template <class T>
+int dalloc(rcell_ctx* c, T** out, size_t count, bool host = false) {   // host: pinned memory
+  void* p = nullptr;
+  const size_t bytes = std::max<size_t>(count, 1) * sizeof(T);
+  for (;;) {
+    const bool injected = c->fault_alloc > 0 && ++c->n_alloc == c->fault_alloc;
+    const hipError_t r = injected ? hipErrorOutOfMemory : host ? hipHostMalloc(&p, bytes) : hipMalloc(&p, bytes);
+    if (r == hipSuccess) break;
+    (void)hipGetLastError();
+    const bool oom = r == hipErrorOutOfMemory || r == hipErrorMemoryAllocation;
+    if (oom && !host && c->pl) {
+      release_pruned(c);
+      continue;
+    }
+    if (injected)
+      return fail(c, RCELL_ERR_OOM, "injected failure of device allocation " + std::to_string(c->n_alloc) +
+                                        " (" + std::to_string(bytes) + " bytes)");
+    return fail(c, oom ? RCELL_ERR_OOM : RCELL_ERR_DEVICE,
+                "device allocation of " + std::to_string(bytes) + " bytes failed: " + hipGetErrorString(r));
+  }
+  (host ? c->host_allocs : c->allocs).push_back(p);
+  *out = (T*)p;
+  return RCELL_OK;
 }
 
 double width_min(const double H[9]) {   // host-side validation of a box against rc + skin
@@ -545,8 +560,7 @@ double prune_reach(const rcell_params& p) {
 // beyond its 16-bit lengths) the passes walk the full list
 void ensure_pruned(rcell_ctx* c) {
   if (c->prune_skin <= 0.0 || c->prune_cap == c->maxnb) return;
-  drop_graphs(c);
-  dfree(c, c->pl); dfree(c, c->pn);
+  release_pruned(c);
   char* q = nullptr;
   unsigned short* n = nullptr;
   const std::string err = c->err;
@@ -565,6 +579,15 @@ void ensure_pruned(rcell_ctx* c) {
 
 void set_prune(rcell_ctx* c) {
   hipLaunchKernelGGL(k_set_prune, dim3((c->ncells + 63) / 64), dim3(64), 0, c->stream, c->cells, c->ncells);
+}
+
+// scratch memory of one call freed, and the pruned list back if it had to give way to it
+void free_scratch(rcell_ctx* c, void* p) {
+  dfree(c, p);
+  if (c->pl || c->prune_skin <= 0.0) return;
+  c->prune_cap = 0;
+  ensure_pruned(c);
+  set_prune(c);
 }
 
 void destroy_all(rcell_ctx* c) {
@@ -1173,10 +1196,7 @@ int rcell_set_lanes(rcell_ctx* c, int32_t lanes) {
   // writes are rewritten before they are next read.
   const size_t nb = sizeof(double) * (size_t)c->N;
   char* tmp = nullptr;
-  if (hipMalloc(&tmp, 9 * nb) != hipSuccess) {
-    (void)hipGetLastError();
-    return fail(c, RCELL_ERR_OOM, "autotune scratch of " + std::to_string(9 * nb) + " bytes");
-  }
+  if (const int st = dalloc(c, &tmp, 9 * nb)) return st;
   MDArgs a = make_args(c);
   double* d[9];
   for (int k = 0; k < 9; ++k) d[k] = (double*)(tmp + k * nb);
@@ -1208,7 +1228,7 @@ int rcell_set_lanes(rcell_ctx* c, int32_t lanes) {
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (t0) (void)hipEventDestroy(t0);
   if (t1) (void)hipEventDestroy(t1);
-  (void)hipFree(tmp);
+  free_scratch(c, tmp);
   set_prune(c);
   if (e != hipSuccess) return fail(c, RCELL_ERR_DEVICE, std::string("autotune: ") + hipGetErrorString(e));
   int best = 0;
@@ -1268,10 +1288,7 @@ int rcell_autotune(rcell_ctx* c, int32_t use_cache, int32_t* lanes, int32_t* bin
   size_t total = 0;
   for (const Piece& pc : pieces) total += (pc.bytes + 255) / 256 * 256;
   char* keep = nullptr;
-  if (hipMalloc(&keep, total) != hipSuccess) {
-    (void)hipGetLastError();
-    return fail(c, RCELL_ERR_OOM, "autotune snapshot of " + std::to_string(total) + " bytes");
-  }
+  if ((e = dalloc(c, &keep, total))) return e;
   auto copy = [&](bool save) {
     size_t o = 0;
     for (const Piece& pc : pieces) {
@@ -1314,7 +1331,7 @@ int rcell_autotune(rcell_ctx* c, int32_t use_cache, int32_t* lanes, int32_t* bin
   if (he == hipSuccess) he = hipStreamSynchronize(c->stream);
   if (t0) (void)hipEventDestroy(t0);
   if (t1) (void)hipEventDestroy(t1);
-  (void)hipFree(keep);
+  free_scratch(c, keep);
   if (he != hipSuccess) return fail(c, RCELL_ERR_DEVICE, std::string("autotune: ") + hipGetErrorString(he));
   if (e) return e;
   if ((e = push_bin_layout(c)) || (e = apply_bin_factor(c, best))) return e;
