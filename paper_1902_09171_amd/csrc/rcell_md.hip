@@ -503,12 +503,16 @@ int layout_bins(rcell_ctx* c, const std::vector<int>& need) {
   }
   if (total > (1ll << 31) - 1) return fail(c, RCELL_ERR_OOM, "too many neighbour bins");
   if (total > c->bins_alloc) {
-    dfree(c, c->bcount); dfree(c, c->bstart); dfree(c, c->bnum); dfree(c, c->bfill);
-    c->bcount = c->bstart = c->bnum = c->bfill = nullptr;
-    int st;
-    if ((st = dalloc(c, &c->bcount, total)) || (st = dalloc(c, &c->bstart, total)) ||
-        (st = dalloc(c, &c->bnum, total)) || (st = dalloc(c, &c->bfill, total)))
+    // allocated before the old ones are freed: on failure the context keeps its bins and runs on
+    int* q[4] = {nullptr, nullptr, nullptr, nullptr};
+    int st = RCELL_OK;
+    for (int k = 0; k < 4 && !st; ++k) st = dalloc(c, &q[k], total);
+    if (st) {
+      for (int* p : q) dfree(c, p);
       return st;
+    }
+    dfree(c, c->bcount); dfree(c, c->bstart); dfree(c, c->bnum); dfree(c, c->bfill);
+    c->bcount = q[0]; c->bstart = q[1]; c->bnum = q[2]; c->bfill = q[3];
     HIPCHK(c, hipMemsetAsync(c->bcount, 0, sizeof(int) * total, c->stream));
     c->bins_alloc = total;
   }
