@@ -70,7 +70,9 @@ struct CellDev {
   long long wcount, step, nrebuild;
   int off, n, tile_off, ntile;
   int nb[3], bin_off, bin_cap;
-  int rebuild, pending, status, pad;
+  int rebuild, pending, status;
+  int span;                       // list build: bins that a wave takes together, at most
+  float span_rate;                // and as many of them per tile that is built
   double Hb[6];                   // H at the last neighbour build, upper triangle (0 1 2 4 5 8)
   float hs2;                      // squared (measured) displacement that still keeps the list complete
   float dmax2;                    // largest squared measured displacement since the last build, as last reduced
@@ -1651,12 +1653,28 @@ __device__ __forceinline__ int block_exscan(int v, int* wsum, int* total) {
   return before + inc - v;
 }
 
-// Bounds on |d|^2 for the list build's FP32 test (build_bin).  A candidate's or an atom's offset from
-// the bin's first atom is at most pm in each component (three bins in every dimension) and is rounded
+// The bins along z whose lists a wave builds together (build_span): as many as have their candidates, those of
+// span + 2 f bins in each column of the stencil, in one register tile, and fewer than half the box.
+constexpr float SPAN_CAND = 165.f;  // of 64 BLD_ROUNDS: a span has a few more than the average now and then
+// A span leaves the waves enough to do: as many bins as the set has bins per SPAN_TILES atoms' worth of tiles,
+// four times as many of half bins.  Longer spans make short work too serial (16 cells of 4000 beads, skin 0.55,
+// 1008 tiles: 24 us bin by bin, 34 in spans of two), shorter ones cost rounds (4 such cells in half bins, skin
+// 0.4, 252 tiles: 13.7 us, 20 in spans of a quarter of the length).
+constexpr float SPAN_TILES = 256.f;
+__device__ __forceinline__ void list_span(const MDArgs& a, CellDev& C) {
+  const int f = a.bin_factor;
+  const float per_atom = (float)(C.nb[0] * C.nb[1] * C.nb[2]) * __builtin_amdgcn_rcpf((float)C.n);
+  const int fit = (int)fminf((f == 1 ? SPAN_CAND / 9.f : SPAN_CAND / 25.f) * per_atom, 1024.f) - 2 * f;
+  C.span = min(C.nb[0], C.nb[1]) < 2 * f + 3 ? 1 : max(1, min(fit, (C.nb[2] - 1) / 2 - f));
+  C.span_rate = (float)(f * f) / SPAN_TILES * per_atom;
+}
+
+// Bounds on |d|^2 for the list build's FP32 test (build_span).  A candidate's or an atom's offset from
+// the span's first atom is at most pm in each component (three bins in x and y, f + span in z) and is rounded
 // once, their difference once more, so a component of d is off by at most 3 2^-24 pm and |d|^2 by at most
 // 2 sqrt(3) (rc + skin) times that, plus its own rounding; doubled.
 __device__ __forceinline__ void list_band(const MDArgs& a, CellDev& C) {
-  const double b0 = 3.0 / C.nb[0], b1 = 3.0 / C.nb[1], b2 = 3.0 / C.nb[2];
+  const double b0 = 3.0 / C.nb[0], b1 = 3.0 / C.nb[1], b2 = (double)(a.bin_factor + C.span) / C.nb[2];
   const double px = fabs(C.H[0]) * b0 + fabs(C.H[1]) * b1 + fabs(C.H[2]) * b2;
   const double py = fabs(C.H[4]) * b1 + fabs(C.H[5]) * b2, pm = fmax(px, fmax(py, fabs(C.H[8]) * b2));
   const double band = 0x1.0p-23 * (10.4 * sqrt(a.rcs2) * pm + 4.0 * a.rcs2);
@@ -1670,6 +1688,7 @@ __device__ __forceinline__ void begin_build(const MDArgs& a, CellDev& C) {
   for (int q = 0; q < 6; ++q) C.Hb[q] = C.H[up[q]];
   C.hs2 = measured_threshold(a.half_skin2, C.qeps);
   C.dmax2 = 0.f;
+  list_span(a, C);
   list_band(a, C);
 }
 
@@ -1987,14 +2006,22 @@ __global__ __launch_bounds__(TILE) void k_reset_order(MDArgs a, int first, int c
 // broadcast against them.  The 64-bit mask of a comparison is the accepted candidates in order: an
 // accepted lane's place is the running count plus the accepted lanes below it.  No lane waits for a
 // longer range of its neighbours', and a cell of 10^4 beads gives ~2200 waves instead of 157.
+//
+// A wave's cost is per round of 64 candidates and per bin, so bins with few atoms (half bins, short skins) are
+// taken several at a time (list_span): `span` bins consecutive in z share the columns of their stencils, which
+// are span + 2 f bins long together.  An atom meets candidates beyond its own f bins too, which the distance
+// test turns down, and its own in the same order: the lists are the same.  Bin by bin such sets took longer than
+// one lane per atom walking its candidates.  16 of 128 cells of 40 000 beads, us, one lane per atom / bin by bin / spans:
+// skin 0.4 164 / 193 / 157, 0.55 189 / 177 / 161, 0.4 with half bins 195 / 608 / 202; all 128 of the last
+// 2002 / 5320 / 1765.  At skin 0.7 (5.8 beads per bin) a bin fills the register tile: 221 / 178 / 178.  The bar of
+// 256 cells of 40 000 beads with some 19 of them rebuilding in every step: 226 / 273 / 220 per step.
 constexpr int MAX_BIN_FACTOR = 2;
-struct BuildGeo {                  // a bin's stencil: bins per dimension and the z ranges
+struct BuildGeo {                  // the stencil of a span of bins: bins per dimension and the z ranges
   int lo[3], cnt[3], nb[3];        // first neighbour bin (unwrapped) and count per dimension
   int zr[2][2], nzr;               // z bins [z0, z1] of every column, or two such ranges
   int ncol, nrange;
 };
-__device__ __forceinline__ void build_geo(const CellDev& C, int pk, int fb, BuildGeo& G) {
-  const int bb[3] = {pk & BIN_MASK, (pk >> BIN_BITS) & BIN_MASK, pk >> (2 * BIN_BITS)};
+__device__ __forceinline__ void build_geo(const CellDev& C, const int bb[3], int z1, int fb, BuildGeo& G) {
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
     G.nb[q] = C.nb[q];
@@ -2006,7 +2033,7 @@ __device__ __forceinline__ void build_geo(const CellDev& C, int pk, int fb, Buil
   const int nbz = G.nb[2];
   G.zr[0][0] = 0; G.zr[0][1] = nbz - 1; G.zr[1][0] = 0; G.zr[1][1] = 0; G.nzr = 1;
   if (nbz >= 2 * fb + 1) {
-    const int lo = bb[2] - fb, hi = bb[2] + fb;
+    const int lo = bb[2] - fb, hi = z1 + fb;
     if (lo < 0) { G.zr[0][0] = 0; G.zr[0][1] = hi; G.zr[1][0] = lo + nbz; G.zr[1][1] = nbz - 1; G.nzr = 2; }
     else if (hi >= nbz) { G.zr[0][0] = lo; G.zr[0][1] = nbz - 1; G.zr[1][0] = 0; G.zr[1][1] = hi - nbz; G.nzr = 2; }
     else { G.zr[0][0] = lo; G.zr[0][1] = hi; }
@@ -2054,40 +2081,42 @@ __device__ __forceinline__ int2 build_range(const MDArgs& a, const CellDev& C, c
 
 constexpr int BLD_WAVES = 4;       // waves per block of the list build
 constexpr int BLD_ROUNDS = 3;      // rounds of 64 candidates held in registers
-constexpr int BLD_RUN_TILES = 1024;  // rebuild sets of at least so many tiles: runs of bins per wave
-struct BinRanges {                 // one bin's candidate ranges, by lane
+constexpr int BLD_RUN_TILES = 1024;  // rebuild sets of at least so many tiles: runs of spans per wave
+struct BinRanges {                 // one span's candidate ranges, by lane
   int off[64];                     // first candidate of each range (past the last range: INT_MAX)
   int delta[64];                   // position of candidate c of range r: c + delta[r]
 };
-struct BinHead {                   // a bin's atoms and stencil, and this lane's range of it
+struct BinHead {                   // a span's atoms and stencil, and this lane's range of it
   int m, first, nrange;
   int2 rng;
 };
 
-// bin (x, y, z) of cell C: its atoms, and the candidate range of every lane below nrange
-__device__ __forceinline__ BinHead bin_head(const MDArgs& a, const CellDev& C, int x, int y, int z) {
-  const int lane = (int)(threadIdx.x & 63u), bin = C.bin_off + (x * C.nb[1] + y) * C.nb[2] + z;
+// bins (x, y, z0) to (x, y, z1) of cell C: their atoms, and the candidate range of every lane below nrange
+__device__ __forceinline__ BinHead bin_head(const MDArgs& a, const CellDev& C, int x, int y, int z0, int z1) {
+  const int lane = (int)(threadIdx.x & 63u), col = C.bin_off + (x * C.nb[1] + y) * C.nb[2];
   BinHead h;
-  h.m = a.bnum[bin];
-  h.first = a.bstart[bin];
+  h.first = a.bstart[col + z0];
+  const bool last = x + 1 == C.nb[0] && y + 1 == C.nb[1] && z1 + 1 == C.nb[2];
+  h.m = (last ? C.n : a.bstart[col + z1 + 1]) - h.first;
   BuildGeo G;
-  build_geo(C, x | (y << BIN_BITS) | (z << (2 * BIN_BITS)), a.bin_factor, G);
+  const int bb[3] = {x, y, z0};
+  build_geo(C, bb, z1, a.bin_factor, G);
   h.nrange = G.nrange;
   h.rng = lane < G.nrange ? build_range(a, C, G, lane) : make_int2(0, 0);
   return h;
 }
 
-// The lists of the atoms of one bin: the wave's share of them, atoms part, part + nparts, ... .
+// The lists of the atoms of one span: the wave's share of them, atoms part, part + nparts, ... .
 // s: the reordered coordinates of the batch.
 //
-// LOCAL (every dimension has at least 2 f + 3 bins): a candidate (within f bins) lies less than half the
-// box from the bin's first atom, as every atom of the bin does, so the difference of the two offsets
-// is the minimum image: the test takes 3 subtractions and 3 multiply-adds in FP32 (issued at nearly
+// LOCAL (at least 2 f + 3 bins in x and y, 2 (f + span) + 1 in z): a candidate (within f bins of the span) lies
+// less than half the box from the span's first atom, as every atom of the span does, so the difference of the
+// two offsets is the minimum image: the test takes 3 subtractions and 3 multiply-adds in FP32 (issued at nearly
 // twice the rate of FP64 and conversions here) on offsets rounded once from FP64.  A candidate whose
 // |d|^2 lies between the cell's list_lo2 and list_hi2 takes the exact test, so the lists are those of the exact
 // test alone.  With fewer bins every test is the exact one.
 template <class P, class LT, bool LOCAL>
-__device__ __forceinline__ void build_bin(const MDArgs& a, int cell, const BinHead& h, int part, int nparts,
+__device__ __forceinline__ void build_span(const MDArgs& a, int cell, const BinHead& h, int part, int nparts,
                                           const typename P::S* s, BinRanges& rg) {
   using R = typename P::R;
   const CellDev& C = a.cells[cell];
@@ -2100,7 +2129,7 @@ __device__ __forceinline__ void build_bin(const MDArgs& a, int cell, const BinHe
   __builtin_amdgcn_wave_barrier();                // the last bin's ranges have been read
   rg.off[lane] = lane < h.nrange ? off : 0x7fffffff;
   rg.delta[lane] = h.rng.x - off;
-  // candidate index of the bin's first atom: its range is the one that holds its position
+  // candidate index of the span's first atom: its range is the one that holds its position
   const unsigned long long own = __builtin_amdgcn_ballot_w64((unsigned)(first - h.rng.x) < (unsigned)h.rng.y);
   const int self0 = first - __builtin_amdgcn_readlane(h.rng.x - off, __builtin_ctzll(own));
   __builtin_amdgcn_wave_barrier();
@@ -2111,7 +2140,7 @@ __device__ __forceinline__ void build_bin(const MDArgs& a, int cell, const BinHe
   const unsigned row = (unsigned)a.npad << a.lblk, bm = (1u << a.lblk) - 1u;   // list_index, by rows of blocks
   const int cap = a.maxnb;
   const typename P::S sref = sc[first];
-  for (int g0 = 0; g0 < m; g0 += 64) {            // the bin's atoms, by lane (one group unless m > 64)
+  for (int g0 = 0; g0 < m; g0 += 64) {            // the span's atoms, by lane (one group unless m > 64)
     const int ng = min(64, m - g0);
     const typename P::S so = sc[first + g0 + min(lane, ng - 1)];
     R po[3] = {0, 0, 0};
@@ -2190,29 +2219,30 @@ __device__ __forceinline__ void build_bin(const MDArgs& a, int cell, const BinHe
   }
 }
 
-// `run` consecutive bins of one cell from its bin b0, the next bin's ranges requested before a bin's
-// candidates are tested
+// `run` consecutive spans of one cell from its span b0, of `len` bins each but the last of a column, the next
+// span's ranges requested before a span's candidates are tested
 template <class P, class LT>
-__device__ __forceinline__ void build_run(const MDArgs& a, int cell, int b0, int run, int part, int nparts,
+__device__ __forceinline__ void build_run(const MDArgs& a, int cell, int b0, int run, int len, int ns, int part, int nparts,
                                           const typename P::S* s, BinRanges& rg) {
   const CellDev& C = a.cells[cell];
   const int nb0 = C.nb[0], nb1 = C.nb[1], nb2 = C.nb[2];
   const bool local = min(min(nb0, nb1), nb2) >= 2 * a.bin_factor + 3;
-  int z = b0 % nb2, t = b0 / nb2;
+  int z = b0 % ns * len, t = b0 / ns;
   int y = t % nb1, x = t / nb1;
-  BinHead cur = bin_head(a, C, x, y, z);
+  BinHead cur = bin_head(a, C, x, y, z, min(z + len, nb2) - 1);
   for (int e = 0; e < run; ++e) {
-    if (++z == nb2) { z = 0; if (++y == nb1) { y = 0; ++x; } }
+    z += len;
+    if (z >= nb2) { z = 0; if (++y == nb1) { y = 0; ++x; } }
     BinHead nxt = cur;
-    if (e + 1 < run) nxt = bin_head(a, C, x, y, z);
-    if (local) build_bin<P, LT, true>(a, cell, cur, part, nparts, s, rg);
-    else build_bin<P, LT, false>(a, cell, cur, part, nparts, s, rg);
+    if (e + 1 < run) nxt = bin_head(a, C, x, y, z, min(z + len, nb2) - 1);
+    if (local) build_span<P, LT, true>(a, cell, cur, part, nparts, s, rg);
+    else build_span<P, LT, false>(a, cell, cur, part, nparts, s, rg);
     cur = nxt;
   }
 }
 
 // The lists of the rebuilding cells, over the work list, block-strided (XcdLoop).  An item is a tile's
-// share of its cell's bins, split over `split` waves: a run of a few consecutive bins whose cell is
+// share of its cell's spans, split over 2^lsplit waves: a run of a few consecutive spans whose cell is
 // looked up once; where bins hold many atoms (copper: ~60), 2^lparts waves share each bin's atoms.
 // scatter: after the phase kernels the reorder's second half is done here too, tile by tile - nothing
 // else reads the arrays that it writes, and the candidates come from the scratch rows, which hold the
@@ -2221,9 +2251,6 @@ __device__ __forceinline__ void build_run(const MDArgs& a, int cell, int b0, int
 // Measured on one MI355X, per MD step, against one lane per atom (sets of 4096 tiles and more) and eight
 // lanes per atom walking the candidate ranges: 100 cells of 10^4 beads 62.6 -> 37.1 us, 50 glassy
 // cells 102 -> 54 us, 128 cells of 40 000 beads 205 -> 147 us (all 5.1 M beads at once 2.19 -> 1.57 ms).
-// Where a few of many large cells rebuild in every step (19 of 256 cells of 40 000 beads) a lane per atom was
-// faster: 226 us against 273 on the same card, ~5400 cycles of a SIMD per bin of 5.8 beads and ~157
-// candidates (three rounds, 82 % of their lanes in use).
 template <class P, class LT>
 __global__ __launch_bounds__(64 * BLD_WAVES) void k_build_list(MDArgs a, int scatter, int lparts) {
   __shared__ BinRanges rg[BLD_WAVES];
@@ -2234,7 +2261,7 @@ __global__ __launch_bounds__(64 * BLD_WAVES) void k_build_list(MDArgs a, int sca
   if (scatter)
     for_work_tiles(a, [&](const Tile& t, long long i) { reorder_scatter_atom<P>(a, a.cells[t.cell], i); });
   const typename P::S* s = scatter ? ro.s : (const typename P::S*)a.s_cur;
-  // a tile holds 10-14 bins at Kremer-Grest densities: single bins until every resident wave has two,
+  // a tile holds 10-14 bins at Kremer-Grest densities: single spans until every resident wave has two,
   // then runs of three or four (5.1 M beads at once: 1.95 ms by single bins, 1.62 ms by runs of four);
   // 3-4 of the glassy cells' fuller bins (two waves each), one of copper's
   const int lsplit = lparts > 1 ? 0 : lparts == 1 ? 2 : ntl < BLD_RUN_TILES ? 4 : 2;
@@ -2245,9 +2272,18 @@ __global__ __launch_bounds__(64 * BLD_WAVES) void k_build_list(MDArgs a, int sca
     const int cell = __builtin_amdgcn_readfirstlane(a.work_cells[w]);
     const int q = it - (__builtin_amdgcn_readfirstlane(a.work_tstart[w]) << lsplit);
     const CellDev& C = a.cells[cell];
-    const unsigned nbins = (unsigned)(C.nb[0] * C.nb[1] * C.nb[2]), nq = (unsigned)C.ntile << lsplit;
-    const int b0 = (int)((unsigned long long)q * nbins / nq), b1 = (int)((unsigned long long)(q + 1) * nbins / nq);
-    if (b1 > b0) build_run<P, LT>(a, cell, b0, b1 - b0, part, 1 << lparts, s, rg[wave]);
+    const int nb2 = C.nb[2], cols = C.nb[0] * C.nb[1];
+    int len = min(C.span, (int)((float)ntl * C.span_rate)), ns = nb2;
+    if (len > 1) {                 // about equal in a column
+      ns = (nb2 + len - 1) / len;
+      len = (nb2 + ns - 1) / ns;
+      ns = (nb2 + len - 1) / len;
+    } else {
+      len = 1;
+    }
+    const unsigned nu = (unsigned)(cols * ns), nq = (unsigned)C.ntile << lsplit;
+    const int b0 = (int)((unsigned long long)q * nu / nq), b1 = (int)((unsigned long long)(q + 1) * nu / nq);
+    if (b1 > b0) build_run<P, LT>(a, cell, b0, b1 - b0, len, ns, part, 1 << lparts, s, rg[wave]);
   }
 }
 
