@@ -120,6 +120,15 @@ bool fused_shape(const rsur_ctx* c) {
   return *std::max_element(c->dp.begin(), c->dp.end()) <= FW && c->L <= MAXL;
 }
 
+FragMap frag_map(const rsur_ctx* c) {
+  FragMap m{};
+  if (!fused_shape(c)) return m;
+  m.L = c->L;
+  for (int l = 0; l <= c->L; ++l) m.dp[l] = c->dp[l];
+  for (int l = 0; l < c->L; ++l) m.woff[l] = c->woff[l];
+  return m;
+}
+
 // The gradient reductions over the batch (weight gradients, bias column sums) are split into S
 // ranges of at least 256 rows (S a power of two up to MAX_SPLIT dividing Mp / 64) so that enough
 // blocks work at once; S partial results are then added in order (deterministic).
@@ -303,14 +312,8 @@ int rsur_set_params(rsur_ctx* c, int32_t member, const float* w) {
   RCHK(c, hipMemcpyAsync(c->p + off, h.data(), sizeof(float) * c->P, hipMemcpyHostToDevice, c->stream));
   RCHK(c, hipMemsetAsync(c->m1 + off, 0, sizeof(float) * c->P, c->stream));
   RCHK(c, hipMemsetAsync(c->m2 + off, 0, sizeof(float) * c->P, c->stream));
-  hipLaunchKernelGGL(k_to_bf16, dim3((unsigned)((c->P + 255) / 256)), dim3(256), 0, c->stream, c->p + off,
-                     c->pb + off, c->P);
-  if (fused_shape(c))
-    for (int l = 0; l < c->L; ++l) {
-      const int n = c->dp[l] / 8 * c->dp[l + 1];
-      hipLaunchKernelGGL(k_frag_w, dim3((n + 255) / 256), dim3(256), 0, c->stream, c->pb + off + c->woff[l],
-                         c->pbf + off + c->woff[l], c->pbt + off + c->woff[l], c->dp[l], c->dp[l + 1]);
-    }
+  hipLaunchKernelGGL(k_to_bf16, dim3((unsigned)((c->P + 255) / 256)), dim3(256), 0, c->stream, (const float*)c->p, c->pb,
+                     c->pbf, c->pbt, frag_map(c), c->P, off);
   RCHK(c, hipStreamSynchronize(c->stream));
   c->t[member] = 0;
   return RCELL_OK;
@@ -508,12 +511,7 @@ int rsur_train_step(rsur_ctx* c, const void* X_dev, const void* Y_dev, int32_t B
     hipLaunchKernelGGL(k_loss_total, dim3(c->K), dim3(64), 0, c->stream, c->lpart, chunks,
                        1.0f / ((float)B * (float)c->dout), c->loss);
   // Adam with per-member bias corrections
-  FragMap map{};
-  if (fused_shape(c)) {
-    map.L = L;
-    for (int l = 0; l <= L; ++l) map.dp[l] = c->dp[l];
-    for (int l = 0; l < L; ++l) map.woff[l] = c->woff[l];
-  }
+  const FragMap map = frag_map(c);
   for (int k0 = 0; k0 < c->K; k0 += ADAM_MEM) {
     AdamBias bias{};
     const int nk = std::min(ADAM_MEM, c->K - k0);

@@ -187,7 +187,7 @@ __global__ __launch_bounds__(256) void k_dw(DwArgs d) {
 // activation, where the row-major product took four 2-byte ones.  Over k in steps of 16 from zero, the
 // order of k_gemm, so the outputs equal the layer-wise forward bit for bit.
 //
-// The weights come from a copy laid out by fragments (k_frag_w): the 64 lanes of a wave read one
+// The weights come from a copy laid out by fragments (frag_index): the 64 lanes of a wave read one
 // operand as 1 KB of consecutive memory (a transposed copy gave 32 pieces of 32 bytes).  They are read
 // once per block, so the large variant takes 128 rows per block (64 before); the small one spreads 32
 // rows over 8 waves and requests a layer's whole operand at once, since a small batch waits for latency.
@@ -550,18 +550,23 @@ __global__ __launch_bounds__(64 * NW, 2) void k_mlp_train(MlpArgs g, TrainArgs h
   mlp_block<RT, NW, true>(g, h, act);
 }
 
-// the fragment copies of one layer's BF16 weights; one thread per 8 consecutive k, and per 8 consecutive n
-// of the transposed copy
-__global__ void k_frag_w(const bf16* pb, bf16* pbf, bf16* pbt, int Kd, int Nd) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= (Kd >> 3) * Nd) return;
-  const int n = e % Nd, k = 8 * (e / Nd);
-  v8bf v;
-#pragma unroll
-  for (int q = 0; q < 8; ++q) v[q] = pb[(long long)(k + q) * Nd + n];
-  *(v8bf*)(pbf + frag_index(k, n, Kd)) = v;
-  const int k1 = e % Kd, n1 = 8 * (e / Kd);
-  *(v8bf*)(pbt + frag_index(n1, k1, Nd)) = *(const v8bf*)(pb + (long long)k1 * Nd + n1);
+struct FragMap { int L; int dp[MAXL + 1]; long long woff[MAXL]; };   // L = 0: no fragment copy
+// parameter o of the member at `base` in BF16, and a weight into its copies by fragments
+__device__ __forceinline__ void store_bf16(bf16* pb, bf16* pbf, bf16* pbt, const FragMap& map, long long base, long long o, float w) {
+  pb[base + o] = (bf16)w;
+  for (int l = 0; l < map.L; ++l) {
+    const long long r = o - map.woff[l];
+    if (r < 0 || r >= (long long)map.dp[l] * map.dp[l + 1]) continue;
+    const int k = (int)r / map.dp[l + 1], n = (int)r - k * map.dp[l + 1];
+    pbf[base + map.woff[l] + frag_index(k, n, map.dp[l])] = (bf16)w;
+    pbt[base + map.woff[l] + frag_index(n, k, map.dp[l + 1])] = (bf16)w;
+  }
+}
+// every parameter of the member at `base`, in one launch: rsur_set_params of 153 -> 4 x 256 -> 6 takes 176 us, 199 with a
+// launch more per layer for the copies
+__global__ void k_to_bf16(const float* p, bf16* pb, bf16* pbf, bf16* pbt, FragMap map, long long P, long long base) {
+  const long long o = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (o < P) store_bf16(pb, pbf, pbt, map, base, o, p[base + o]);
 }
 
 // raw inputs (B x din, FP32) -> normalised BF16 rows of width dp0, zero padding
@@ -627,7 +632,6 @@ __global__ __launch_bounds__(64) void k_loss_total(const float* part, int chunks
 // out, 19.7 us (9 us before, and 10 launches of 4.8 that added the ranges up into a buffer of their own).
 constexpr int ADAM_MEM = 16;
 struct AdamBias { float c1[ADAM_MEM], c2[ADAM_MEM]; };   // bias corrections of members mem0 .. of this launch
-struct FragMap { int L; int dp[MAXL + 1]; long long woff[MAXL]; };   // L = 0: no fragment copy
 __global__ void k_adam(float* p, float* gr, const float* part, int S, long long sRange, float* m1, float* m2, bf16* pb,
                        bf16* pbf, bf16* pbt, FragMap map, long long P, int mem0, AdamBias bias, float lr, float b1, float b2,
                        float eps) {
@@ -650,20 +654,7 @@ __global__ void k_adam(float* p, float* gr, const float* part, int S, long long 
   const float mh = a / bias.c1[q], vh = b / bias.c2[q];
   const float w = p[e] - lr * mh / (sqrtf(vh) + eps);
   p[e] = w;
-  pb[e] = (bf16)w;
-  for (int l = 0; l < map.L; ++l) {
-    const long long r = o - map.woff[l];
-    if (r < 0 || r >= (long long)map.dp[l] * map.dp[l + 1]) continue;
-    const int k = (int)r / map.dp[l + 1], n = (int)r - k * map.dp[l + 1];
-    const long long base = (long long)(mem0 + q) * P + map.woff[l];
-    pbf[base + frag_index(k, n, map.dp[l])] = (bf16)w;
-    pbt[base + frag_index(n, k, map.dp[l + 1])] = (bf16)w;
-  }
-}
-
-__global__ void k_to_bf16(const float* p, bf16* pb, long long n) {
-  const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < n) pb[e] = (bf16)p[e];
+  store_bf16(pb, pbf, pbt, map, (long long)(mem0 + q) * P, o, w);
 }
 
 // ensemble mean and population variance of the de-normalised outputs (and per-member outputs)
