@@ -28,9 +28,13 @@ typedef struct rsur_ctx rsur_ctx;
 
 /* Allocate a K-member ensemble for batches of up to max_batch rows on the current device.
  * Parameters start at zero: load them with rsur_set_params.  Normalisation starts as identity.
- * All device memory is allocated here (parameters, Adam moments, activations for max_batch rows,
- * and the partial sums of the training step's split reductions: up to 8 x K x the member's
- * parameters in FP32, at most 256 MiB); the forward and training calls allocate nothing. */
+ * All device memory is allocated here; the forward and training calls allocate nothing.  It is, in bytes, with
+ * every width padded to a multiple of 64: per row of max_batch 2 x the input width, and per member 2 x the
+ * hidden widths (activations) and 4 x the hidden and output widths (pre-activations and outputs), and, for
+ * networks with a padded width above 256 or more than 8 layers, 4 x the largest width (output gradients); per
+ * parameter and member 22 (parameters, gradients, Adam moments, BF16 weights in three layouts); and up to
+ * 8 x 4 per parameter and member, at most 256 MiB, for the partial sums of the training step's split
+ * reductions. */
 int rsur_create(int32_t din, int32_t width, int32_t depth, int32_t dout, int32_t ensemble,
                 int32_t max_batch, void* hip_stream, rsur_ctx** out);
 int rsur_destroy(rsur_ctx* ctx);

@@ -76,8 +76,8 @@ struct rsur_ctx {
   std::vector<bf16*> act;                    // act[l]: K x Mp x dp[l] (act[0] shared: Mp x dp[0])
   std::vector<float*> Z;                     // Z[l]: K x Mp x dp[l + 1], hidden layers
   float* out = nullptr;                      // K x Mp x dp[L]
-  std::vector<bf16*> dz;                     // fused pass: dz[l]: K x Mp x dp[l + 1], output gradients
-  bf16 *dza = nullptr, *dzb = nullptr;       // layer by layer: K x Mp x max(dp), two of them in turn
+  bf16 *dza = nullptr, *dzb = nullptr;       // output gradients layer by layer: K x Mp x max(dp), two in turn (the
+                                             // fused pass keeps them in Z and out)
   float *xmu = nullptr, *xsd = nullptr, *ymu = nullptr, *ysd = nullptr, *loss = nullptr;
   int max_split = 0;                         // most ranges of a split gradient reduction; 0: never split
   float* split = nullptr;                    // max_split x K x P: their partial sums
@@ -255,13 +255,9 @@ int rsur_create(int32_t din, int32_t width, int32_t depth, int32_t dout, int32_t
   for (int l = 0; l < c->L - 1; ++l)
     if ((e = ralloc(c, &c->Z[l], (size_t)c->K * c->Mp * c->dp[l + 1]))) return bail(e);
   const int dmax = *std::max_element(c->dp.begin(), c->dp.end());
-  if (fused_shape(c)) {
-    c->dz.resize(c->L);
-    for (int l = 0; l < c->L; ++l)
-      if ((e = ralloc(c, &c->dz[l], (size_t)c->K * c->Mp * c->dp[l + 1]))) return bail(e);
-  } else if ((e = ralloc(c, &c->dza, (size_t)c->K * c->Mp * dmax)) || (e = ralloc(c, &c->dzb, (size_t)c->K * c->Mp * dmax))) {
+  if (!fused_shape(c) &&
+      ((e = ralloc(c, &c->dza, (size_t)c->K * c->Mp * dmax)) || (e = ralloc(c, &c->dzb, (size_t)c->K * c->Mp * dmax))))
     return bail(e);
-  }
   if ((e = ralloc(c, &c->split, (size_t)c->max_split * KP))) return bail(e);
   if ((e = ralloc(c, &c->out, (size_t)c->K * c->Mp * c->dp[c->L])) ||
       (e = ralloc(c, &c->xmu, din)) || (e = ralloc(c, &c->xsd, din)) || (e = ralloc(c, &c->ymu, dout)) ||
@@ -390,8 +386,7 @@ static void forward_fused(rsur_ctx* c, const float* X, int B, float* out, long l
 static int train_pass(rsur_ctx* c, const float* X, const float* Y, int B, int Mp) {
   TrainArgs h{};
   h.Y = Y; h.ymu = c->ymu; h.ysd = c->ysd; h.wt = c->pbt;
-  for (int l = 0; l < c->L; ++l) { h.act[l] = c->act[l]; h.dz[l] = c->dz[l]; }
-  for (int l = 0; l < c->L - 1; ++l) h.Z[l] = c->Z[l];
+  for (int l = 0; l < c->L; ++l) { h.act[l] = c->act[l]; h.Z[l] = l < c->L - 1 ? c->Z[l] : c->out; }
   h.lpart = c->lpart; h.Mp = Mp; h.rows = c->Mp; h.inv = 1.0f / ((float)B * (float)c->dout);
   const MlpArgs g = mlp_args(c, X, B);
   // 32 rows per block while two of them per CU hold the whole batch, 64 (the weights read half as often)
@@ -404,11 +399,11 @@ static int train_pass(rsur_ctx* c, const float* X, const float* Y, int B, int Mp
   return (int)grid.x;
 }
 
-// the arguments of layer l's weight and bias gradients over Mp rows in S ranges
-static GemmArgs dw_args(const rsur_ctx* c, int l, const bf16* dz, long long sdz, int Mp, int S, float* grads) {
+// the arguments of layer l's weight and bias gradients over Mp rows in S ranges (dz: rows of lddz, members sdz apart)
+static GemmArgs dw_args(const rsur_ctx* c, int l, const bf16* dz, int lddz, long long sdz, int Mp, int S, float* grads) {
   GemmArgs w{};                                      // dW_l = act_l^T dZ_l
   w.A = c->act[l]; w.lda = c->dp[l]; w.sA = l == 0 ? 0 : (long long)c->Mp * c->dp[l];
-  w.B = dz; w.ldb = c->dp[l + 1]; w.sB = sdz;
+  w.B = dz; w.ldb = lddz; w.sB = sdz;
   w.M = c->dp[l]; w.N = c->dp[l + 1]; w.K = Mp;
   w.Z = grads + c->woff[l]; w.ldz = c->dp[l + 1]; w.sZ = c->P;
   w.nmem = c->K; w.ksplit = S; w.sRange = (long long)c->K * c->P;
@@ -480,7 +475,8 @@ int rsur_train_step(rsur_ctx* c, const void* X_dev, const void* Y_dev, int32_t B
     chunks = train_pass(c, (const float*)X_dev, (const float*)Y_dev, B, Mp);
     DwArgs d{};
     for (int l = 0; l < L; ++l) {
-      d.g[l] = dw_args(c, l, c->dz[l], (long long)c->Mp * c->dp[l + 1], Mp, S, grads);
+      const int ld = 2 * c->dp[l + 1];               // TrainArgs::Z
+      d.g[l] = dw_args(c, l, (const bf16*)(l < L - 1 ? c->Z[l] : c->out), ld, (long long)c->Mp * ld, Mp, S, grads);
       d.first[l + 1] = d.first[l] + d.g[l].M / TM * (d.g[l].N / TN);
     }
     hipLaunchKernelGGL(k_dw, dim3(d.first[L], c->K * S), dim3(256), 0, c->stream, d);
@@ -494,7 +490,7 @@ int rsur_train_step(rsur_ctx* c, const void* X_dev, const void* Y_dev, int32_t B
                        (const float*)Y_dev, B, c->dout, c->ymu, c->ysd, c->dza, sdz, c->lpart);
     bf16 *dz = c->dza, *dzn = c->dzb;
     for (int l = L - 1; l >= 0; --l) {
-      gemm<true, false, EPI_BWD_DW>(c, dw_args(c, l, dz, sdz, Mp, S, grads));
+      gemm<true, false, EPI_BWD_DW>(c, dw_args(c, l, dz, c->dp[l + 1], sdz, Mp, S, grads));
       if (l > 0) {                                   // dZ_{l-1} = (dZ_l W_l^T) * SiLU'(Z_{l-1})
         GemmArgs d{};
         d.A = dz; d.lda = c->dp[l + 1]; d.sA = sdz;

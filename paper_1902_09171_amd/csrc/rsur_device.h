@@ -237,24 +237,27 @@ __device__ __forceinline__ float silu_fast(float z) {
 struct TrainArgs {
   const float *Y, *ymu, *ysd;
   const bf16* wt;                            // BF16 transposed weights by fragments, member stride sW
-  bf16 *act[MAXL], *dz[MAXL];                // normalised input and activations; output gradients of the layers
-  float* Z[MAXL];                            // pre-activations in accumulator order
+  bf16* act[MAXL];                           // normalised input and activations
+  // Pre-activations in accumulator order, then (and for the output layer from the first) the layer's output
+  // gradient: 32 rows of either lie in the same bytes, a row of the gradient in the first half of its share, and
+  // a block has read its pre-activations before it writes there.
+  float* Z[MAXL];
   float* lpart;                              // [member][block] squared-error sums
   int Mp, rows;                              // padded rows of this batch; rows of a member in the buffers
   float inv;
 };
 
-// rows of a block's LDS buffer to / from memory, dp <= FW columns, two rows per wave at a time
+// rows of a block's LDS buffer to / from memory, dp <= FW columns, rows of ld in memory, two rows per wave at a time
 template <int ROWS, int NW, bool OUT>
-__device__ __forceinline__ void mlp_rows(bf16* lds, bf16* mem, int dp, int nrows) {
+__device__ __forceinline__ void mlp_rows(bf16* lds, bf16* mem, int dp, int ld, int nrows) {
   const int l = threadIdx.x & 63, k = 8 * (l & 31);
   for (int r = 2 * (threadIdx.x >> 6) + (l >> 5); r < ROWS; r += 2 * NW) {
     if (k >= dp) continue;
     if constexpr (OUT) {
-      if (r < nrows) *(v8bf*)(mem + (long long)r * dp + k) = *(const v8bf*)(lds + r * FLD + k);
+      if (r < nrows) *(v8bf*)(mem + (long long)r * ld + k) = *(const v8bf*)(lds + r * FLD + k);
     } else {
       v8bf v = {};
-      if (r < nrows) v = *(const v8bf*)(mem + (long long)r * dp + k);
+      if (r < nrows) v = *(const v8bf*)(mem + (long long)r * ld + k);
       *(v8bf*)(lds + r * FLD + k) = v;
     }
   }
@@ -375,7 +378,7 @@ __device__ __forceinline__ void mlp_block(const MlpArgs& g, const TrainArgs& h, 
     if constexpr (TRAIN)                         // this layer's input, the network's (alike for all members) once
       if (L > 0 || mem == 0)
         mlp_rows<ROWS, NW, true>(act, h.act[L] + (L > 0 ? mem * (long long)h.rows * g.dp[L] : 0) + (long long)m0 * g.dp[L],
-                                 g.dp[L], nrows);
+                                 g.dp[L], g.dp[L], nrows);
     v16f acc[FT][RT];
     product(acc, Wm + g.woff[L], g.dp[L] >> 4, NF);
     if constexpr (TRAIN) {
@@ -428,15 +431,16 @@ __device__ __forceinline__ void mlp_block(const MlpArgs& g, const TrainArgs& h, 
   if constexpr (TRAIN)
     if (g.L > 1 || mem == 0)
       mlp_rows<ROWS, NW, true>(act, h.act[g.L - 1] + (g.L > 1 ? mem * (long long)h.rows * g.dp[g.L - 1] : 0) +
-                               (long long)m0 * g.dp[g.L - 1], g.dp[g.L - 1], nrows);
-  bf16* dzo = TRAIN ? h.dz[g.L - 1] + (mem * (long long)h.rows + m0) * dpo : nullptr;
+                               (long long)m0 * g.dp[g.L - 1], g.dp[g.L - 1], g.dp[g.L - 1], nrows);
+  const int ldo = 2 * dpo;                       // rows of the output gradient
+  bf16* dzo = TRAIN ? (bf16*)h.Z[g.L - 1] + (mem * (long long)h.rows + m0) * ldo : nullptr;
   float sq = 0.0f;                               // training: squared errors of this lane
   for (int it = w; it < (TRAIN ? dpo >> 5 : NF) * RT; it += NW) {
     const int ft = it / RT, c = it % RT;
     if (TRAIN && ft >= NF) {                     // padding columns
       if (32 * c < nrows)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) *(v4bf*)(dzo + (32 * c + lr) * dpo + 32 * ft + 8 * q + lf) = (v4bf){};
+        for (int q = 0; q < 4; ++q) *(v4bf*)(dzo + (32 * c + lr) * ldo + 32 * ft + 8 * q + lf) = (v4bf){};
       continue;
     }
     const bf16* W0 = Wm + g.woff[g.L - 1] + ((long long)ft * KS * 64 + l) * 8;
@@ -466,7 +470,7 @@ __device__ __forceinline__ void mlp_block(const MlpArgs& g, const TrainArgs& h, 
           sq += r * r;
           d[e] = (bf16)(2.0f * r * h.inv);
         }
-        if (32 * c < nrows) *(v4bf*)(dzo + (32 * c + lr) * dpo + 32 * ft + 8 * q + lf) = d;
+        if (32 * c < nrows) *(v4bf*)(dzo + (32 * c + lr) * ldo + 32 * ft + 8 * q + lf) = d;
       }
     } else if (m < g.B) {
 #pragma unroll
@@ -492,7 +496,7 @@ __device__ __forceinline__ void mlp_block(const MlpArgs& g, const TrainArgs& h, 
       for (int q = 0; q < NW; ++q) v += sums[q];
       h.lpart[(long long)mem * gridDim.x + blockIdx.x] = v;
     }
-    if (g.L > 1) mlp_rows<ROWS, NW, false>(act, dzo, dpo, nrows);
+    if (g.L > 1) mlp_rows<ROWS, NW, false>(act, dzo, dpo, ldo, nrows);
     __syncthreads();
 #pragma unroll 1
     for (int L = g.L - 1; L >= 1; --L) {         // dZ_{L-1} = (dZ_L W_L^T) * SiLU'(Z_{L-1})
@@ -534,7 +538,7 @@ __device__ __forceinline__ void mlp_block(const MlpArgs& g, const TrainArgs& h, 
       back([&](float y) { const float d = silu_grad_fast(y); bad = fmaf(d, 0.0f, bad); return d; });
       if (__any(!(bad == 0.0f))) back([](float y) { return silu_grad(y); });
       __syncthreads();
-      mlp_rows<ROWS, NW, true>(act, h.dz[L - 1] + (mem * (long long)h.rows + m0) * g.dp[L], g.dp[L], nrows);
+      mlp_rows<ROWS, NW, true>(act, (bf16*)h.Z[L - 1] + (mem * (long long)h.rows + m0) * 2 * g.dp[L], g.dp[L], 2 * g.dp[L], nrows);
     }
   }
 }
