@@ -411,51 +411,6 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
   return r;
 }
 
-template <int NT>
-__device__ __forceinline__ long long block_sum_ll(long long v, long long* sh) {
-  const int t = threadIdx.x;
-  sh[t] = v;
-  __syncthreads();
-#pragma unroll
-  for (int s = NT / 2; s > 0; s >>= 1) {
-    if (t < s) sh[t] += sh[t + s];
-    __syncthreads();
-  }
-  const long long r = sh[0];
-  __syncthreads();
-  return r;
-}
-
-template <int NT>
-__device__ __forceinline__ float block_max(float v, float* sh) {
-  const int t = threadIdx.x;
-  sh[t] = v;
-  __syncthreads();
-#pragma unroll
-  for (int s = NT / 2; s > 0; s >>= 1) {
-    if (t < s) sh[t] = fmaxf(sh[t], sh[t + s]);
-    __syncthreads();
-  }
-  const float r = sh[0];
-  __syncthreads();
-  return r;
-}
-
-template <int NT>
-__device__ __forceinline__ int block_min_i(int v, int* sh) {
-  const int t = threadIdx.x;
-  sh[t] = v;
-  __syncthreads();
-#pragma unroll
-  for (int s = NT / 2; s > 0; s >>= 1) {
-    if (t < s) sh[t] = min(sh[t], sh[t + s]);
-    __syncthreads();
-  }
-  const int r = sh[0];
-  __syncthreads();
-  return r;
-}
-
 // reduce a value across the TPA consecutive lanes that share one atom (result in every lane)
 template <int TPA, class T>
 __device__ __forceinline__ T lane_sum(T v) {

@@ -272,7 +272,9 @@ __device__ __forceinline__ float silu_grad_fast(float z) {
 
 template <int RT, int NW, bool TRAIN>
 __device__ __forceinline__ void mlp_block(const MlpArgs& g, const TrainArgs& h, bf16* act) {
-  constexpr int ROWS = 32 * RT, FT = (FW / 32) / NW;   // FT feature tiles per wave at most
+  // FT feature tiles per wave at most: one with the eight waves of every instance.  (Without the loops over f
+  // k_mlp_train<1, 8> takes 134 registers instead of 118, and a CU holds one block of it instead of two.)
+  constexpr int ROWS = 32 * RT, FT = (FW / 32) / NW;
   const int mem = blockIdx.y, m0 = blockIdx.x * ROWS;
   const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = t & 63;
   const int lr = l & 31, lk = 8 * (l >> 5), lf = 4 * (l >> 5);
