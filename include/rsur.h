@@ -75,7 +75,8 @@ int rsur_forward_members(rsur_ctx* ctx, const void* X_dev, int32_t B, void* out_
 
 /* One Adam step of every member on the same minibatch (raw X_dev B x din, raw Y_dev B x dout,
  * FP32), learning rate lr.  loss: host array of K floats receiving each member's MSE on the
- * normalised outputs before the step (synchronises), or NULL (enqueue only).  The reductions over
+ * normalised outputs before the step (synchronises), or NULL (enqueue only: X_dev and Y_dev are
+ * read after the call returns, and must keep until then).  The reductions over
  * the minibatch (weight and bias gradients, loss) are split over blocks for large B and their
  * partial sums added in a fixed order, so a step is reproducible bit for bit. */
 int rsur_train_step(rsur_ctx* ctx, const void* X_dev, const void* Y_dev, int32_t B, float lr, float* loss);

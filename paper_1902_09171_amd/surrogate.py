@@ -109,8 +109,10 @@ def train(torch, net, X, Y, steps, batch=1024, lr=1e-3, seed=0, lr_final=None, l
     net.fit_norm(Xd.data_ptr(), Yd.data_ptr(), len(X))
     gen = torch.Generator(device="cuda").manual_seed(int(seed))
     b = min(batch, len(X), net.max_batch)
-    xb = torch.empty((b, X.shape[1]), dtype=torch.float32, device="cuda")
-    yb = torch.empty((b, Y.shape[1]), dtype=torch.float32, device="cuda")
+    # Two minibatches in turn: a step is only enqueued, on the context's stream, and reads its batch while the
+    # next one is gathered on torch's.  The wait for that gather is also the wait for the step.
+    xb = torch.empty((2, b, X.shape[1]), dtype=torch.float32, device="cuda")
+    yb = torch.empty((2, b, Y.shape[1]), dtype=torch.float32, device="cuda")
     per_epoch = len(X) // b
     perm = None
     losses = []
@@ -118,12 +120,13 @@ def train(torch, net, X, Y, steps, batch=1024, lr=1e-3, seed=0, lr_final=None, l
         if t % per_epoch == 0:
             perm = torch.randperm(len(X), generator=gen, device="cuda")
         idx = perm[(t % per_epoch) * b:(t % per_epoch + 1) * b]
-        torch.index_select(Xd, 0, idx, out=xb)
-        torch.index_select(Yd, 0, idx, out=yb)
+        xt, yt = xb[t % 2], yb[t % 2]
+        torch.index_select(Xd, 0, idx, out=xt)
+        torch.index_select(Yd, 0, idx, out=yt)
         torch.cuda.synchronize()
         rate = lr if lr_final is None else lr * (lr_final / lr) ** (t / max(steps - 1, 1))
         want = log_every and (t % log_every == 0 or t == steps - 1)
-        loss = net.train_step(xb.data_ptr(), yb.data_ptr(), b, rate, want_loss=bool(want))
+        loss = net.train_step(xt.data_ptr(), yt.data_ptr(), b, rate, want_loss=bool(want))
         if want:
             losses.append((t, float(np.mean(loss))))
     torch.cuda.synchronize()
@@ -136,8 +139,8 @@ def predict(torch, net, X):
     for lo in range(0, len(X), net.max_batch):
         xs = X[lo:lo + net.max_batch]
         Xd = torch.tensor(xs.astype(np.float32), device="cuda")
-        m = torch.zeros((len(xs), net.dout), dtype=torch.float32, device="cuda")
-        v = torch.zeros_like(m)
+        m = torch.empty((len(xs), net.dout), dtype=torch.float32, device="cuda")   # no fill on torch's stream, which
+        v = torch.empty_like(m)                                                    # the context's does not wait for
         net.forward(Xd.data_ptr(), len(xs), m.data_ptr(), v.data_ptr())
         torch.cuda.synchronize()
         mean.append(m.cpu().numpy())
