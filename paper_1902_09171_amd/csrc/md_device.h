@@ -450,30 +450,6 @@ struct TailIn {                   // the atom's own data, requested ahead of the
     if (step) sb = a.sb[i];
   }
 };
-// The same for a block of one wave (its pass is short of waves, ~5 per SIMD), copied from memory straight into LDS while the pair loop runs: no
-// registers are held for it, and its round trip to memory is over when the pairs are.  Every piece
-// is read as 16 bytes per lane, two arrays at a time; the arrays have room for the few elements
-// past a ragged tile's end.
-struct TileLds {
-  double vx[TILE], vy[TILE], vz[TILE];
-  uint2 sb[TILE], bond[TILE];
-  int gid[2 * TILE];
-  double x[3][TILE];
-};
-__device__ __forceinline__ void lds_copy(const void* src, void* dst, bool on) {
-  if (on)
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                     (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
-}
-__device__ __forceinline__ void tile_prefetch(const MDArgs& a, const Tile& t, TileLds& L) {
-  const int ln = (int)threadIdx.x, h = ln & 31;
-  const bool hi = ln >= 32, on = 2 * h < t.count;          // 16 bytes: two elements of 8
-  const size_t o = (size_t)t.begin * 8 + 16 * (size_t)h;
-  lds_copy((const char*)(hi ? a.vy : a.vx) + o, L.vx, on);
-  lds_copy((hi ? (const char*)a.sb : (const char*)a.vz) + o, L.vz, on);
-  lds_copy(hi ? (const char*)a.gid + (size_t)t.begin * 4 + 16 * (size_t)h : (const char*)a.bond + o, L.bond,
-           hi ? 4 * h < t.count : on);
-}
 
 struct TailOut {
   double K[6];
@@ -885,10 +861,7 @@ template <class P, int TPA, class LT, bool MID>
 __global__ __launch_bounds__(TILE * TPA) void k_force_kg(MDArgs a, int mode_) {
   using R = typename P::R;
   constexpr int NT = TILE * TPA;
-  constexpr bool LDS_TAIL = TPA == 1 && sizeof(LT) == 2;
   __shared__ PartShared<NT / 64> psh;
-  __shared__ __attribute__((aligned(16))) char tile_mem[LDS_TAIL ? sizeof(TileLds) : 16];
-  TileLds& L = *(TileLds*)tile_mem;
   __shared__ __attribute__((aligned(16))) PruneBuf<NT, LT> pbuf;
   const int mode = MID ? (int)MODE_STEP : mode_;
   const int tb = block_tile_xcd(a.ntiles, blockIdx.x);
@@ -906,9 +879,6 @@ __global__ __launch_bounds__(TILE * TPA) void k_force_kg(MDArgs a, int mode_) {
   double w[6] = {0, 0, 0, 0, 0, 0};
   TailIn in;
   int status = 0;
-  if constexpr (LDS_TAIL) {
-    if (!skip) tile_prefetch(a, t, L);
-  }
   if (active) {
     // the atom's own fixed-point coordinates are recomputed from its position (they are stored only
     // for the neighbours' gathers): the position is read here for the drift anyway
@@ -921,10 +891,6 @@ __global__ __launch_bounds__(TILE * TPA) void k_force_kg(MDArgs a, int mode_) {
     auto pairs = [&](auto&& walk, auto&& out) {
       si = fixed_pos<P>(ck, in.x[0], in.x[1], in.x[2]);
       walk.nx.arrived();
-      if constexpr (LDS_TAIL) {
-#pragma unroll
-        for (int q = 0; q < 3; ++q) L.x[q][slot] = in.x[q];
-      }
       while (walk.more()) {
         typename P::S sj[UNR];
         bool ok[UNR];
@@ -961,10 +927,9 @@ __global__ __launch_bounds__(TILE * TPA) void k_force_kg(MDArgs a, int mode_) {
     if (lane == 0) {
       const int li = (int)(i - coff);
       int bp[4];
-      if constexpr (LDS_TAIL) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): the copies into LDS have landed
-      else in.load(a, i, mode == MODE_STEP);
+      in.load(a, i, mode == MODE_STEP);
       if constexpr (sizeof(LT) == 2) {
-        const uint2 b = LDS_TAIL ? L.bond[slot] : ((const uint2*)a.bond)[i];
+        const uint2 b = ((const uint2*)a.bond)[i];
         bp[0] = (int)(b.x & 0xffffu); bp[1] = (int)(b.x >> 16); bp[2] = (int)(b.y & 0xffffu); bp[3] = (int)(b.y >> 16);
       } else {
         const int4 b = ((const int4*)a.bond)[i];
@@ -993,13 +958,6 @@ __global__ __launch_bounds__(TILE * TPA) void k_force_kg(MDArgs a, int mode_) {
         const typename P::S b2 = P::load_rel(sc, bp[2]), b3 = P::load_rel(sc, bp[3]);
         fene(bp[2], b2);
         fene(bp[3], b3);
-      }
-      if constexpr (LDS_TAIL) {
-        in.v[0] = L.vx[slot]; in.v[1] = L.vy[slot]; in.v[2] = L.vz[slot];
-        in.sb = L.sb[slot];
-        in.gid = L.gid[slot];
-#pragma unroll
-        for (int q = 0; q < 3; ++q) in.x[q] = L.x[q][slot];
       }
     }
   }

@@ -787,14 +787,13 @@ int rcell_create(const rcell_params* params, const rcell_cell_init* cells, int32
   const size_t ssz = c->fp64 ? sizeof(S64) : sizeof(int4);
   int e;
   char *f0, *f1, *f2, *s0, *s1, *bondp;
-  const long long Nr = N + 4;      // room for the 16-byte reads at a ragged tile's end (tile_prefetch)
   if ((e = dalloc(c, &c->x, N)) || (e = dalloc(c, &c->y, N)) || (e = dalloc(c, &c->z, N)) ||
-      (e = dalloc(c, &c->vx, Nr)) || (e = dalloc(c, &c->vy, Nr)) || (e = dalloc(c, &c->vz, Nr)) ||
+      (e = dalloc(c, &c->vx, N)) || (e = dalloc(c, &c->vy, N)) || (e = dalloc(c, &c->vz, N)) ||
       (e = dalloc(c, &f0, fsz * N)) || (e = dalloc(c, &f1, fsz * N)) || (e = dalloc(c, &f2, fsz * N)) ||
       (e = dalloc(c, &s0, ssz * N)) || (e = dalloc(c, &s1, ssz * N)) ||
-      (e = dalloc(c, &c->sb, Nr)) || (e = dalloc(c, &bondp, (c->list16 ? 8 : 16) * (size_t)Nr)) ||
+      (e = dalloc(c, &c->sb, N)) || (e = dalloc(c, &bondp, (c->list16 ? 8 : 16) * (size_t)N)) ||
       (e = dalloc(c, &c->bond0, N)) ||
-      (e = dalloc(c, &c->gid, Nr)) || (e = dalloc(c, &c->pos_of, N)) ||
+      (e = dalloc(c, &c->gid, N)) || (e = dalloc(c, &c->pos_of, N)) ||
       (e = dalloc(c, &c->pscr, (6 * sizeof(double) + ssz + 2 * sizeof(int)) * (size_t)c->npad)) ||
       (e = dalloc(c, &c->nn, N)) ||
       (e = dalloc(c, &c->abin, N)) || (e = dalloc(c, &c->binned, N)) || (e = dalloc(c, &c->bkey, N)) ||
