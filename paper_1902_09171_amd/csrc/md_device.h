@@ -755,10 +755,12 @@ struct NbrWalk {
 // A pair left out was at least sqrt(prune_rc2) apart, so the list is complete while no atom has moved
 // further than (sqrt(prune_rc2) - rc) / 2 since: every step adds its largest displacement to the
 // cell's pmove, and past prune_move the cell's next pass prunes again (reduce_cell).
-// Kremer-Grest lists shrink from ~21 entries to ~9 this way, copper's from 237 to ~140.  A pass over 5.1 M
-// Kremer-Grest beads takes 269 us on the pruned list and 450 where it writes it, 330 on the average of a
-// run, against 398 on the full list; copper's two passes over 512 000 atoms 105 + 152 against 129 + 194.
-// Pruning in a walk of its own before the forces (FP32 distances only) was slower: 590 us.
+// Kremer-Grest lists shrink from ~21 entries to ~9 this way, copper's from 237 to ~140.  Traced, a pass over 5.1 M
+// Kremer-Grest beads (skin 0.7) takes 261 us on the pruned list and 400 where it writes it, 321 on the average of
+// a run, against 376 without a pruned list; copper's two passes over 512 000 atoms 84 + 133 us and 212 + 138
+// where the first writes, 98 + 140 on average, against 117 + 175.  A cell whose fastest atom uses the margin up
+// in every step pays for writing each time, 6 % of such a Kremer-Grest pass.
+// Pruning in a walk of its own before the forces (FP32 distances only) was slower.
 template <class P, int TPA, class LT>
 struct PruneWalk {
   const LT* p;

@@ -496,7 +496,7 @@ int layout_bins(rcell_ctx* c, const std::vector<int>& need) {
   long long total = 0;
   std::vector<int> off(c->ncells), cap(c->ncells);
   for (int k = 0; k < c->ncells; ++k) {
-    // whole 64-entry pieces per cell
+    // rounded up, so that small changes of a box find room
     cap[k] = (std::max(need[k], c->bin_cap.empty() ? 0 : c->bin_cap[k]) + 63) / 64 * 64;
     off[k] = (int)total;
     total += cap[k];

@@ -19,7 +19,7 @@ enum Epi : int { EPI_FWD_HIDDEN = 0, EPI_FWD_OUT = 1, EPI_BWD_DA = 2, EPI_BWD_DW
 struct GemmArgs {
   const bf16* A; long long lda, sA;        // operand A, row stride, member stride
   const bf16* B; long long ldb, sB;
-  int M, N, K;                             // C is M x N, reduction over K (multiples of 64/64/32)
+  int M, N, K;                             // C is M x N, reduction over K (multiples of 64, K / ksplit too)
   const float* bias; long long sBias;
   float* Z; long long ldz, sZ;             // FP32 result (pre-activation, output or gradient)
   bf16* O; long long ldo, sO;              // BF16 result (activation or backpropagated gradient)
@@ -194,10 +194,10 @@ __global__ __launch_bounds__(256) void k_dw(DwArgs d) {
 //
 // Bound: per block of 128 rows the matrix products take ~16 000 cycles of every SIMD (32 each) and SiLU
 // ~25 000 (12 instructions, two of them transcendental, per 64 elements); two blocks per CU run them side by
-// side.  Measured (one MI355X, 153 -> 4 x 256 -> 6, 5 members): 60 001 rows 255 us, 683 with 64 rows per block,
-// a transposed weight copy, a full division and inputs normalised one load at a time (304 us with four
-// waves of two tiles instead of eight of one, 288 in the end); 256 rows 15.8 us, ~44 layer by layer in
-// six launches.
+// side.  Measured (one MI355X, 153 -> 4 x 256 -> 6, 5 members), this kernel alone, traced, which slows it: 60 001 rows
+// 266 us, 683 with 64 rows per block, a transposed weight copy, a full division and inputs normalised one load at a
+// time (four waves of two tiles instead of eight of one 13 % more); 256 rows 15.8 us, ~44 layer by layer in six
+// launches.  Untraced, with the ensemble mean behind it, a call among others takes 214-224 and 8.6 us.
 constexpr int FW = 256, FLD = FW + 8;
 
 struct MlpArgs {
