@@ -2007,12 +2007,17 @@ struct BinHead {                   // a span's atoms and stencil, and this lane'
 };
 
 // bins (x, y, z0) to (x, y, z1) of cell C: their atoms, and the candidate range of every lane below nrange
+template <bool SPANS>
 __device__ __forceinline__ BinHead bin_head(const MDArgs& a, const CellDev& C, int x, int y, int z0, int z1) {
   const int lane = (int)(threadIdx.x & 63u), col = C.bin_off + (x * C.nb[1] + y) * C.nb[2];
   BinHead h;
   h.first = a.bstart[col + z0];
-  const bool last = x + 1 == C.nb[0] && y + 1 == C.nb[1] && z1 + 1 == C.nb[2];
-  h.m = (last ? C.n : a.bstart[col + z1 + 1]) - h.first;
+  if constexpr (SPANS) {           // (the last bin's start and count instead take a wave per SIMD, in registers)
+    const bool last = x + 1 == C.nb[0] && y + 1 == C.nb[1] && z1 + 1 == C.nb[2];
+    h.m = (last ? C.n : a.bstart[col + z1 + 1]) - h.first;
+  } else {
+    h.m = a.bnum[col + z0];
+  }
   BuildGeo G;
   const int bb[3] = {x, y, z0};
   build_geo(C, bb, z1, a.bin_factor, G);
@@ -2135,8 +2140,8 @@ __device__ __forceinline__ void build_span(const MDArgs& a, int cell, const BinH
 }
 
 // `run` consecutive spans of one cell from its span b0, of `len` bins each but the last of a column, the next
-// span's ranges requested before a span's candidates are tested
-template <class P, class LT>
+// span's ranges requested before a span's candidates are tested (SPANS: len may be more than one)
+template <class P, class LT, bool SPANS>
 __device__ __forceinline__ void build_run(const MDArgs& a, int cell, int b0, int run, int len, int ns, int part, int nparts,
                                           const typename P::S* s, BinRanges& rg) {
   const CellDev& C = a.cells[cell];
@@ -2144,12 +2149,13 @@ __device__ __forceinline__ void build_run(const MDArgs& a, int cell, int b0, int
   const bool local = min(min(nb0, nb1), nb2) >= 2 * a.bin_factor + 3;
   int z = b0 % ns * len, t = b0 / ns;
   int y = t % nb1, x = t / nb1;
-  BinHead cur = bin_head(a, C, x, y, z, min(z + len, nb2) - 1);
+  auto head = [&] { return bin_head<SPANS>(a, C, x, y, z, SPANS ? min(z + len, nb2) - 1 : z); };
+  BinHead cur = head();
   for (int e = 0; e < run; ++e) {
     z += len;
     if (z >= nb2) { z = 0; if (++y == nb1) { y = 0; ++x; } }
     BinHead nxt = cur;
-    if (e + 1 < run) nxt = bin_head(a, C, x, y, z, min(z + len, nb2) - 1);
+    if (e + 1 < run) nxt = head();
     if (local) build_span<P, LT, true>(a, cell, cur, part, nparts, s, rg);
     else build_span<P, LT, false>(a, cell, cur, part, nparts, s, rg);
     cur = nxt;
@@ -2166,7 +2172,9 @@ __device__ __forceinline__ void build_run(const MDArgs& a, int cell, int b0, int
 // Measured on one MI355X, per MD step, against one lane per atom (sets of 4096 tiles and more) and eight
 // lanes per atom walking the candidate ranges: 100 cells of 10^4 beads 62.6 -> 37.1 us, 50 glassy
 // cells 102 -> 54 us, 128 cells of 40 000 beads 205 -> 147 us (all 5.1 M beads at once 2.19 -> 1.57 ms).
-template <class P, class LT>
+// SPANS: batches with a cell whose bins are few atoms (set_occupancy); the others keep the shorter code, 2 % of a
+// build of 5.1 M beads.
+template <class P, class LT, bool SPANS>
 __global__ __launch_bounds__(64 * BLD_WAVES) void k_build_list(MDArgs a, int scatter, int lparts) {
   __shared__ BinRanges rg[BLD_WAVES];
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -2188,17 +2196,18 @@ __global__ __launch_bounds__(64 * BLD_WAVES) void k_build_list(MDArgs a, int sca
     const int q = it - (__builtin_amdgcn_readfirstlane(a.work_tstart[w]) << lsplit);
     const CellDev& C = a.cells[cell];
     const int nb2 = C.nb[2], cols = C.nb[0] * C.nb[1];
-    int len = min(C.span, (int)((float)ntl * C.span_rate)), ns = nb2;
-    if (len > 1) {                 // about equal in a column
-      ns = (nb2 + len - 1) / len;
-      len = (nb2 + ns - 1) / ns;
-      ns = (nb2 + len - 1) / len;
-    } else {
-      len = 1;
+    int len = 1, ns = nb2;
+    if constexpr (SPANS) {
+      len = max(1, min(C.span, (int)((float)ntl * C.span_rate)));
+      if (len > 1) {               // about equal in a column
+        ns = (nb2 + len - 1) / len;
+        len = (nb2 + ns - 1) / ns;
+        ns = (nb2 + len - 1) / len;
+      }
     }
     const unsigned nu = (unsigned)(cols * ns), nq = (unsigned)C.ntile << lsplit;
     const int b0 = (int)((unsigned long long)q * nu / nq), b1 = (int)((unsigned long long)(q + 1) * nu / nq);
-    if (b1 > b0) build_run<P, LT>(a, cell, b0, b1 - b0, len, ns, part, 1 << lparts, s, rg[wave]);
+    if (b1 > b0) build_run<P, LT, SPANS>(a, cell, b0, b1 - b0, len, ns, part, 1 << lparts, s, rg[wave]);
   }
 }
 

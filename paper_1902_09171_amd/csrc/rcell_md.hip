@@ -74,6 +74,7 @@ struct rcell_ctx {
   double fire_ftol2 = 0.0;        // statics: convergence threshold and move limit of the current call
   int fire_max_iter = 0;
   int build_lparts = 0;           // log2 of the list build's waves per bin
+  bool build_spans = true;        // a cell's bins are so empty that a wave may take several (list_span)
   // device memory
   double *x = nullptr, *y = nullptr, *z = nullptr, *vx = nullptr, *vy = nullptr, *vz = nullptr;
   void *fx = nullptr, *fy = nullptr, *fz = nullptr;
@@ -127,15 +128,18 @@ void drop_graphs(rcell_ctx* c) {
 
 // Waves of the list build per bin: one up to ~10 atoms per bin (Kremer-Grest: 4-6), where a bin's
 // candidates fit in registers and are read once; more for fuller bins, whose atoms are shared out so
-// that a cell still gives enough waves.  A change invalidates the captured graphs.
+// that a cell still gives enough waves.  Several bins per wave where two have their candidates in one register
+// tile (list_span).  A change invalidates the captured graphs.
 void set_occupancy(rcell_ctx* c, int cell, double atoms_per_bin) {
   c->occ[cell] = atoms_per_bin;
-  double m = 0.0;
-  for (double o : c->occ) m = std::max(m, o);
-  const int lp = m <= 10.0 ? 0 : m <= 24.0 ? 1 : 3;
-  if (lp != c->build_lparts) {
+  double m = 0.0, least = atoms_per_bin;
+  for (double o : c->occ) { m = std::max(m, o); least = std::min(least, o); }
+  const int lp = m <= 10.0 ? 0 : m <= 24.0 ? 1 : 3, f = c->bin_factor;
+  const bool spans = least * (2 * f + 1) * (2 * f + 1) * (2 * f + 2) <= SPAN_CAND * 1.01;
+  if (lp != c->build_lparts || spans != c->build_spans) {
     drop_graphs(c);
     c->build_lparts = lp;
+    c->build_spans = spans;
   }
 }
 
@@ -416,9 +420,14 @@ void launch_build(rcell_ctx* c, int reduce_mode = -1) {
   const int scatter = c->cell_prep ? 0 : 1, lp = c->build_lparts;
   const long long items = (long long)c->ntiles << (lp ? 3 : 4);
   const dim3 gl(round8((int)std::min<long long>(WORK_BLOCKS, (items + BLD_WAVES - 1) / BLD_WAVES))), bl(64 * BLD_WAVES);
-  if (c->fp64) hipLaunchKernelGGL((k_build_list<FP64, int>), gl, bl, 0, c->stream, a, scatter, lp);
-  else if (c->list16) hipLaunchKernelGGL((k_build_list<Mixed, uint16_t>), gl, bl, 0, c->stream, a, scatter, lp);
-  else hipLaunchKernelGGL((k_build_list<Mixed, int>), gl, bl, 0, c->stream, a, scatter, lp);
+  auto lists = [&](auto spans) {
+    constexpr bool S = decltype(spans)::value;
+    if (c->fp64) hipLaunchKernelGGL((k_build_list<FP64, int, S>), gl, bl, 0, c->stream, a, scatter, lp);
+    else if (c->list16) hipLaunchKernelGGL((k_build_list<Mixed, uint16_t, S>), gl, bl, 0, c->stream, a, scatter, lp);
+    else hipLaunchKernelGGL((k_build_list<Mixed, int, S>), gl, bl, 0, c->stream, a, scatter, lp);
+  };
+  if (c->build_spans) lists(std::true_type());
+  else lists(std::false_type());
 }
 
 void launch_start(rcell_ctx* c) {
@@ -668,6 +677,7 @@ int apply_bin_factor(rcell_ctx* c, int f) {
   HIPCHK(c, hipMemcpyAsync(hc.data(), c->cells, sizeof(CellDev) * nc, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   const double bw = (c->p.rc + c->p.skin) / f;
+  c->bin_factor = f;
   std::vector<int> need(nc);
   bool grow = false;
   for (int k = 0; k < nc; ++k) {
@@ -676,7 +686,6 @@ int apply_bin_factor(rcell_ctx* c, int f) {
     grow = grow || need[k] > c->bin_cap[k];
   }
   drop_graphs(c);                                  // the captured steps carry the bin factor
-  c->bin_factor = f;
   int e;
   if (grow && (e = layout_bins(c, need))) return e;
   hipLaunchKernelGGL(k_set_bin_width, dim3((nc + 63) / 64), dim3(64), 0, c->stream, c->cells, nc, bw);
