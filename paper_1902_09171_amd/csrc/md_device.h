@@ -2172,7 +2172,7 @@ __device__ __forceinline__ void build_run(const MDArgs& a, int cell, int b0, int
 // Measured on one MI355X, per MD step, against one lane per atom (sets of 4096 tiles and more) and eight
 // lanes per atom walking the candidate ranges: 100 cells of 10^4 beads 62.6 -> 37.1 us, 50 glassy
 // cells 102 -> 54 us, 128 cells of 40 000 beads 205 -> 147 us (all 5.1 M beads at once 2.19 -> 1.57 ms).
-// SPANS: batches with a cell whose bins are few atoms (set_occupancy); the others keep the shorter code, 2 % of a
+// SPANS: batches with a cell whose bins are few atoms (set_build_shape); the others keep the shorter code, 2 % of a
 // build of 5.1 M beads.
 template <class P, class LT, bool SPANS>
 __global__ __launch_bounds__(64 * BLD_WAVES) void k_build_list(MDArgs a, int scatter, int lparts) {

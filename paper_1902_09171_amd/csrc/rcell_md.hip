@@ -74,7 +74,7 @@ struct rcell_ctx {
   double fire_ftol2 = 0.0;        // statics: convergence threshold and move limit of the current call
   int fire_max_iter = 0;
   int build_lparts = 0;           // log2 of the list build's waves per bin
-  bool build_spans = true;        // a cell's bins are so empty that a wave may take several (list_span)
+  bool build_spans = false;       // a cell's bins are so empty that a wave may take several (list_span)
   // device memory
   double *x = nullptr, *y = nullptr, *z = nullptr, *vx = nullptr, *vy = nullptr, *vz = nullptr;
   void *fx = nullptr, *fy = nullptr, *fz = nullptr;
@@ -126,16 +126,17 @@ void drop_graphs(rcell_ctx* c) {
     if (c->graph[q]) { (void)hipGraphExecDestroy(c->graph[q]); c->graph[q] = nullptr; }
 }
 
-// Waves of the list build per bin: one up to ~10 atoms per bin (Kremer-Grest: 4-6), where a bin's
-// candidates fit in registers and are read once; more for fuller bins, whose atoms are shared out so
-// that a cell still gives enough waves.  Several bins per wave where two have their candidates in one register
-// tile (list_span).  A change invalidates the captured graphs.
-void set_occupancy(rcell_ctx* c, int cell, double atoms_per_bin) {
-  c->occ[cell] = atoms_per_bin;
-  double m = 0.0, least = atoms_per_bin;
-  for (double o : c->occ) { m = std::max(m, o); least = std::min(least, o); }
-  const int lp = m <= 10.0 ? 0 : m <= 24.0 ? 1 : 3, f = c->bin_factor;
-  const bool spans = least * (2 * f + 1) * (2 * f + 1) * (2 * f + 2) <= SPAN_CAND * 1.01;
+// The list build's shape from the cells' atoms per bin (occ).  Waves per bin: one up to ~10 atoms
+// (Kremer-Grest: 4-6), where a bin's candidates fit in registers and are read once; more for fuller bins, whose
+// atoms are shared out so that a cell still gives enough waves.  Several bins per wave where two have their
+// candidates in one register tile (list_span), and until none is within a seventh of that: a change invalidates
+// the captured graphs, so a cell near the line should not cross it with every F.
+void set_build_shape(rcell_ctx* c) {
+  double most = 0.0, least = c->occ[0];
+  for (double o : c->occ) { most = std::max(most, o); least = std::min(least, o); }
+  const int lp = most <= 10.0 ? 0 : most <= 24.0 ? 1 : 3, f = c->bin_factor;
+  const double line = SPAN_CAND * (c->build_spans ? 1.15 : 1.01);
+  const bool spans = least * (2 * f + 1) * (2 * f + 1) * (2 * f + 2) <= line;
   if (lp != c->build_lparts || spans != c->build_spans) {
     drop_graphs(c);
     c->build_lparts = lp;
@@ -416,7 +417,7 @@ void launch_build(rcell_ctx* c, int reduce_mode = -1) {
     if (c->fp64) hipLaunchKernelGGL(k_reorder_gather<FP64>, gw, bw, 0, c->stream, a);
     else hipLaunchKernelGGL(k_reorder_gather<Mixed>, gw, bw, 0, c->stream, a);
   }
-  // the lists, one wave per bin or run of bins (more for full bins: set_occupancy)
+  // the lists, one wave per bin or run of bins (more for full bins: set_build_shape)
   const int scatter = c->cell_prep ? 0 : 1, lp = c->build_lparts;
   const long long items = (long long)c->ntiles << (lp ? 3 : 4);
   const dim3 gl(round8((int)std::min<long long>(WORK_BLOCKS, (items + BLD_WAVES - 1) / BLD_WAVES))), bl(64 * BLD_WAVES);
@@ -653,10 +654,11 @@ int deformation_common(rcell_ctx* c, const double* F_dev) {
   double dens = 0.0;
   bool grow = false;
   for (int k = 0; k < nc; ++k) {
-    set_occupancy(c, k, (double)c->n[k] / std::max(1, h.nbins[k]));
+    c->occ[k] = (double)c->n[k] / std::max(1, h.nbins[k]);
     grow = grow || h.nbins[k] > c->bin_cap[k];
     dens = std::max(dens, h.density[k]);
   }
+  set_build_shape(c);
   if (grow || dens > dens_ok) {
     int e;
     if (grow && (e = layout_bins(c, std::vector<int>(h.nbins, h.nbins + nc)))) return e;
@@ -682,9 +684,10 @@ int apply_bin_factor(rcell_ctx* c, int f) {
   bool grow = false;
   for (int k = 0; k < nc; ++k) {
     need[k] = bins_for(hc[k].H, bw);
-    set_occupancy(c, k, (double)c->n[k] / bins_exact(hc[k].H, bw));
+    c->occ[k] = (double)c->n[k] / bins_exact(hc[k].H, bw);
     grow = grow || need[k] > c->bin_cap[k];
   }
+  set_build_shape(c);
   drop_graphs(c);                                  // the captured steps carry the bin factor
   int e;
   if (grow && (e = layout_bins(c, need))) return e;
@@ -777,9 +780,9 @@ int rcell_create(const rcell_params* params, const rcell_cell_init* cells, int32
   c->small_cells = *std::max_element(c->n.begin(), c->n.end()) <= PREP_ATOMS;
   c->cell_prep = c->small_cells;
   c->ntiles = ntiles;
-  c->occ.assign(ncells, 0.0);
   for (int k = 0; k < ncells; ++k)
-    set_occupancy(c, k, (double)cells[k].natoms / bins_exact(cells[k].H0, rcs / c->bin_factor));
+    c->occ.push_back((double)cells[k].natoms / bins_exact(cells[k].H0, rcs / c->bin_factor));
+  set_build_shape(c);
 
   // ---- stream and memory
   if (hip_stream) {
@@ -1103,7 +1106,8 @@ int rcell_set_state(rcell_ctx* c, int32_t cell, const double* x, const double* v
   const long long o = c->off[cell], n = c->n[cell];
   std::vector<int> need(c->bin_cap);
   need[cell] = std::max(need[cell], bins_for(H, bin_width(c)));
-  set_occupancy(c, cell, (double)n / bins_exact(H, bin_width(c)));
+  c->occ[cell] = (double)n / bins_exact(H, bin_width(c));
+  set_build_shape(c);
   int e;
   if (need[cell] > c->bin_cap[cell] && (e = layout_bins(c, need))) return e;
   const int cap0 = c->maxnb;
